@@ -52,7 +52,7 @@ class _GreedyOpts(ctypes.Structure):
 
 def _load():
     if not os.path.exists(LIB_PATH):
-        raise ImportError(f"{LIB_PATH} is missing: build it with `python -m paper_2105_13336_amd.build` "
+        raise ImportError(f"{LIB_PATH} is missing: build it with `python paper_2105_13336_amd/build.py` "
                           "(there is no CPU fallback)")
     lib = ctypes.CDLL(LIB_PATH)
     lib.tensile_last_error.restype = ctypes.c_char_p
