@@ -130,7 +130,6 @@ def main() -> int:
     ap.add_argument("--print-sources-hash", action="store_true", help="print the hash that ties a counter summary to the kernel sources and exit")
     ap.add_argument("--no-greedy", action="store_true", help="skip the greedy-planner leg")
     ap.add_argument("--eval-only", action="store_true", help="steps run tensile_eval_plans alone (profiling aid)")
-    ap.add_argument("--fused", action="store_true", help="the one-call row forces the fused evaluation + scoring kernel (profiling aid)")
     ap.add_argument("--no-extras", action="store_true", help="skip the per-job and recomputation rows (profiling aid)")
     ap.add_argument("--ceilings", action="store_true",
                     help="instead of the benchmark: time plain fill / copy / reduction kernels over 6.55 GB and print them")
@@ -242,8 +241,6 @@ def main() -> int:
 
     if not args.eval_only:
         # the same step through the one-call entry point
-        if args.fused:
-            P.tensile_tuning_set("step_fused", 1)
         sc1, wo1, wi1 = torch.empty_like(sc), torch.empty_like(wo), torch.empty_like(wi)
         pk1, ar1, mn1 = torch.empty_like(peak), torch.empty_like(arg), torch.empty_like(mn)
         res1 = torch.empty_like(res)
@@ -259,7 +256,7 @@ def main() -> int:
         for x, y in ((res1, res), (pk1, peak), (ar1, arg), (mn1, mn), (sc1, sc), (wo1, wo), (wi1, wi)):
             assert torch.equal(x, y)
         out["rows"]["eval_score_plans"] = {"ms": ms1, "plan_timesteps_per_s": plan_timesteps / (ms1 * 1e-3),
-                                           "kernels": "one fused kernel (forced)" if args.fused else "evaluation, then scoring"}
+                                           "kernels": "evaluation, then scoring"}
         P.tensile_tuning_reset()
         del sc1, wo1, wi1, pk1, ar1, mn1, res1
 

@@ -362,10 +362,7 @@ int tensile_greedy_plan(const tensile_tas *tas, int64_t budget_bytes, const tens
  *   "eval_r"          intervals per thread kept in registers (0 = automatic)
  *   "score_blocks"    size of the scoring grid (0 = automatic)
  *   "link_packed"     0: search the cumulative latencies themselves even when their packed form exists (1 = automatic)
- *   "step_fused"      1: tensile_eval_score_plans takes each plan through evaluation and scoring in ONE kernel when the
- *                     batch has the shape for it (sizes in 32-bit units, T even and at most 131,072, 16-byte aligned
- *                     rows, plans of at most about 5,400 intervals on average); measured slower than the two kernels,
- *                     hence never chosen automatically (0 / -1: two kernels)
+ *   "step_fused"      accepted, without effect
  * TENSILE_E_INVAL for an unknown name. */
 int tensile_tuning_set(const char *knob, int value);
 

@@ -61,6 +61,7 @@ struct DevBuf {
 // Launch geometry of the evaluation kernel (see eval.hip).
 constexpr int kEvalThreads = 1024;
 constexpr int kEvalTile = 8192;   // steps per LDS difference tile
+constexpr int kScoreMini = 256;   // steps of a piece of the row in the scoring passes: 4 consecutive steps per lane
 
 // Arguments of the fused scatter + scan + reduce kernel.
 struct EvalArgs {
@@ -106,7 +107,6 @@ struct Workspace {
     DevBuf<int32_t> part_arg;
     DevBuf<unsigned long long> tail_flag;   // eval: see EvalArgs::tail_flag (zero when allocated, then monotone)
     unsigned long long epoch = 0;           // launches of the evaluation kernel through this workspace
-    DevBuf<int64_t> score_tab;     // score: per-workgroup sub-span maxima when they do not fit in LDS
     DevBuf<int32_t> job_arg;       // per-job evaluation: peak steps when the caller does not want them
     DevBuf<int2> bin_recs;         // eval, binned mode: see EvalArgs
     DevBuf<int32_t> bin_off;
@@ -147,7 +147,7 @@ struct Tuning {
     int eval_nt = -1;          // footprint rows written with nontemporal stores: 0 never, 1 always, -1 by row length
     int score_blocks = 0;      // size of the scoring grid
     int link_packed = 1;       // 0: search C itself even when its packed form exists
-    int step_fused = -1;       // tensile_eval_score_plans: 0 = two kernels, 1 = the fused kernel whenever its shape allows
+    int step_fused = -1;       // (no effect: the fused kernel it chose is gone)
 };
 extern Tuning g_tuning;
 
@@ -163,39 +163,28 @@ struct JobTables {
     DevBuf<uint32_t> units;            // [J][N] when the handle has 32-bit size units
 };
 
-// Geometry the scoring kernel shares with the index built at load time (see score.hip).
-constexpr int kScoreThreads = 1024;
-constexpr int kScoreWaves = kScoreThreads / 64;
-constexpr int kScoreMaxLocal = 3072;   // bucket entries one pass handles (a "slice"); larger buckets take several
-constexpr int kScoreStage = 192;       // tensors whose output (16 bytes each) one wavefront composes in LDS at a time
-constexpr int kScoreMini = 256;    // steps one wavefront takes up at a time (4 consecutive steps per lane)
+// What the scoring kernel shares with the index built at load time (see score.hip).
+constexpr int kScoreWaves = 8;         // wavefronts of the batch kernel's workgroup
+constexpr int kScoreStage = 128;       // tensors whose output (16 bytes each) one wavefront composes in LDS at a time
 
 // Candidate index: every gap (p, q) with a feasible earliest swap-out step o, filed under each
 // bucket of 2^shift steps that o+1 .. q-1 overlaps.  Per bucket (entries e0 .. e1-1, local
-// index = e - e0):
-//   cand / cand_size / cand_o   the entries sorted by o; slices are runs of kScoreMaxLocal of them
-//   qord                        per slice, its entries as {q, index within the slice} sorted by q
-//   tord                        per slice, its entries as {tensor, index within the slice} sorted by tensor
-//   wave_ptr[4][kScoreWaves+1]  per slice (slices numbered from slice_first[bucket]): rows 0-2 = first position
-//                               within the slice with o (resp. q) >= the w-th span boundary, tensor >= w * tspan,
-//                               per order; row 3 = the span boundaries themselves: first step of wavefront w's
-//                               part of the row (multiples of kScoreMini, the last one T), placed so that
-//                               steps and entries together are spread evenly over the wavefronts
-//   hash_dir / hash_slots       open-addressing table tensor -> {tensor, p, q, local | last << 31}
+// index = e - e0), in the order of (tensor, p):
+//   cand_oq / cand_tensor / cand_size   what the scoring pass reads of every entry
+//   cand_p / cand_gap           p, and the entry's gap: its number among the gaps of length >= 2 in tensor order
+//   wave_ptr[kScoreWaves]       first entry with tensor >= w * tspan
+//   hash_dir / hash_slots       open-addressing table tensor -> its first entry, {tensor, p, q, local | last << 31}
+//                               (last: the tensor has no other entry in the bucket)
 //   filter                      one bit per (tensor mod filter_bits): some entry has this tensor
 struct CandIndex {
     int32_t shift = 0, n_buckets = 0;
     int32_t tspan = kScoreStage;   // tensors per wavefront: ceil(N / kScoreWaves) rounded up to kScoreStage
     int32_t filter_words = 0;      // words per bucket, a power of two
-    int32_t max_bucket = 0;        // entries in the largest bucket
     DevBuf<int32_t> bucket_off;    // [n_buckets + 1]
-    DevBuf<int4> cand;
+    DevBuf<int2> cand_oq;
+    DevBuf<int32_t> cand_tensor, cand_p, cand_gap;
     DevBuf<int64_t> cand_size;
-    DevBuf<int32_t> cand_o;
-    DevBuf<int32_t> cand_gap;      // the entry's gap: its number among the gaps of length >= 2 in tensor order
-    DevBuf<int2> qord, tord;
-    DevBuf<int32_t> slice_first;   // [n_buckets + 1]
-    DevBuf<int32_t> wave_ptr;      // [slices][4][kScoreWaves + 1]
+    DevBuf<int32_t> wave_ptr;      // [n_buckets][kScoreWaves]
     DevBuf<int2> hash_dir;         // [n_buckets] {first slot, log2(slots)}
     DevBuf<int4> hash_slots;
     DevBuf<uint32_t> filter;       // [n_buckets][filter_words]
@@ -261,18 +250,12 @@ struct ScoreHeader {
 struct ScoreCand {
     int64_t score;
     int32_t tensor, wo, wi;
-    int32_t gap;                   // number of the candidate's gap (planner's kernel; -1 from the batch kernel's one-plan form)
+    int32_t gap;                   // number of the candidate's gap
 };
-// (any_interval: an interval of the entry's tensor cancels the entry wherever it lies, not only inside the gap.
-//  compact != null, B == 1 only: instead of the dense rows, one record per tensor with a window, in no
-//  particular order, behind *hdr = {peak, peak step, number of records}; score/win_out/win_in are not touched.
-//  hdr and compact may point into pinned host memory; with ready != null the kernel, once all of that is
-//  visible to the host, stores ready_value to *ready (system scope), so the host can wait for the word
-//  instead of the stream.)
+// (any_interval: an interval of the entry's tensor cancels the entry wherever it lies, not only inside the gap.)
 int launch_score(const tensile_tas *tas, Workspace &ws, const CandIndex &ix, bool any_interval, const tensile_plans *plans,
                  const int64_t *resident, const int64_t *peak, const int32_t *argmax, int64_t *score, int32_t *win_out,
-                 int32_t *win_in, ScoreHeader *hdr = nullptr, ScoreCand *compact = nullptr,
-                 unsigned long long *ready = nullptr, unsigned long long ready_value = 0);
+                 int32_t *win_in);
 // One iteration of the planner in one launch (score.hip: greedy_step_kernel).  fresh: the interval that joins the plan
 // (applied to the row, written to `position` of the plan's device arrays), or null.
 struct GreedyNew {

@@ -9,43 +9,36 @@
 // cumulative latency) and o < t* < q.  tensile_tas_load files every such gap
 // under each bucket of 2^shift steps that (o, q) overlaps, so a plan looks at the
 // one bucket of its t* (see CandIndex in common.h).  Everything a plan needs
-// beyond its own footprint row and interval list is static, shared by all plans
-// with the same bucket, and read in order; the row is read exactly once, in
-// order, and nothing per plan is kept in global memory (except, for rows longer
-// than 131,072 steps, one word per 256 steps).  The recomputation savings
-// (section IV-D) use the same kernel on a second index in which every gap is
-// filed with o = p, and any interval of a tensor cancels its entries.
+// beyond its own footprint row and interval list is static and shared by all plans
+// with the same bucket.  The recomputation savings (section IV-D) use the same
+// kernel on a second index in which every gap is filed with o = p, and any interval
+// of a tensor cancels its entries.
 //
-// One workgroup walks a plan at a time (persistent workgroups, plans dealt
-// round-robin).  Per plan, with acc[] one word per bucket entry in LDS:
-//   1. the plan's output rows are cleared (score 0, windows -1); acc = -inf;
-//   2. every wavefront streams its own contiguous span of the row, 256 steps at a
-//      time, four consecutive steps per lane.  With two wave-level scans it forms,
-//      per lane, the running maximum from the span's start up to the lane's steps
-//      and the maximum from after them to the end of the 256, and puts both, with
-//      the values themselves, in a small LDS buffer of its own; the entries whose
-//      o (resp. q) falls inside these 256 steps complete their value from the
-//      buffer and fold it into acc (atomic max).  Entries are met in order because
-//      the bucket is sorted by o, and a second list is sorted by q; both lists sit
-//      in LDS (reloaded only when the bucket changes) and the wavefront takes them
-//      up 64 at a time.  The maxima of the 256-step pieces go to a table
-//      (LDS), suffix-scanned within the span at the end;
-//   3. the plan's own intervals cancel candidates: an interval inside the gap of
-//      an entry of its tensor sets acc = +inf (Alg. 2 of the paper only takes tensors
-//      that are not swapped out yet).  A per-bucket bit filter over tensors, kept in LDS,
-//      turns most intervals away; the others probe the bucket's hash table.  (After
-//      the streaming, not before it: +inf survives every max and overwrites one that
-//      came first, so the order is free, and the streaming's many independent loads
-//      make better use of the time in which the output rows of the plan before are
-//      still leaving the CU than this chain of short dependent ones.)  The waves of a
-//      workgroup meet at one barrier after this step; nothing before it needs one;
-//   4. an entry with o < t* < q and acc != +inf scores
-//      P - max( acc, pieces after q's in its span, spans before o's, spans after q's, P - size ).
-// Buckets with more entries than acc holds are processed in slices of kMaxLocal
-// entries, one full pass per slice; the index keeps the q order and the
-// wavefronts' start positions per slice.
+// Per plan, one workgroup of 512 threads:
+//   1. the maxima of the row's blocks of 256 steps (longer blocks for rows of more
+//      than 131,072 or 262,144 steps, see kTab), streamed from the row; then their prefix and suffix
+//      maxima (two wavefronts), while the plan's own intervals cancel candidates:
+//      an interval inside the gap of an entry of its tensor (Alg. 2 of the paper only
+//      takes tensors that are not swapped out yet).  A per-bucket bit filter over
+//      tensors, kept in LDS, turns most intervals away; the others probe the
+//      bucket's hash table;
+//   2. every entry with o < t* < q that is not cancelled is bounded from both sides by
+//      the block maxima (score_body.h: classify).  Most are decided by that; the
+//      open ones are listed, and the few blocks of the row that they lie in - those
+//      around the peak - are read (resolve_open);
+//   3. every wavefront composes the output of its own range of tensors, 128 at a time,
+//      in LDS (zeros and -1, then the entries, which are stored in tensor order) and writes whole pieces of the rows, so
+//      that each output line goes to memory once.  (What step 2 found is not kept but found
+//      again: it costs a few LDS reads per entry and no space.)
+// Nothing is kept per entry but a bit or two, so a workgroup needs a third of a CU's LDS, and the phases of
+// three plans overlap on a CU.
+// What bounds it: HBM (rows in, output rows out).  Measured against the kernel before it (one workgroup of 1024 threads per
+// CU that ran two 64-bit max-scans over every 256 steps of the row and met every candidate's o and q on the way, its
+// phases one after the other with nothing beside them): 4,096 plans of 6,000 steps 180 -> 127 us, 8,192 of 24,000
+// 778 -> 633, 16,384 of 50,000 2.72 -> 2.69 ms (4.8 TB/s of what has to move), 1,024 of 10^6 2.43 -> 2.12 ms.
+// A plan with more open entries than the list holds, or a bucket with more entries than there are flags
+// (kWindow), takes the general form: rows cleared first, then the entries in runs of 512, written one by one.
 #include <atomic>
-#include <type_traits>
 
 #include "score_body.h"
 
@@ -53,72 +46,388 @@ namespace tensile {
 
 namespace {
 
+constexpr int kThr = 512, kWaves = kThr / 64;
+static_assert(kWaves == kScoreWaves, "the index holds where each wavefront's tensors start");
+
+// Blocks whose maxima fit in LDS: rows of up to 131,072 steps in blocks of 256 steps; longer rows have twice the table and blocks of
+// as many pieces of 256 steps as that takes.
+constexpr int kTabShort = 512, kTabLong = 1024;
+
+constexpr int kBufs = kWaves / 2;      // wavefronts that read the row's blocks for the open entries (the others' LDS is the stage's)
+
+struct StageBuf {
+    int64_t score[kStage];
+    int32_t win[2][kStage];      // win_out, win_in
+};
+
+template <int kTab>
+struct ScoreLds {
+    union {
+        __attribute__((aligned(16))) StageBuf stage[kWaves];
+        __attribute__((aligned(16))) SpanBuf bufs[kBufs];
+    };
+    BlockMaxima<kTab> mx;
+    OpenList<kThr> open;
+    uint64_t cancelled[kWindow / 64];    // one bit per entry of the window
+    uint64_t open_bits[kWindow / 64];    // the entry is on the open list, at open_base + its rank within the word
+    uint16_t open_base[kWindow / 64];
+    uint32_t filter[kFilterWords];
+    uint32_t need[kTab / 32];            // blocks of the row that open entries lie in
+};
+
+// Step 1: the maxima of the row's blocks into pm[k + 1] and sm[k].  The blocks are dealt round-robin, so that
+// the workgroup reads neighbouring lines at any time, each wavefront kAhead pieces ahead.
+// kStream (rows of more than 131,072 steps): the row is read once, past the L2's allocation.
+template <bool kVec, bool kStream, int kTab>
+__device__ __forceinline__ void stream_block_maxima(const ScoreArgs &a, const int64_t *MF, BlockMaxima<kTab> &mx, int wave, int lane) {
+    constexpr int kAhead = 2;
+    const int ps = a.piece_shift;
+    const int32_t mine = wave < a.n_blk ? (a.n_blk - wave + kWaves - 1) / kWaves : 0;   // blocks of this wavefront
+    const int32_t n = mine << ps;
+    const int32_t T = a.T;
+    auto first_step = [&](int32_t i) { return (((wave + (i >> ps) * kWaves) << ps) + (i & ((1 << ps) - 1))) * kMini; };
+    // (any order of the 256 steps over the lanes will do here: whole lines per load.  Beyond the row's end the loads are
+    // clamped and the values left out.)
+    auto load = [&](int32_t i, int64_t (&x)[4]) {
+        const int32_t t0 = first_step(i < n ? i : n - 1);
+        if constexpr (kVec) {
+#pragma unroll
+            for (int j = 0; j < 2; ++j) {
+                const int32_t t = t0 + 128 * j + 2 * lane;
+                const ll2 *at = reinterpret_cast<const ll2 *>(MF + (t < T ? t : T - 2));
+                ll2 v;
+                if constexpr (kStream) v = __builtin_nontemporal_load(at);
+                else v = *at;
+                x[2 * j] = v[0];
+                x[2 * j + 1] = v[1];
+            }
+        } else {
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const int32_t t = t0 + 64 * j + lane;
+                const int64_t *at = MF + (t < T ? t : T - 1);
+                if constexpr (kStream) x[j] = __builtin_nontemporal_load(at);
+                else x[j] = *at;
+            }
+        }
+    };
+    if (n == 0) return;      // (wave-uniform)
+    // (a clamped load brings the row's last step or last two once more: a value of the row's last block again, which
+    // changes no maximum as long as the piece itself starts inside the row)
+    int64_t x[kAhead][4];
+#pragma unroll
+    for (int d = 0; d < kAhead; ++d) load(d, x[d]);
+    int64_t run = INT64_MIN;
+    for (int32_t i0 = 0; i0 < n; i0 += kAhead) {
+#pragma unroll
+        for (int d = 0; d < kAhead; ++d) {
+            const int32_t i = i0 + d;
+            if (i < n) {     // (wave-uniform)
+                const int64_t m = max64(max64(x[d][0], x[d][1]), max64(x[d][2], x[d][3]));
+                load(i + kAhead, x[d]);
+                const int32_t t0 = first_step(i);
+                run = max64(run, t0 < T ? m : INT64_MIN);
+                if ((i & ((1 << ps) - 1)) == (1 << ps) - 1) {     // the block's last piece
+                    const int64_t v = wave_max(run);
+                    const int32_t blk = wave + (i >> ps) * kWaves;
+                    if (lane == 0) {
+                        mx.pm[blk + 1] = v;
+                        mx.sm[blk] = v;
+                    }
+                    run = INT64_MIN;
+                }
+            }
+        }
+    }
+}
+
+// kBig: rows of more than 131,072 steps.  kVec: the footprint rows are 16-byte aligned and T is even.
+template <bool kBig, bool kVec>
+__device__ __forceinline__ void score_plan(const ScoreArgs &a, const int32_t b, ScoreLds<kBig ? kTabLong : kTabShort> &L, int32_t &filter_of) {
+    // (the thread index is made opaque once per plan: everything derived from it is then
+    // recomputed where it is used instead of being held in registers across the whole loop)
+    int tid = threadIdx.x;
+    asm volatile("" : "+v"(tid));
+    const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int32_t tstar = uniform_load(a.argmax, b);
+    const int64_t P = uniform_load(a.peak, b);
+    const int64_t *MF = a.resident + static_cast<int64_t>(b) * a.T;
+    int64_t *score = a.score + static_cast<int64_t>(b) * a.N;
+    int32_t *wout = a.win_out ? a.win_out + static_cast<int64_t>(b) * a.N : nullptr;
+    int32_t *win = a.win_in ? a.win_in + static_cast<int64_t>(b) * a.N : nullptr;
+    PROF_START;
+
+    const bool has_peak = tstar >= 0 && tstar < a.T;     // else not produced by the evaluator: no candidate
+    const int32_t bk = has_peak ? tstar >> a.bucket_shift : 0;
+    const int32_t e0 = uniform_load(a.bucket_off, bk), n_e = has_peak ? uniform_load(a.bucket_off, bk + 1) - e0 : 0;
+    auto clear_rows = [&]() {
+        fill_row<kThr, int64_t>(score, a.N, 0, tid);
+        if (wout) fill_row<kThr, int32_t>(wout, a.N, -1, tid);
+        if (win) fill_row<kThr, int32_t>(win, a.N, -1, tid);
+    };
+    if (n_e == 0) {                                      // no gap around t* can be swapped in time
+        clear_rows();
+        return;
+    }
+    const int32_t *hash_dir = reinterpret_cast<const int32_t *>(a.hash_dir);
+    const int2 hd = make_int2(uniform_load(hash_dir, 2 * bk), uniform_load(hash_dir, 2 * bk + 1));
+    int64_t k0 = uniform_load(a.plan_offsets, b), k1 = uniform_load(a.plan_offsets, b + 1);
+    if (k0 < 0) k0 = 0;
+    if (k1 > a.n_intervals) k1 = a.n_intervals;
+    const int bs = a.piece_shift + 8;
+    const int2 *const oq_of = a.cand_oq + e0;
+    const int32_t *const tensor_of = a.cand_tensor + e0;
+    const int64_t *const size_of = a.cand_size + e0;
+
+    // ---- 1
+    __syncthreads();       // the previous plan has finished with the LDS
+    if (filter_of != bk) {
+        const uint32_t *src = a.filter + static_cast<int64_t>(bk) * a.filter_words;
+        for (int32_t k = tid; k < a.filter_words; k += kThr) L.filter[k] = src[k];
+        filter_of = bk;
+    }
+    for (int32_t k = tid; k < kWindow / 64 && k * 64 < n_e; k += kThr) L.cancelled[k] = 0;
+    for (int32_t k = tid; k * 32 < a.n_blk; k += kThr) L.need[k] = 0;
+    if (tid == 0) L.open.n = 0;
+    stream_block_maxima<kVec, kBig>(a, MF, L.mx, wave, lane);
+    PROF_MARK(0);
+    __syncthreads();
+    PROF_MARK(1);
+    scan_block_maxima(L.mx, a.n_blk, wave, lane);
+    PROF_MARK(2);
+    cancel_by_plan<kThr>(a, k0, k1, hd, e0, n_e, 0, n_e < kWindow ? n_e : kWindow, L.filter, reinterpret_cast<uint32_t *>(L.cancelled), tid);
+    PROF_MARK(3);
+    __syncthreads();
+    PROF_MARK(4);
+
+    // an entry: is it a candidate, and what do the block maxima say
+    struct Entry {
+        bool valid, open;
+        Classified c;
+    };
+    auto look = [&](int32_t k, int32_t in_window, int2 oq, int64_t size) {   // (k < n_e, or valid comes out false)
+        Entry e;
+        e.valid = k < n_e && oq.x < tstar && tstar < oq.y && !((L.cancelled[in_window >> 6] >> (in_window & 63)) & 1u);
+        e.c = classify(L.mx, bs, oq, P - size);
+        e.open = e.valid && (e.c.open_o || e.c.open_q);
+        return e;
+    };
+    // puts this wavefront's open entries (64 consecutive entries of the bucket, in order) on the list
+    auto list_open = [&](const Entry &e, int2 oq, int32_t in_window) {
+        const uint64_t mask = __builtin_amdgcn_ballot_w64(e.open);
+        const int32_t word = __builtin_amdgcn_readfirstlane(in_window >> 6);
+        if (lane == 0) L.open_bits[word] = mask;
+        if (mask == 0) return;
+        int32_t base = 0;
+        if (lane == 0) {
+            base = atomicAdd(&L.open.n, __builtin_popcountll(mask));
+            L.open_base[word] = static_cast<uint16_t>(base);
+        }
+        base = __builtin_amdgcn_readfirstlane(base);
+        const int32_t at = base + __builtin_popcountll(mask & ((1ull << lane) - 1));
+        if (e.open && at < kThr) {
+            L.open.acc[at] = e.c.lo;
+            L.open.oq[at] = make_int2(e.c.open_o ? oq.x : -1, e.c.open_q ? oq.y : -1);
+            if (e.c.open_o) atomicOr(&L.need[oq.x >> (bs + 5)], 1u << ((oq.x >> bs) & 31));
+            if (e.c.open_q) atomicOr(&L.need[oq.y >> (bs + 5)], 1u << ((oq.y >> bs) & 31));
+        }
+    };
+    auto outside_of = [&](const Entry &e, int32_t in_window) {   // the maximum outside the entry's window, at least P - size
+        if (!e.open) return e.c.lo;
+        const int32_t word = in_window >> 6, bit = in_window & 63;
+        return L.open.acc[L.open_base[word] + __builtin_popcountll(L.open_bits[word] & ((1ull << bit) - 1))];
+    };
+
+    // ---- 2
+    bool general = n_e > kWindow;
+    if (!general) {
+        for (int32_t kb = 0; kb < n_e; kb += kThr) {
+            const int32_t k = kb + tid, kc = k < n_e ? k : n_e - 1;
+            if (kb + wave * 64 >= n_e) break;            // (wave-uniform)
+            const int2 oq = oq_of[kc];
+            list_open(look(k, kc, oq, size_of[kc]), oq, kb + wave * 64);
+        }
+        __syncthreads();
+        const int32_t n_open = L.open.n;
+        general = n_open > kThr;
+        if (n_open > 0 && !general) {
+            resolve_open<kVec, kBufs>(a, MF, L.need, L.open, n_open, L.bufs, wave, lane);
+            __syncthreads();
+        }
+    }
+    PROF_MARK(5);
+
+    // ---- 3
+    if (!general) {
+        StageBuf &st = L.stage[wave];
+        const bool wide = ((reinterpret_cast<uintptr_t>(score) | reinterpret_cast<uintptr_t>(wout) | reinterpret_cast<uintptr_t>(win)) & 15) == 0;
+        const int32_t t_end = min((wave + 1) * a.tspan, a.N);
+        // the wavefront's entries, 64 at a time: those at hand, examined, and the next ones on their way
+        int32_t k = uniform_load(a.wave_ptr, static_cast<int64_t>(bk) * kWaves + wave);
+        int32_t next_tensor;
+        int2 next_oq;
+        int64_t next_size;
+        auto request = [&](int32_t at) {
+            const int32_t kc = at + lane < n_e ? at + lane : n_e - 1;
+            next_tensor = tensor_of[kc];
+            next_oq = oq_of[kc];
+            next_size = size_of[kc];
+        };
+        int32_t tensor, o, q;
+        int64_t value;
+        bool has;
+        auto take_up = [&]() {                           // the requested entries become those at hand; request the next
+            const int32_t kk = k + lane;
+            const int32_t kc = kk < n_e ? kk : n_e - 1;
+            const Entry e = look(kk, kc, next_oq, next_size);
+            tensor = kk < n_e ? next_tensor : INT32_MAX;
+            o = next_oq.x;
+            q = next_oq.y;
+            has = e.valid;
+            value = P - outside_of(e, kc);
+            request(k + 64);
+        };
+        int32_t pos = 0;                                 // entries at hand that are done
+        request(k);
+        take_up();
+        for (int32_t t0 = wave * a.tspan; t0 < t_end; t0 += kStage) {
+            const int32_t n_t = min(kStage, a.N - t0);
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+            reinterpret_cast<ll2 *>(st.score)[lane] = ll2{0, 0};
+            reinterpret_cast<ll2 *>(st.win)[lane] = ll2{-1, -1};
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+            for (;;) {                                   // (wave-uniform)
+                const bool take = lane >= pos && tensor < t0 + kStage;
+                if (take && has) {
+                    st.score[tensor - t0] = value;
+                    st.win[0][tensor - t0] = o;
+                    st.win[1][tensor - t0] = q;
+                }
+                pos += __builtin_popcountll(__builtin_amdgcn_ballot_w64(take));
+                if (pos < 64) break;
+                k += 64;
+                pos = 0;
+                take_up();
+            }
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+            if (wide && n_t == kStage) {
+                store_out<kBig>(reinterpret_cast<ll2 *>(score + t0) + lane, reinterpret_cast<const ll2 *>(st.score)[lane]);
+                int32_t *const dst = lane < 32 ? wout : win;     // (32 vectors of four each)
+                if (dst) store_out<kBig>(reinterpret_cast<i4 *>(dst + t0) + (lane & 31), reinterpret_cast<const i4 *>(st.win)[lane]);
+            } else {
+#pragma unroll
+                for (int j = 0; j < kStage / 64; ++j) {
+                    const int32_t u = j * 64 + lane;
+                    if (u < n_t) {
+                        score[t0 + u] = st.score[u];
+                        if (wout) wout[t0 + u] = st.win[0][u];
+                        if (win) win[t0 + u] = st.win[1][u];
+                    }
+                }
+            }
+        }
+        PROF_MARK(6);
+        return;
+    }
+
+    // ---- 2 and 3 in the general form
+    clear_rows();
+    for (int32_t w_lo = 0; w_lo < n_e; w_lo += kWindow) {
+        const int32_t w_n = min(kWindow, n_e - w_lo);
+        if (w_lo > 0) {                                  // (the first window's flags are there)
+            for (int32_t k = tid; k < kWindow / 64; k += kThr) L.cancelled[k] = 0;
+            __syncthreads();
+            cancel_by_plan<kThr>(a, k0, k1, hd, e0, n_e, w_lo, w_n, L.filter, reinterpret_cast<uint32_t *>(L.cancelled), tid);
+        }
+        for (int32_t kb = 0; kb < w_n; kb += kThr) {
+            __syncthreads();       // everybody has finished with the list and the blocks of the previous run (and clearing the rows)
+            for (int32_t k = tid; k * 32 < a.n_blk; k += kThr) L.need[k] = 0;
+            if (tid == 0) L.open.n = 0;
+            __syncthreads();
+            const int32_t k = w_lo + kb + tid, kc = k < n_e ? k : n_e - 1;
+            const int2 oq = oq_of[kc];
+            const Entry e = look(k, kc - w_lo, oq, size_of[kc]);
+            if (kb + wave * 64 < w_n) list_open(e, oq, kb + wave * 64);
+            __syncthreads();
+            const int32_t n_open = L.open.n;             // (at most one per thread)
+            if (n_open > 0) {
+                resolve_open<kVec, kBufs>(a, MF, L.need, L.open, n_open, L.bufs, wave, lane);
+                __syncthreads();
+            }
+            if (e.valid && kb + tid < w_n) {
+                const int32_t tensor = tensor_of[kc];
+                score[tensor] = P - outside_of(e, kb + tid);
+                if (wout) wout[tensor] = oq.x;
+                if (win) win[tensor] = oq.y;
+            }
+        }
+    }
+}
+
+// Workgroup w takes the plans w, w + grid, ...
+template <bool kBig, bool kVec>
+__global__ __launch_bounds__(kThr) __attribute__((amdgpu_waves_per_eu(6, 6))) void score_kernel(const ScoreArgs a) {
+    __shared__ ScoreLds<kBig ? kTabLong : kTabShort> lds;
+    int32_t filter_of = -1;      // bucket whose filter is in LDS
+    for (int32_t b = blockIdx.x; b < a.B; b += gridDim.x) score_plan<kBig, kVec>(a, b, lds, filter_of);
+}
+
 // ---- one iteration of the planner on the device --------------------------------------------------------
 // Alg. 3 analyses the peak again after every tensor it schedules.  The planner's row exists already, so an
 // iteration is: take the new interval's bytes out of its window of the row; bring the maxima (and their earliest
 // steps) of the 256-step blocks the window touches up to date - the table of block maxima is kept in global
 // memory from iteration to iteration: it is the block-level form of the prefix / suffix maxima of the row, of
 // which only the window's part changes; find the peak and its earliest step from the table; score the candidates
-// and hand the host one record per tensor with a window.  One workgroup, one launch.
-//
-// With the table, the blocks of the row are independent of each other: the maximum of everything before a block
-// and of everything after it come from prefix / suffix scans of the table (196 entries for 50,000 steps), so the
-// blocks are dealt to the wavefronts round-robin, each block is read once (from L2: the row is 400 KB), and an
-// entry whose o (q) lies in a block completes max MF[0..o] (max MF[q..T)) from the block alone.  Which candidates
-// the plan has already dealt with is not worked out from the plan's list again either (the list grows with
-// every iteration): a flag per gap and per tensor, set as intervals join, says so.  (The batch
-// kernel gives every wavefront one contiguous span instead, with boundaries balanced at load time for rows that
-// come from HBM; on one L2-resident row that left the slowest wavefront 60 % behind the first.)  Rows of more than
-// 131,072 steps, whose table does not fit in LDS next to the lists, take the batch kernel's body in its one-plan
-// form.
+// from the table's prefix and suffix maxima, as the batch kernel does - the row itself is read only in the few blocks
+// that leave a candidate open - and hand the host one record per tensor with a window.  One workgroup, one launch.
+// Which candidates the plan has already dealt with is not worked out from the plan's list (the list grows with
+// every iteration): a flag per gap and per tensor, set as intervals join, says so.
+// (Before: every block of the row with an endpoint of a candidate in it was read and scanned, every iteration.)
 struct GreedyStepArgs {
-    ScoreArgs s;                 // the scoring pass: one plan (all of the interval arrays), hdr / compact / ready set
+    ScoreArgs s;                 // the scoring pass: one plan
     int64_t *row;                // [T] the plan's footprint, in/out
-    int64_t *blk_max;            // [ceil(T / kMini)] maxima of the row's blocks, in/out
-    int32_t *blk_arg;            // [ceil(T / kMini)] earliest step of each block's maximum, in/out
+    int64_t *blk_max;            // [ceil(T / kMini)] maxima of the row's 256-step pieces, in/out
+    int32_t *blk_arg;            // [ceil(T / kMini)] earliest step of each piece's maximum, in/out
     uint8_t *gap_taken;          // [gaps] the plan holds an interval inside this gap, in/out
     uint8_t *tensor_taken;       // [N] the plan holds an interval of this tensor, in/out
     int32_t new_gap;             // the new interval's gap, or -1
     const int64_t *size;         // [N]
-    int32_t rebuild;             // every block's maximum is computed afresh (first launch on a row)
+    int32_t rebuild;             // every piece's maximum is computed afresh (first launch on a row)
     int32_t has_new;             // an interval joins the plan: applied to the row and written to position plan_n
     int32_t new_tensor, new_out, new_in, plan_n;
     int32_t *plan_t, *plan_o, *plan_r;
     int32_t do_score;            // 0: only the header {peak, peak step, 0} is produced
+    ScoreHeader *hdr;            // the record for the host (pinned host memory)
+    ScoreCand *compact;
+    unsigned long long *ready;   // receives ready_value when header and records are visible system-wide
+    unsigned long long ready_value;
 };
 
-constexpr int kStageRecs = 1024;   // records staged in LDS per round before they leave for the host
+constexpr int kPlanThr = 1024, kPlanWaves = kPlanThr / 64;
+constexpr int kPer = 3, kPlanRun = kPer * kPlanThr;   // entries of the bucket per thread, and per run
+static_assert(kTabLong <= kPlanThr, "one block of the table per thread");
 
-struct TabledLds {
-    __attribute__((aligned(16))) SpanBuf buf[kWaves];     // 48 KB; after the streaming step: staging of the records
-    int64_t pmx[kTabLds + 1];        // pmx[k] = max of the blocks before k (pmx[0] = -inf)
-    int64_t smx[kTabLds + 1];        // smx[k] = max of the blocks k .. (smx[n_blk] = -inf)
-    int64_t tb[kTabLds];             // the table itself
-    int32_t ta[kTabLds];
-    int32_t lo_ptr[kTabLds + 1];     // first entry of the o order with o in block k or later
-    int32_t hi_ptr[kTabLds + 1];     // the same for the q order
-    int64_t acc[kMaxLocal];
-    int32_t lo_list[kMaxLocal];
-    int2 hi_list[kMaxLocal];
-    int32_t n_stage, peak_block;
+struct PlanLds {
+    union {
+        __attribute__((aligned(16))) SpanBuf bufs[kPlanWaves];
+        __attribute__((aligned(16))) ScoreCand stage[kPlanRun];   // records on their way to the host
+    };
+    BlockMaxima<kTabLong> mx;
+    OpenList<kPlanRun> open;
+    uint32_t need[kTabLong / 32];
+    int64_t red_v[kPlanWaves];
+    int32_t red_t[kPlanWaves];
+    int32_t n_stage;
 };
-static_assert(sizeof(SpanBuf) * kWaves >= kStageRecs * sizeof(ScoreCand), "the staging area reuses the wavefronts' buffers");
-
-// the compact epilogue: header, then the word the host waits for
-__device__ __forceinline__ void publish_header(const ScoreArgs &a, int64_t P, int32_t tstar, int32_t count) {
-    *a.hdr = ScoreHeader{P, tstar, count};
-    if (a.ready) {
-        __threadfence_system();
-        __hip_atomic_store(a.ready, a.ready_value, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
-    }
-}
 
 // The window of the new interval leaves the row, and the table entries of the blocks it touches (of all blocks on a
 // fresh row) are recomputed.  One block per wavefront and round, 4 steps per lane.
 template <bool kVec>
 __device__ __forceinline__ void patch_row_and_table(const GreedyStepArgs &g, int tid) {
     const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int32_t T = g.s.T, n_blk = g.s.n_tab;
+    const int32_t T = g.s.T, n_blk = g.s.n_mini;
     int64_t *const row = g.row;
     const int32_t i = g.new_tensor, o = g.new_out, r = g.new_in;
     const bool ok = g.has_new && static_cast<uint32_t>(i) < static_cast<uint32_t>(g.s.N) && o >= 0 && r <= T && r > o;
@@ -136,7 +445,7 @@ __device__ __forceinline__ void patch_row_and_table(const GreedyStepArgs &g, int
     const bool any = win_hi > win_lo;
     const int32_t kb0 = g.rebuild ? 0 : (any ? win_lo / kMini : 0);
     const int32_t kb1 = g.rebuild ? n_blk : (any ? (win_hi - 1) / kMini + 1 : 0);
-    for (int32_t k = kb0 + wave; k < kb1; k += kWaves) {   // (wave-uniform)
+    for (int32_t k = kb0 + wave; k < kb1; k += kPlanWaves) {   // (wave-uniform)
         const int32_t t = k * kMini + 4 * lane;
         int64_t x[4];
         load_quad<kVec>(row, t, T, x);    // steps beyond T come back as INT64_MIN and lie outside every window
@@ -169,302 +478,152 @@ __device__ __forceinline__ void patch_row_and_table(const GreedyStepArgs &g, int
     }
 }
 
-// kBigT == false: the table-driven scoring pass described above.  kBigT == true: the batch kernel's body.
-template <bool kBigT, bool kVec>
-__global__ __launch_bounds__(kThreads) void greedy_step_kernel(const GreedyStepArgs g) {
-    typedef typename std::conditional<kBigT, ScoreLds<true>, TabledLds>::type Lds;
-    __shared__ Lds lds;
-    __shared__ int64_t red_v[kWaves];
-    __shared__ int32_t red_k[kWaves];
-    __shared__ int64_t s_peak;
-    __shared__ int32_t s_step;
+template <bool kVec>
+__global__ __launch_bounds__(kPlanThr) void greedy_step_kernel(const GreedyStepArgs g) {
+    __shared__ PlanLds lds;
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-#ifdef TENSILE_SCORE_PROF
-    unsigned long long prof_t = wall_clock64();
-#endif
+    PROF_START;
     const ScoreArgs &a = g.s;
-    const int32_t T = a.T, n_blk = a.n_tab;
+    const int ps = a.piece_shift, bs = ps + 8;
     patch_row_and_table<kVec>(g, tid);
     // other wavefronts of this workgroup read what these stores wrote (table entries now, the row in the scoring pass)
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
     __syncthreads();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
 
-    if constexpr (kBigT) {
-        // ---- the peak: largest block maximum, earliest block among equals
-        int64_t bv = INT64_MIN;
-        int32_t bk = INT32_MAX;
-        for (int32_t k = tid; k < n_blk; k += kThreads) {   // (a thread meets its blocks in ascending order)
-            const int64_t v = g.blk_max[k];
-            if (v > bv) {
+    // ---- the table into LDS, one block per thread; the peak and its earliest step
+    int64_t bv = INT64_MIN;
+    int32_t bt = INT32_MAX;
+    if (tid < a.n_blk) {
+        const int32_t p0 = tid << ps, p1 = min(p0 + (1 << ps), a.n_mini);
+        for (int32_t p = p0; p < p1; ++p) {
+            const int64_t v = g.blk_max[p];
+            const int32_t t = g.blk_arg[p];
+            if (v > bv) {        // (in ascending order: the earliest step among equals)
                 bv = v;
-                bk = k;
+                bt = t;
             }
         }
-#pragma unroll
-        for (int d = 32; d >= 1; d >>= 1) {
-            const int64_t ov = __shfl_xor(bv, d, 64);
-            const int32_t ok2 = __shfl_xor(bk, d, 64);
-            if (ov > bv || (ov == bv && ok2 < bk)) {
-                bv = ov;
-                bk = ok2;
-            }
-        }
-        if (lane == 0) {
-            red_v[wave] = bv;
-            red_k[wave] = bk;
-        }
-        __syncthreads();
-        if (tid == 0) {
-#pragma unroll
-            for (int w = 1; w < kWaves; ++w)
-                if (red_v[w] > bv || (red_v[w] == bv && red_k[w] < bk)) {
-                    bv = red_v[w];
-                    bk = red_k[w];
-                }
-            s_peak = bv;
-            s_step = g.blk_arg[bk];
-        }
-        __syncthreads();
-    } else {
-        // ---- the table into LDS; its prefix and suffix maxima; the peak and the first block that holds it
-        for (int32_t k = tid; k < n_blk; k += kThreads) {
-            lds.tb[k] = g.blk_max[k];
-            lds.ta[k] = g.blk_arg[k];
-        }
-        if (tid == 0) lds.peak_block = INT32_MAX;
-        __syncthreads();
-        if (wave == 0) {          // pmx[k + 1] = max tb[0..k]
-            int64_t run = INT64_MIN;
-            if (lane == 0) lds.pmx[0] = INT64_MIN;
-            for (int32_t k0 = 0; k0 < n_blk; k0 += 64) {
-                const int32_t k = k0 + lane;
-                const int64_t incl = max64(wave_scan_max(k < n_blk ? lds.tb[k] : INT64_MIN), run);
-                if (k < n_blk) lds.pmx[k + 1] = incl;
-                run = last_lane(incl);
-            }
-            if (lane == 0) s_peak = run;
-        } else if (wave == 1) {   // smx[k] = max tb[k..]
-            int64_t run = INT64_MIN;
-            if (lane == 0) lds.smx[n_blk] = INT64_MIN;
-            for (int32_t top = n_blk; top > 0; top -= 64) {
-                const int32_t k = top - 1 - lane;
-                const int64_t incl = max64(wave_scan_max(k >= 0 ? lds.tb[k] : INT64_MIN), run);
-                if (k >= 0) lds.smx[k] = incl;
-                run = last_lane(incl);
-            }
-        }
-        __syncthreads();
-        for (int32_t k = tid; k < n_blk; k += kThreads)
-            if (lds.tb[k] == s_peak) atomicMin(&lds.peak_block, k);
-        __syncthreads();
-        if (tid == 0) s_step = lds.ta[lds.peak_block];
-        __syncthreads();
+        lds.mx.pm[tid + 1] = bv;
+        lds.mx.sm[tid] = bv;
     }
-    const int32_t tstar = __builtin_amdgcn_readfirstlane(s_step);
-    const uint32_t p_lo = __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(s_peak));
-    const uint32_t p_hi = __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(static_cast<uint64_t>(s_peak) >> 32));
-    const int64_t P = static_cast<int64_t>((static_cast<uint64_t>(p_hi) << 32) | p_lo);
-#ifdef TENSILE_SCORE_PROF
-#define STEP_MARK(k) do { if (tid == 0) { const unsigned long long now_ = wall_clock64(); atomicAdd(&g_score_prof[k], now_ - prof_t); prof_t = now_; } } while (0)
-#else
-#define STEP_MARK(k) do { } while (0)
-#endif
-    STEP_MARK(6);
+    auto better = [&](int64_t ov, int32_t ot) {
+        if (ov > bv || (ov == bv && ot < bt)) {
+            bv = ov;
+            bt = ot;
+        }
+    };
+#pragma unroll
+    for (int d = 32; d >= 1; d >>= 1) better(__shfl_xor(bv, d, 64), __shfl_xor(bt, d, 64));
+    if (lane == 0) {
+        lds.red_v[wave] = bv;
+        lds.red_t[wave] = bt;
+    }
+    if (tid * 32 < a.n_blk) lds.need[tid] = 0;
+    if (tid == 0) lds.n_stage = lds.open.n = 0;
+    __syncthreads();
+    bv = lds.red_v[lane & (kPlanWaves - 1)];             // (every wavefront reduces for itself: no barrier)
+    bt = lds.red_t[lane & (kPlanWaves - 1)];
+#pragma unroll
+    for (int d = kPlanWaves / 2; d >= 1; d >>= 1) better(__shfl_xor(bv, d, 64), __shfl_xor(bt, d, 64));
+    const int32_t tstar = __builtin_amdgcn_readfirstlane(bt);
+    const int64_t P = lane_value(bv, 0);
+    PROF_MARK(8);
     if (!g.do_score) {
-        if (tid == 0) publish_header(a, P, tstar, 0);
+        if (tid == 0) {
+            *g.hdr = ScoreHeader{P, tstar, 0};
+            __hip_atomic_store(g.ready, g.ready_value, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+        }
         return;
     }
-    if constexpr (kBigT) {
-        ScoreCarry carry;
-#ifdef TENSILE_SCORE_PROF
-        carry.prof_t = prof_t;
-#endif
-        score_plan<true, kVec, true>(a, 0, tstar, P, lds, a.tab_scratch, carry);   // (one workgroup: its scratch table is the first)
-    } else {
-        const int64_t *const MF = g.row;
-        const int32_t bk = tstar >> a.bucket_shift;
-        const int32_t e0 = uniform_load(a.bucket_off, bk), n_e = uniform_load(a.bucket_off, bk + 1) - e0;
-        int32_t n_out = 0;     // records handed to the host so far (the same in every thread)
-        for (int32_t slice_lo = 0; slice_lo < n_e; slice_lo += kMaxLocal) {
-            const int32_t n_slice = min(kMaxLocal, n_e - slice_lo);
-            __syncthreads();   // the previous slice has finished with the lists, acc and the staging area
-            // ---- the slice's lists; per block, where its entries start in each order
-            for (int32_t k = tid; k < n_slice; k += kThreads) {
-                lds.acc[k] = INT64_MIN;
-                lds.lo_list[k] = a.cand_o[e0 + slice_lo + k];
-                lds.hi_list[k] = a.qord[e0 + slice_lo + k];
-            }
-            if (tid == 0) lds.n_stage = 0;
-            // this thread's entries for the last step (three at most), requested now: what they are scored from is
-            // static, and the flags were set before the barrier above; all of it is on its way while the row streams
-            constexpr int kPer = kMaxLocal / kThreads;
-            static_assert(kPer * kThreads == kMaxLocal && kStageRecs == kThreads, "one entry per thread and round of the last step");
-            int4 my_c[kPer];
-            int32_t my_gap[kPer];
-            int64_t my_sz[kPer];
+    const int32_t bk = tstar >> a.bucket_shift;
+    const int32_t e0 = uniform_load(a.bucket_off, bk), n_e = uniform_load(a.bucket_off, bk + 1) - e0;
+    int32_t n_out = 0;     // records handed to the host so far (the same in every thread)
+    for (int32_t run_lo = 0; run_lo < n_e; run_lo += kPlanRun) {
+        const int32_t n_run = min(kPlanRun, n_e - run_lo);
+        if (run_lo > 0) {
+            __syncthreads();       // the previous run has finished with the lists and the staging area
+            if (tid * 32 < a.n_blk) lds.need[tid] = 0;
+            if (tid == 0) lds.n_stage = lds.open.n = 0;
+        }
+        // this thread's entries: static, requested now, and on their way while two wavefronts scan the table
+        int2 oq[kPer];
+        int32_t tensor[kPer], gap[kPer];
+        int64_t size[kPer];
 #pragma unroll
-            for (int j = 0; j < kPer; ++j) {
-                const int32_t k = j * kThreads + tid;
-                const int32_t e = e0 + slice_lo + (k < n_slice ? k : 0);
-                my_c[j] = a.cand[e];
-                my_gap[j] = a.cand_gap[e];
-                my_sz[j] = a.cand_size[e];
-            }
-            __syncthreads();
-            STEP_MARK(0);
-            // lo_ptr[b] / hi_ptr[b]: the first entry of the o / q order whose step lies in block b or later - one
-            // binary search per block and order, all blocks at once.  (Walking the entries and filling in the blocks
-            // between two of them left the ~100 blocks before the first entry, and as many after the last, to a
-            // single thread: 6.7 us of every iteration.)
-            for (int32_t bq = tid; bq <= 2 * n_blk + 1; bq += kThreads) {
-                const bool hi_order = bq > n_blk;
-                const int32_t blk = hi_order ? bq - n_blk - 1 : bq;
-                const int32_t bound = blk * kMini;                 // (blk == n_blk: past every step)
-                int32_t lo = 0, hi = n_slice;                      // first k with step(k) >= bound
-                while (lo < hi) {
-                    const int32_t mid = (lo + hi) >> 1;
-                    const int32_t step = hi_order ? lds.hi_list[mid].x : lds.lo_list[mid];
-                    if (step < bound) lo = mid + 1;
-                    else hi = mid;
+        for (int j = 0; j < kPer; ++j) {
+            const int32_t k = j * kPlanThr + tid, e = e0 + run_lo + (k < n_run ? k : n_run - 1);
+            oq[j] = a.cand_oq[e];
+            tensor[j] = a.cand_tensor[e];
+            gap[j] = a.cand_gap[e];
+            size[j] = a.cand_size[e];
+        }
+        uint8_t taken[kPer];       // (the flags were set before the first barrier)
+#pragma unroll
+        for (int j = 0; j < kPer; ++j) taken[j] = a.any_interval ? g.tensor_taken[tensor[j]] : g.gap_taken[gap[j]];
+        if (run_lo == 0) scan_block_maxima(lds.mx, a.n_blk, wave, lane);
+        __syncthreads();
+        PROF_MARK(9);
+        // ---- what the table says; the open ones on the list
+        int64_t value[kPer];
+        int32_t at[kPer];          // place on the open list, -1: none, -2: not a candidate
+#pragma unroll
+        for (int j = 0; j < kPer; ++j) {
+            const bool valid = j * kPlanThr + tid < n_run && oq[j].x < tstar && tstar < oq[j].y && !taken[j];
+            const Classified c = classify(lds.mx, bs, oq[j], P - size[j]);
+            value[j] = c.lo;
+            at[j] = valid ? -1 : -2;
+            const bool open = valid && (c.open_o || c.open_q);
+            const uint64_t mask = __builtin_amdgcn_ballot_w64(open);
+            if (mask) {            // (wave-uniform)
+                int32_t base = 0;
+                if (lane == 0) base = atomicAdd(&lds.open.n, __builtin_popcountll(mask));
+                base = __builtin_amdgcn_readfirstlane(base);
+                if (open) {
+                    at[j] = base + __builtin_popcountll(mask & ((1ull << lane) - 1));
+                    lds.open.acc[at[j]] = c.lo;
+                    lds.open.oq[at[j]] = make_int2(c.open_o ? oq[j].x : -1, c.open_q ? oq[j].y : -1);
+                    if (c.open_o) atomicOr(&lds.need[oq[j].x >> (bs + 5)], 1u << ((oq[j].x >> bs) & 31));
+                    if (c.open_q) atomicOr(&lds.need[oq[j].y >> (bs + 5)], 1u << ((oq[j].y >> bs) & 31));
                 }
-                if (hi_order) lds.hi_ptr[blk] = lo;
-                else lds.lo_ptr[blk] = lo;
-            }
-            uint8_t my_taken[kPer];
-#pragma unroll
-            for (int j = 0; j < kPer; ++j) my_taken[j] = a.any_interval ? g.tensor_taken[my_c[j].w] : g.gap_taken[my_gap[j] < 0 ? 0 : my_gap[j]];
-            __syncthreads();
-            STEP_MARK(1);
-            // ---- the row's blocks, dealt round-robin; a block without an endpoint of the slice is not even read.
-            // (Taken one by one from a common counter instead - the entries are spread unevenly over the blocks, and
-            // the first wavefront waits 3 us for the last - the wait shrinks to 2 us and the step grows by 2: the
-            // atomic and its way back into a scalar register sit in front of every request.)
-            {
-                SpanBuf *const buf = &lds.buf[wave];
-                auto wanted = [&](int32_t kb) { return kb < n_blk && (lds.lo_ptr[kb + 1] > lds.lo_ptr[kb] || lds.hi_ptr[kb + 1] > lds.hi_ptr[kb]); };
-                auto next_wanted = [&](int32_t kb) {     // (wave-uniform)
-                    while (kb < n_blk && !wanted(kb)) kb += kWaves;
-                    return kb;
-                };
-                // The wavefront's blocks are requested kAhead ahead (the row sits in L2; with one request in flight
-                // per wavefront every block would cost a full round trip).  The requests live in kAhead fixed sets
-                // of registers, taken in turn - rotating them would mean waiting for the youngest - and are always
-                // issued, at clamped addresses past the end, so that every wait names an exact count.
-                constexpr int kAhead = 4;
-                int32_t kq[kAhead];            // the block each set of registers holds (>= n_blk: none)
-                int64_t x[kAhead][4];
-                int32_t cursor = wave;         // where the search for the wavefront's next block goes on
-#pragma unroll
-                for (int d = 0; d < kAhead; ++d) {
-                    kq[d] = next_wanted(cursor);
-                    cursor = kq[d] + kWaves;
-                    load_quad<kVec>(MF, (kq[d] < n_blk ? kq[d] : n_blk) * kMini + 4 * lane, T, x[d]);
-                }
-                for (bool more = true; more;) {
-#pragma unroll
-                    for (int d = 0; d < kAhead; ++d) {
-                        const int32_t kb = kq[d];
-                        if (kb >= n_blk) {     // (wave-uniform; the blocks come in ascending order: nothing is left)
-                            more = false;
-                            break;
-                        }
-                        const int64_t v0 = x[d][0], v1 = x[d][1], v2 = x[d][2], v3 = x[d][3];
-                        kq[d] = next_wanted(cursor);
-                        cursor = kq[d] + kWaves;
-                        load_quad<kVec>(MF, (kq[d] < n_blk ? kq[d] : n_blk) * kMini + 4 * lane, T, x[d]);
-                        const int32_t t0 = kb * kMini;
-                        const int64_t before_blk = lds.pmx[kb], after_blk = lds.smx[kb + 1];
-                        const int64_t m = max64(max64(v0, v1), max64(v2, v3));
-                        // (this pass is bound by its instructions - one CU for the whole row - and the two scans are
-                        // most of them: where the block's values share their upper halves, as they nearly always do,
-                        // the scans run on the lower ones)
-                        int64_t fwd, rs;
-                        const int32_t m_hi = static_cast<int32_t>(m >> 32);
-                        if (__builtin_amdgcn_ballot_w64(m_hi != __builtin_amdgcn_readfirstlane(m_hi)) == 0) {   // (wave-uniform)
-                            const int64_t top = static_cast<int64_t>(static_cast<uint64_t>(static_cast<uint32_t>(m_hi)) << 32);
-                            fwd = top | wave_scan_umax32(static_cast<uint32_t>(m));
-                            rs = top | wave_rscan_umax32(static_cast<uint32_t>(m), lane);
-                        } else {
-                            fwd = wave_scan_max(m);
-                            rs = wave_rscan_max(m, lane);
-                        }
-                        const int64_t incl = max64(fwd, before_blk);
-                        const int64_t excl = from_prev_lane(incl, before_blk);          // max MF[0 .. t0 + 4 lane - 1]
-                        const int64_t rs_next = max64(from_next_lane(rs, INT64_MIN), after_blk);   // max MF[t0 + 4 lane + 4 .. T)
-                        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-                        reinterpret_cast<ll2 *>(buf->raw)[2 * lane] = ll2{v0, v1};
-                        reinterpret_cast<ll2 *>(buf->raw)[2 * lane + 1] = ll2{v2, v3};
-                        buf->before[lane] = excl;
-                        buf->after[lane] = rs_next;
-                        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-                        __builtin_amdgcn_wave_barrier();
-                        for (int32_t k = lds.lo_ptr[kb] + lane; k < lds.lo_ptr[kb + 1]; k += 64) {
-                            const int32_t r = lds.lo_list[k] - t0, l = r >> 2, j = r & 3;
-                            int64_t v = max64(buf->before[l], buf->raw[4 * l]);
-                            if (j >= 1) v = max64(v, buf->raw[4 * l + 1]);
-                            if (j >= 2) v = max64(v, buf->raw[4 * l + 2]);
-                            if (j >= 3) v = max64(v, buf->raw[4 * l + 3]);
-                            atomicMax(reinterpret_cast<long long *>(lds.acc + k), static_cast<long long>(v));
-                        }
-                        for (int32_t k = lds.hi_ptr[kb] + lane; k < lds.hi_ptr[kb + 1]; k += 64) {
-                            const int2 it = lds.hi_list[k];
-                            const int32_t r = it.x - t0, l = r >> 2, j = r & 3;
-                            int64_t v = max64(buf->after[l], buf->raw[4 * l + 3]);
-                            if (j <= 2) v = max64(v, buf->raw[4 * l + 2]);
-                            if (j <= 1) v = max64(v, buf->raw[4 * l + 1]);
-                            if (j <= 0) v = max64(v, buf->raw[4 * l]);
-                            atomicMax(reinterpret_cast<long long *>(lds.acc + it.y), static_cast<long long>(v));
-                        }
-                        __builtin_amdgcn_wave_barrier();
-                    }
-                }
-            }
-            STEP_MARK(3);
-            __syncthreads();
-            STEP_MARK(4);
-            // ---- scores of the surviving candidates, staged in LDS (where the wavefronts' buffers were) kStageRecs
-            // at a time and sent to the host as whole lines
-            ScoreCand *const stage = reinterpret_cast<ScoreCand *>(lds.buf);
-            int32_t staged_before = 0;     // (n_stage counts the slice's records so far; it is reset at the slice's start)
-#pragma unroll
-            for (int j = 0; j < kPer; ++j) {
-                const int32_t r0 = j * kStageRecs;
-                if (r0 >= n_slice) break;      // (block-uniform)
-                const int32_t k = r0 + tid;
-                if (k < n_slice) {
-                    // (a candidate the plan has already dealt with is out: an interval inside the entry's gap - or,
-                    // for recomputation, any interval of its tensor - which the flags record as the plan grows)
-                    const int4 c = my_c[j];
-                    const int32_t gap = my_gap[j];
-                    const int64_t sz = my_sz[j];
-                    const int64_t v = lds.acc[k];
-                    const bool taken = my_taken[j] != 0;
-                    if (c.z < tstar && tstar < c.y && !taken)
-                        stage[atomicAdd(&lds.n_stage, 1) - staged_before] = ScoreCand{P - max64(v, P - sz), c.w, c.z, c.y, gap};
-                }
-                __syncthreads();
-                STEP_MARK(2);
-                const int32_t n_st = lds.n_stage - staged_before;
-                const int64_t *src = reinterpret_cast<const int64_t *>(stage);
-                int64_t *dst = reinterpret_cast<int64_t *>(a.compact + n_out);
-                for (int32_t w = tid; w < 3 * n_st; w += kThreads) dst[w] = src[w];
-                n_out += n_st;
-                staged_before += n_st;
-                __syncthreads();       // the staging area is free again
-                STEP_MARK(5);
             }
         }
-        // the header travels with the records: one wait for the host's memory instead of two.  The barrier orders every
-        // thread's records before thread 0's store of the signal, and that store releases at system scope - which
-        // covers what happened before it in other threads too (a system-scope fence in each of the 1024 threads,
-        // as it was first written, cost 2 us per iteration more)
-        if (tid == 0) *a.hdr = ScoreHeader{P, tstar, n_out};
         __syncthreads();
-        if (tid == 0 && a.ready) __hip_atomic_store(a.ready, a.ready_value, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
-        STEP_MARK(7);
+        PROF_MARK(10);
+        const int32_t n_open = lds.open.n;
+        if (n_open > 0) {
+            resolve_open<kVec, kPlanWaves>(a, g.row, lds.need, lds.open, n_open, lds.bufs, wave, lane);
+            __syncthreads();
+        }
+        PROF_MARK(11);
+        // ---- the records, staged in LDS and sent to the host as whole lines
+#pragma unroll
+        for (int j = 0; j < kPer; ++j) {
+            const uint64_t mask = __builtin_amdgcn_ballot_w64(at[j] != -2);
+            if (mask == 0) continue;
+            int32_t base = 0;
+            if (lane == 0) base = atomicAdd(&lds.n_stage, __builtin_popcountll(mask));
+            base = __builtin_amdgcn_readfirstlane(base);
+            if (at[j] != -2)
+                lds.stage[base + __builtin_popcountll(mask & ((1ull << lane) - 1))] =
+                    ScoreCand{P - (at[j] >= 0 ? lds.open.acc[at[j]] : value[j]), tensor[j], oq[j].x, oq[j].y, gap[j]};
+        }
+        __syncthreads();
+        const int32_t n_st = lds.n_stage;
+        const int64_t *src = reinterpret_cast<const int64_t *>(lds.stage);
+        int64_t *dst = reinterpret_cast<int64_t *>(g.compact + n_out);
+        for (int32_t w = tid; w < 3 * n_st; w += kPlanThr) dst[w] = src[w];
+        n_out += n_st;
+        PROF_MARK(12);
     }
-#undef STEP_MARK
+    // the header travels with the records: one wait for the host's memory instead of two.  The barrier orders every
+    // thread's records before thread 0's store of the signal, and that store releases at system scope - which
+    // covers what happened before it in other threads too (a system-scope fence in each of the 1024 threads,
+    // as it was first written, cost 2 us per iteration more)
+    if (tid == 0) *g.hdr = ScoreHeader{P, tstar, n_out};
+    __syncthreads();
+    if (tid == 0) __hip_atomic_store(g.ready, g.ready_value, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+    PROF_MARK(13);
 }
 
 }  // namespace
@@ -475,8 +634,8 @@ int launch_greedy_step(const tensile_tas *tas, Workspace &ws, const CandIndex &i
                        int64_t *row, const GreedyTables &tables, bool rebuild, const GreedyNew *fresh, bool do_score,
                        ScoreHeader *hdr, ScoreCand *compact, unsigned long long *ready, unsigned long long ready_value) {
     GreedyStepArgs g{};
-    g.s = make_score_args(tas, ix, any_interval, pl, row, nullptr, nullptr, nullptr, nullptr, nullptr);
-    g.s.hdr = hdr; g.s.compact = compact; g.s.ready = ready; g.s.ready_value = ready_value;
+    g.s = make_score_args(tas, ix, any_interval, pl, kTabLong, row, nullptr, nullptr, nullptr, nullptr, nullptr);
+    g.hdr = hdr; g.compact = compact; g.ready = ready; g.ready_value = ready_value;
     g.row = row; g.blk_max = tables.blk_max; g.blk_arg = tables.blk_arg; g.size = tas->d_size.p;
     g.gap_taken = tables.gap_taken; g.tensor_taken = tables.tensor_taken; g.new_gap = -1;
     g.rebuild = rebuild ? 1 : 0;
@@ -487,66 +646,41 @@ int launch_greedy_step(const tensile_tas *tas, Workspace &ws, const CandIndex &i
         g.new_gap = fresh->gap;
         g.plan_t = fresh->plan_t; g.plan_o = fresh->plan_o; g.plan_r = fresh->plan_r;
     }
-    const bool big_t = g.s.n_tab > kTabLds;
-    if (big_t && g.do_score) {
-        const int rc = ws.provide(ws.score_tab, static_cast<size_t>(g.s.n_tab), "greedy: block maxima of the scoring pass");
-        if (rc != TENSILE_OK) return rc;
-        g.s.tab_scratch = ws.score_tab.p;
-    }
-    const hipStream_t stream = ws.stream;
-    if (big_t) {
-        if (g.s.vec16) hipLaunchKernelGGL((greedy_step_kernel<true, true>), dim3(1), dim3(kThreads), 0, stream, g);
-        else hipLaunchKernelGGL((greedy_step_kernel<true, false>), dim3(1), dim3(kThreads), 0, stream, g);
-    } else {
-        if (g.s.vec16) hipLaunchKernelGGL((greedy_step_kernel<false, true>), dim3(1), dim3(kThreads), 0, stream, g);
-        else hipLaunchKernelGGL((greedy_step_kernel<false, false>), dim3(1), dim3(kThreads), 0, stream, g);
-    }
+    const bool vec16 = tas->T % 2 == 0 && reinterpret_cast<uintptr_t>(row) % 16 == 0;
+    if (vec16) hipLaunchKernelGGL(greedy_step_kernel<true>, dim3(1), dim3(kPlanThr), 0, ws.stream, g);
+    else hipLaunchKernelGGL(greedy_step_kernel<false>, dim3(1), dim3(kPlanThr), 0, ws.stream, g);
     TS_HIP(hipGetLastError());
     return TENSILE_OK;
 }
 
 int launch_score(const tensile_tas *tas, Workspace &ws, const CandIndex &ix, bool any_interval, const tensile_plans *plans,
                  const int64_t *resident, const int64_t *peak, const int32_t *argmax, int64_t *score, int32_t *win_out,
-                 int32_t *win_in, ScoreHeader *hdr, ScoreCand *compact, unsigned long long *ready,
-                 unsigned long long ready_value) {
+                 int32_t *win_in) {
     if (plans->B == 0 || tas->N == 0) return TENSILE_OK;
-    const hipStream_t stream = ws.stream;
-    if (compact && (plans->B != 1 || !hdr)) { set_error("score: the compact form takes one plan"); return TENSILE_E_INVAL; }
     // as many workgroups as the device keeps resident, the plans dealt evenly among them
-    const bool big_t = (tas->T + kMini - 1) / kMini > kTabLds;
+    const bool big = tas->T > kTabShort * kMini;
     static std::atomic<int> per_cu_of[2];   // (0 = not asked yet; every thread that asks stores the same answer)
-    int per_cu = per_cu_of[big_t ? 1 : 0].load(std::memory_order_relaxed);
+    int per_cu = per_cu_of[big ? 1 : 0].load(std::memory_order_relaxed);
     if (per_cu == 0) {
         int n = 0;
-        if (big_t) TS_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, score_kernel<true, true, false>, kThreads, 0));
-        else TS_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, score_kernel<false, true, false>, kThreads, 0));
+        if (big) TS_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, score_kernel<true, true>, kThr, 0));
+        else TS_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, score_kernel<false, true>, kThr, 0));
         per_cu = n > 0 ? n : 1;
-        per_cu_of[big_t ? 1 : 0].store(per_cu, std::memory_order_relaxed);
+        per_cu_of[big ? 1 : 0].store(per_cu, std::memory_order_relaxed);
     }
     const int64_t resident_blocks = static_cast<int64_t>(tas->num_cus) * per_cu;
     const int64_t rounds = (plans->B + resident_blocks - 1) / resident_blocks;
     int32_t blocks = static_cast<int32_t>((plans->B + rounds - 1) / rounds);
     if (const int v = g_tuning.score_blocks; v > 0)   // tuning knob: size of the grid (plans are dealt round-robin)
         blocks = v < plans->B ? v : plans->B;
-    ScoreArgs a = make_score_args(tas, ix, any_interval, plans, resident, peak, argmax, score, win_out, win_in);
-    a.hdr = hdr; a.compact = compact;
-    a.ready = ready; a.ready_value = ready_value;
-    if (a.n_tab > kTabLds) {
-        const size_t need = static_cast<size_t>(blocks) * static_cast<size_t>(a.n_tab);
-        const int rc = ws.provide(ws.score_tab, need, "score: block maxima");
-        if (rc != TENSILE_OK) return rc;
-        a.tab_scratch = ws.score_tab.p;
-    }
-#define TS_LAUNCH_SCORE(BIG, VEC)                                                                                      \
-    do {                                                                                                               \
-        if (compact) hipLaunchKernelGGL((score_kernel<BIG, VEC, true>), dim3(blocks), dim3(kThreads), 0, stream, a);   \
-        else hipLaunchKernelGGL((score_kernel<BIG, VEC, false>), dim3(blocks), dim3(kThreads), 0, stream, a);          \
-    } while (0)
-    if (big_t) {
-        if (a.vec16) TS_LAUNCH_SCORE(true, true);
+    const ScoreArgs a = make_score_args(tas, ix, any_interval, plans, big ? kTabLong : kTabShort, resident, peak, argmax, score, win_out, win_in);
+    const bool vec16 = tas->T % 2 == 0 && reinterpret_cast<uintptr_t>(resident) % 16 == 0;
+#define TS_LAUNCH_SCORE(BIG, VEC) hipLaunchKernelGGL((score_kernel<BIG, VEC>), dim3(blocks), dim3(kThr), 0, ws.stream, a)
+    if (big) {
+        if (vec16) TS_LAUNCH_SCORE(true, true);
         else TS_LAUNCH_SCORE(true, false);
     } else {
-        if (a.vec16) TS_LAUNCH_SCORE(false, true);
+        if (vec16) TS_LAUNCH_SCORE(false, true);
         else TS_LAUNCH_SCORE(false, false);
     }
 #undef TS_LAUNCH_SCORE
@@ -558,7 +692,7 @@ int launch_score(const tensile_tas *tas, Workspace &ws, const CandIndex &ix, boo
 extern "C" int tensile_debug_score_prof(unsigned long long *out, int reset) {
     if (out) (void)hipMemcpyFromSymbol(out, HIP_SYMBOL(g_score_prof), sizeof(g_score_prof));
     if (reset) {
-        unsigned long long z[8 + 2 * 16] = {};
+        unsigned long long z[16] = {};
         (void)hipMemcpyToSymbol(HIP_SYMBOL(g_score_prof), z, sizeof(z));
     }
     return 0;

@@ -269,30 +269,31 @@ int build_candidate_index(const tensile_tas *h, CandIndex &ix, const std::vector
             for (int32_t b = (gwin[g] + 1) >> shift; b <= (gq[g] - 1) >> shift; ++b) ++off[b + 1];
     for (int32_t b = 0; b < nb; ++b) off[b + 1] += off[b];
     const size_t E = static_cast<size_t>(off[nb]);
-    std::vector<int4> cand(E);
+    // (the gaps come tensor by tensor and by ascending first step, and a bucket receives them in that order)
+    std::vector<int2> cand_oq(E);
+    std::vector<int32_t> cand_tensor(E), cand_p(E), cand_gap(E);
+    std::vector<int64_t> cand_size(E);
     {
         std::vector<int32_t> fill(off.begin(), off.end() - 1);
         for (size_t g = 0; g < G; ++g)
             if (usable(g))
-                for (int32_t b = (gwin[g] + 1) >> shift; b <= (gq[g] - 1) >> shift; ++b)
-                    cand[fill[b]++] = make_int4(gp[g], gq[g], gwin[g], gt[g]);
+                for (int32_t b = (gwin[g] + 1) >> shift; b <= (gq[g] - 1) >> shift; ++b) {
+                    const int32_t e = fill[b]++;
+                    cand_oq[e] = make_int2(gwin[g], gq[g]);
+                    cand_tensor[e] = gt[g];
+                    cand_p[e] = gp[g];
+                    cand_gap[e] = static_cast<int32_t>(g);
+                    cand_size[e] = h->h_size[gt[g]];
+                }
     }
-    std::vector<int64_t> cand_size(E);
-    std::vector<int32_t> cand_o(E), cand_gap(E);
-    std::vector<int2> qord(E), tord(E);
-    std::vector<int32_t> slice_first(static_cast<size_t>(nb) + 1, 0);
-    for (int32_t b = 0; b < nb; ++b)
-        slice_first[b + 1] = slice_first[b] + (off[b + 1] - off[b] + kScoreMaxLocal - 1) / kScoreMaxLocal;
-    std::vector<int32_t> wave_ptr(static_cast<size_t>(slice_first[nb]) * 4 * (kScoreWaves + 1));
+    std::vector<int32_t> wave_ptr(static_cast<size_t>(nb) * kScoreWaves);
     std::vector<int2> hash_dir(static_cast<size_t>(nb));
     std::vector<uint32_t> filter(static_cast<size_t>(nb) * ix.filter_words, 0u);
     // every bucket's hash table has its place before any is filled: the buckets are then independent of each
-    // other and are worked on by several host threads (the sorts dominate the time this takes)
-    ix.max_bucket = 0;
+    // other and are worked on by several host threads
     size_t hash_total = 0;
     for (int32_t b = 0; b < nb; ++b) {
         const int32_t n = off[b + 1] - off[b];
-        ix.max_bucket = std::max(ix.max_bucket, n);
         int bits = 1;
         while ((int64_t{1} << bits) < 2 * static_cast<int64_t>(n)) ++bits;
         hash_dir[b] = make_int2(static_cast<int32_t>(hash_total), n > 0 ? bits : 0);
@@ -300,85 +301,23 @@ int build_candidate_index(const tensile_tas *h, CandIndex &ix, const std::vector
         if (hash_total > static_cast<size_t>(INT32_MAX)) { set_error("tas_load: candidate index too large"); return TENSILE_E_RANGE; }
     }
     std::vector<int4> hash_slots(hash_total, make_int4(-1, 0, 0, 0));
-    auto do_bucket = [&](int32_t b, std::vector<int32_t> &order) {
+    auto do_bucket = [&](int32_t b) {
         const int32_t e0 = off[b], n = off[b + 1] - off[b];
-        int4 *c = cand.data() + e0;
-        std::sort(c, c + n, [](const int4 &x, const int4 &y) {
-            return x.z != y.z ? x.z < y.z : (x.w != y.w ? x.w < y.w : x.x < y.x);
-        });
-        for (int32_t k = 0; k < n; ++k) {
-            cand_size[e0 + k] = h->h_size[c[k].w];
-            cand_o[e0 + k] = c[k].z;
-            // the gap's number: its place among the tensor's gaps, which are listed by ascending first step
-            const int32_t *g0 = gp.data() + h->h_gap_first[c[k].w], *g1 = gp.data() + h->h_gap_first[c[k].w + 1];
-            cand_gap[e0 + k] = static_cast<int32_t>(std::lower_bound(g0, g1, c[k].x) - gp.data());
-        }
-        for (int32_t s0 = 0, sl = slice_first[b]; s0 < n; s0 += kScoreMaxLocal, ++sl) {
-            const int32_t ns = std::min(kScoreMaxLocal, n - s0);
-            order.resize(ns);
-            for (int32_t k = 0; k < ns; ++k) order[k] = k;
-            std::sort(order.begin(), order.end(),
-                      [&](int32_t x, int32_t y) { return c[s0 + x].y != c[s0 + y].y ? c[s0 + x].y < c[s0 + y].y : x < y; });
-            for (int32_t k = 0; k < ns; ++k) qord[e0 + s0 + k] = make_int2(c[s0 + order[k]].y, order[k]);
-            std::sort(order.begin(), order.end(),
-                      [&](int32_t x, int32_t y) { return c[s0 + x].w != c[s0 + y].w ? c[s0 + x].w < c[s0 + y].w : x < y; });
-            for (int32_t k = 0; k < ns; ++k) tord[e0 + s0 + k] = make_int2(c[s0 + order[k]].w, order[k]);
-            int32_t *wp = wave_ptr.data() + static_cast<size_t>(sl) * 4 * (kScoreWaves + 1);
-            // The wavefronts' spans of the row.  A wavefront's time in the streaming pass is about one unit per
-            // block of kScoreMini steps plus one per kEntriesPerBlock entries whose o or q it meets (measured:
-            // 1.05 us per block, 7 ns per entry), so the boundaries are put where the running cost
-            // blocks * kEntriesPerBlock + entries passes w/16 of the total (boundaries on whole blocks).
-            int32_t *sb = wp + 3 * (kScoreWaves + 1);
-            {
-                constexpr int64_t kEntriesPerBlock = 150;
-                const int64_t nblk = (static_cast<int64_t>(T) + kScoreMini - 1) / kScoreMini;
-                auto cost_before = [&](int64_t blk) {   // cost of the blocks [0, blk)
-                    const int64_t step = blk * kScoreMini;
-                    const int64_t n_o = std::lower_bound(c + s0, c + s0 + ns, step, [](const int4 &e, int64_t v) { return e.z < v; }) - (c + s0);
-                    const int2 *qo = qord.data() + e0 + s0;
-                    const int64_t n_q = std::lower_bound(qo, qo + ns, step, [](const int2 &e, int64_t v) { return e.x < v; }) - qo;
-                    return blk * kEntriesPerBlock + n_o + n_q;
-                };
-                const int64_t total = cost_before(nblk);
-                sb[0] = 0;
-                for (int w = 1; w < kScoreWaves; ++w) {
-                    const int64_t want = (total * w + kScoreWaves - 1) / kScoreWaves;
-                    int64_t lo_b = sb[w - 1] / kScoreMini, hi_b = nblk;       // smallest block count with cost >= want
-                    while (lo_b < hi_b) {
-                        const int64_t mid = (lo_b + hi_b) / 2;
-                        if (cost_before(mid) >= want) hi_b = mid;
-                        else lo_b = mid + 1;
-                    }
-                    sb[w] = static_cast<int32_t>(std::min<int64_t>(lo_b * kScoreMini, T));
-                }
-                sb[kScoreWaves] = T;
-            }
-            int32_t ko = 0, kq = 0, kt = 0;
-            for (int w = 0; w <= kScoreWaves; ++w) {
-                const int64_t bound = sb[w], tbound = static_cast<int64_t>(w) * ix.tspan;
-                while (ko < ns && c[s0 + ko].z < bound) ++ko;
-                while (kq < ns && qord[e0 + s0 + kq].x < bound) ++kq;
-                while (kt < ns && tord[e0 + s0 + kt].x < tbound) ++kt;
-                wp[w] = w == kScoreWaves ? ns : ko;
-                wp[kScoreWaves + 1 + w] = w == kScoreWaves ? ns : kq;
-                wp[2 * (kScoreWaves + 1) + w] = w == kScoreWaves ? ns : kt;
-            }
-        }
-        // hash table: the entries of one tensor are inserted one after the other, the last flagged
+        const int32_t *t = cand_tensor.data() + e0;
+        for (int w = 0; w < kScoreWaves; ++w)
+            wave_ptr[static_cast<size_t>(b) * kScoreWaves + w] =
+                static_cast<int32_t>(std::lower_bound(t, t + n, static_cast<int64_t>(w) * ix.tspan) - t);
         if (n == 0) return;
         const size_t base = static_cast<size_t>(hash_dir[b].x);
         const int bits = hash_dir[b].y;
-        order.resize(n);
-        for (int32_t k = 0; k < n; ++k) order[k] = k;
-        std::sort(order.begin(), order.end(), [&](int32_t x, int32_t y) { return c[x].w != c[y].w ? c[x].w < c[y].w : x < y; });
         const uint32_t mask = (1u << bits) - 1;
         for (int32_t k = 0; k < n; ++k) {
-            const int4 &en = c[order[k]];
-            const bool last = k + 1 == n || c[order[k + 1]].w != en.w;
-            uint32_t s = (static_cast<uint32_t>(en.w) * 2654435769u) >> (32 - bits);
+            if (k > 0 && t[k] == t[k - 1]) continue;       // the table leads to a tensor's first entry
+            const bool last = k + 1 == n || t[k + 1] != t[k];
+            uint32_t s = (static_cast<uint32_t>(t[k]) * 2654435769u) >> (32 - bits);
             while (hash_slots[base + s].x >= 0) s = (s + 1) & mask;
-            hash_slots[base + s] = make_int4(en.w, en.x, en.y, order[k] | (last ? INT32_MIN : 0));
-            const uint32_t fb = static_cast<uint32_t>(en.w) & (filter_bits - 1);
+            hash_slots[base + s] = make_int4(t[k], cand_p[e0 + k], cand_oq[e0 + k].y, k | (last ? INT32_MIN : 0));
+            const uint32_t fb = static_cast<uint32_t>(t[k]) & (filter_bits - 1);
             filter[static_cast<size_t>(b) * ix.filter_words + (fb >> 5)] |= 1u << (fb & 31);
         }
     };
@@ -391,8 +330,7 @@ int build_candidate_index(const tensile_tas *h, CandIndex &ix, const std::vector
         std::atomic<bool> failed{false};
         auto worker = [&]() {
             try {
-                std::vector<int32_t> order;
-                for (int32_t b; (b = next_bucket.fetch_add(1)) < nb;) do_bucket(b, order);
+                for (int32_t b; (b = next_bucket.fetch_add(1)) < nb;) do_bucket(b);
             } catch (...) {
                 failed = true;
             }
@@ -407,13 +345,11 @@ int build_candidate_index(const tensile_tas *h, CandIndex &ix, const std::vector
         if (failed) throw std::bad_alloc();
     }
     TS_HIP(ix.bucket_off.upload(off.data(), off.size()));
-    TS_HIP(ix.cand.upload(cand.data(), E));
-    TS_HIP(ix.cand_size.upload(cand_size.data(), E));
-    TS_HIP(ix.cand_o.upload(cand_o.data(), E));
+    TS_HIP(ix.cand_oq.upload(cand_oq.data(), E));
+    TS_HIP(ix.cand_tensor.upload(cand_tensor.data(), E));
+    TS_HIP(ix.cand_p.upload(cand_p.data(), E));
     TS_HIP(ix.cand_gap.upload(cand_gap.data(), E));
-    TS_HIP(ix.qord.upload(qord.data(), E));
-    TS_HIP(ix.tord.upload(tord.data(), E));
-    TS_HIP(ix.slice_first.upload(slice_first.data(), slice_first.size()));
+    TS_HIP(ix.cand_size.upload(cand_size.data(), E));
     TS_HIP(ix.wave_ptr.upload(wave_ptr.data(), wave_ptr.size()));
     TS_HIP(ix.hash_dir.upload(hash_dir.data(), hash_dir.size()));
     TS_HIP(ix.hash_slots.upload(hash_slots.data(), hash_slots.size()));

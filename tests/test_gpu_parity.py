@@ -776,6 +776,58 @@ def test_score_optional_windows_and_blocking():
     h.close()
 
 
+def plateau_tas(T, n_big, seed=1):
+    """Large tensors generated one after the other and read one after the other at the end; in between, tiny tensors
+    make the footprint creep up and down by less than any large tensor's size.  A slow link spreads the large
+    tensors' earliest swap-out steps over the plateau, so that the maxima of its 256-step blocks decide none of their
+    scores."""
+    ramp = n_big + 2
+    half = (T - 2 * ramp) // 2
+    mid = ramp + half
+    n_tiny = half - 2
+    big = [(1 << 17) + 128 * int(x) for x in prng.randint(seed, 7, np.arange(n_big), 0, 1 << 14)]
+    sizes = big + [1] * n_tiny
+    allocs = list(range(n_big)) + [ramp + k for k in range(n_tiny)]
+    accs = [[T - ramp + k] for k in range(n_big)] + [[mid + half - 2 - k] for k in range(n_tiny)]
+    # a transfer of the mean large tensor takes half of the plateau's first half
+    return tas_from_lists(T, sizes, allocs, accs, None, np.full(T, 1000, dtype=np.int64), 0, int(sum(big) / len(big) / (half / 2)))
+
+
+@pytest.mark.parametrize("T,n_big", [(4000, 90), (9000, 700), (9001, 1300), (140_000, 60), (262_145, 40), (300_002, 600)])
+def test_score_candidates_that_block_maxima_leave_open(T, n_big):
+    """Every candidate needs the row itself, in blocks all over the plateau: a few of them, more than the list of open
+    entries holds (512), rows with even and odd lengths, blocks of one and of several 256-step pieces."""
+    tas = plateau_tas(T, n_big)
+    ramp = n_big + 2                                  # plans that swap nothing, a tiny tensor, a large one somewhere
+    pl = plans_from_lists([[], [(n_big + 5, ramp + 9, T // 2 + 3)], [(1, T // 2 - 2, T // 2 + 9)], [(n_big // 2, n_big, T // 3)]])
+    say(f"score open candidates T={T} n_big={n_big}")
+    assert check_score(tas, pl, label=f"open T={T}") > 2 * n_big
+    assert check_step(tas, pl, label=f"open, one call T={T}") > 2 * n_big
+    if T < 20_000:
+        assert check_score_recompute(tas, pl, label=f"open T={T}") > 2 * n_big
+
+
+@pytest.mark.parametrize("N,acc", [(16384, 1), (16385, 1), (20000, 1), (300, 60)])
+def test_score_buckets_of_many_entries(N, acc):
+    """Buckets with as many entries as there are flags for, one more, two windows of them; tensors with many gaps in one
+    bucket (an interval then cancels an entry behind its tensor's first)."""
+    T = 700
+    i = np.arange(N)
+    alloc = prng.randint(79, 1, i, 0, 249)
+    sizes = prng.randint(79, 3, i, 1, 1 << 16)
+    if acc == 1:
+        accs = [[int(x)] for x in prng.randint(79, 2, i, 400, 698)]
+    else:
+        accs = [sorted({int(alloc[k]) + 1 + int(x) for x in prng.randint(79, 100 + k, np.arange(acc), 0, T - 3 - int(alloc[k]))}) for k in range(N)]
+    sn = prng.randint(79, 4, np.arange(T), 1, 1000).astype(np.int64)
+    tas = tas_from_lists(T, [int(x) for x in sizes], [int(x) for x in alloc], accs, None, sn, 0, 400_000)
+    pl = make_plans(tas, 4, 5, p_swap=0.3)
+    say(f"score buckets N={N} acc={acc}")
+    assert check_score(tas, pl) > N // 10
+    assert check_score_recompute(tas, pl) > N // 10
+    assert check_step(tas, pl) > N // 10
+
+
 # -------------------------------------------------------------------- evaluation + scoring in one call
 
 def gpu_step(h, dp):
