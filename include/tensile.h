@@ -227,8 +227,9 @@ int tensile_score_candidates(const tensile_tas *tas, const tensile_plans *plans,
  * Outputs and their meaning are exactly those of tensile_eval_plans followed by
  * tensile_score_candidates on the same batch (resident is required here, the
  * scores are computed from it); the two kernels are enqueued back to back
- * under one lock of the stream's workspace.  Asynchronous on hip_stream.
- * B == 0 is a no-op. */
+ * under one lock of the stream's workspace, which holds what the evaluation
+ * hands to the scoring (the maxima of every 256 steps of the rows: 1/256 of
+ * the rows' size).  Asynchronous on hip_stream.  B == 0 is a no-op. */
 int tensile_eval_score_plans(const tensile_tas *tas, const tensile_plans *plans, int64_t *resident, int64_t *peak,
                              int32_t *argmax, int64_t *min_resident, int64_t *score, int32_t *win_out, int32_t *win_in,
                              void *hip_stream);
@@ -362,7 +363,8 @@ int tensile_greedy_plan(const tensile_tas *tas, int64_t budget_bytes, const tens
  *   "eval_r"          intervals per thread kept in registers (0 = automatic)
  *   "score_blocks"    size of the scoring grid (0 = automatic)
  *   "link_packed"     0: search the cumulative latencies themselves even when their packed form exists (1 = automatic)
- *   "step_fused"      accepted, without effect
+ *   "step_fused"      0: in tensile_eval_score_plans the scoring reads the rows, as tensile_score_candidates does; else it
+ *                     takes the maxima of the rows' 256-step blocks from the evaluation
  * TENSILE_E_INVAL for an unknown name. */
 int tensile_tuning_set(const char *knob, int value);
 

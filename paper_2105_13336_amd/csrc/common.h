@@ -76,6 +76,7 @@ struct EvalArgs {
     const int64_t *MF0;            // [T] unscheduled timeline (read at segment starts only)
     const int64_t *dMF0;           // MF0[t] - MF0[t-1], dMF0[0] = MF0[0]; zero padded to whole tiles plus one tile
     int64_t *resident;             // [B*T] or null
+    int64_t *blk_max;              // [B][ceil(T / kScoreMini)] maxima of the rows' pieces, for a scoring pass, or null (rows only)
     int64_t tail_threshold;        // plans with more intervals than this belong to the tail kernel
     unsigned long long *tail_flag; // set to `epoch` by the common kernel when it leaves a plan to the tail kernel
     unsigned long long epoch;      // number of this launch (per handle)
@@ -107,6 +108,7 @@ struct Workspace {
     DevBuf<int32_t> part_arg;
     DevBuf<unsigned long long> tail_flag;   // eval: see EvalArgs::tail_flag (zero when allocated, then monotone)
     unsigned long long epoch = 0;           // launches of the evaluation kernel through this workspace
+    DevBuf<int64_t> blk_max;       // evaluation and scoring in one call: see EvalArgs
     DevBuf<int32_t> job_arg;       // per-job evaluation: peak steps when the caller does not want them
     DevBuf<int2> bin_recs;         // eval, binned mode: see EvalArgs
     DevBuf<int32_t> bin_off;
@@ -147,7 +149,7 @@ struct Tuning {
     int eval_nt = -1;          // footprint rows written with nontemporal stores: 0 never, 1 always, -1 by row length
     int score_blocks = 0;      // size of the scoring grid
     int link_packed = 1;       // 0: search C itself even when its packed form exists
-    int step_fused = -1;       // (no effect: the fused kernel it chose is gone)
+    int step_fused = -1;       // tensile_eval_score_plans: 0 = scoring reads the rows, else the evaluation hands it their block maxima
 };
 extern Tuning g_tuning;
 
@@ -165,29 +167,29 @@ struct JobTables {
 
 // What the scoring kernel shares with the index built at load time (see score.hip).
 constexpr int kScoreWaves = 8;         // wavefronts of the batch kernel's workgroup
+constexpr int kScoreFilterWords = 1024;  // most words of a bucket's filter (32768 bits)
 constexpr int kScoreStage = 128;       // tensors whose output (16 bytes each) one wavefront composes in LDS at a time
 
 // Candidate index: every gap (p, q) with a feasible earliest swap-out step o, filed under each
 // bucket of 2^shift steps that o+1 .. q-1 overlaps.  Per bucket (entries e0 .. e1-1, local
 // index = e - e0), in the order of (tensor, p):
-//   cand_oq / cand_tensor / cand_size   what the scoring pass reads of every entry
-//   cand_p / cand_gap           p, and the entry's gap: its number among the gaps of length >= 2 in tensor order
+//   cand / cand_size            {tensor, p, q, o} and the tensor's size
+//   cand_gap                    the entry's gap: its number among the gaps of length >= 2 in tensor order
 //   wave_ptr[kScoreWaves]       first entry with tensor >= w * tspan
-//   hash_dir / hash_slots       open-addressing table tensor -> its first entry, {tensor, p, q, local | last << 31}
-//                               (last: the tensor has no other entry in the bucket)
-//   filter                      one bit per (tensor mod filter_bits): some entry has this tensor
+//   filter / filter_base        one bit per 2^filter_shift tensors (some entry has one of them), and per word of bits its
+//                               first entry: a tensor's first entry is found from there (see cancel_by_plan)
 struct CandIndex {
     int32_t shift = 0, n_buckets = 0;
     int32_t tspan = kScoreStage;   // tensors per wavefront: ceil(N / kScoreWaves) rounded up to kScoreStage
-    int32_t filter_words = 0;      // words per bucket, a power of two
+    int32_t filter_shift = 0;      // tensors per filter bit, as a power of two
+    int32_t filter_words = 0;      // words per bucket: at most kScoreFilterWords
     DevBuf<int32_t> bucket_off;    // [n_buckets + 1]
-    DevBuf<int2> cand_oq;
-    DevBuf<int32_t> cand_tensor, cand_p, cand_gap;
+    DevBuf<int4> cand;
+    DevBuf<int32_t> cand_gap;
     DevBuf<int64_t> cand_size;
     DevBuf<int32_t> wave_ptr;      // [n_buckets][kScoreWaves]
-    DevBuf<int2> hash_dir;         // [n_buckets] {first slot, log2(slots)}
-    DevBuf<int4> hash_slots;
     DevBuf<uint32_t> filter;       // [n_buckets][filter_words]
+    DevBuf<int32_t> filter_base;   // [n_buckets][filter_words + 1]
 };
 
 }  // namespace tensile
@@ -252,10 +254,11 @@ struct ScoreCand {
     int32_t tensor, wo, wi;
     int32_t gap;                   // number of the candidate's gap
 };
-// (any_interval: an interval of the entry's tensor cancels the entry wherever it lies, not only inside the gap.)
+// (any_interval: an interval of the entry's tensor cancels the entry wherever it lies, not only inside the gap.
+//  blk_max: the maxima of the rows' pieces as the evaluation wrote them, or null: taken from the rows.)
 int launch_score(const tensile_tas *tas, Workspace &ws, const CandIndex &ix, bool any_interval, const tensile_plans *plans,
                  const int64_t *resident, const int64_t *peak, const int32_t *argmax, int64_t *score, int32_t *win_out,
-                 int32_t *win_in);
+                 int32_t *win_in, const int64_t *blk_max = nullptr);
 // One iteration of the planner in one launch (score.hip: greedy_step_kernel).  fresh: the interval that joins the plan
 // (applied to the row, written to `position` of the plan's device arrays), or null.
 struct GreedyNew {

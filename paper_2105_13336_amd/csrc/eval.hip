@@ -81,13 +81,15 @@ __global__ __launch_bounds__(kThr) __attribute__((amdgpu_waves_per_eu(4, 4))) vo
 // Plans with more intervals than the registers hold are left to the tail kernel as before.
 template <int kThr, int R, bool kNarrow, int kOut>
 __global__ __launch_bounds__(kThr) __attribute__((amdgpu_waves_per_eu(4, 4))) void eval_stream_kernel(const EvalArgs a) {
-    constexpr bool kStore = kOut != 0, kVec16 = kOut == 2;
+    constexpr int kMode = kOut & ~kOutPieces;
+    constexpr bool kStore = kMode != 0, kVec16 = kMode == 2, kPieces = (kOut & kOutPieces) != 0;
     constexpr int kWaves = Geom<kThr>::kWaves, kTile = Geom<kThr>::kTile, kTileCells = Geom<kThr>::kTileCells;
     __shared__ __attribute__((aligned(16))) int64_t delta[kTileCells + 64];   // the tile, then 64 "trash" cells
     __shared__ __attribute__((aligned(16))) int64_t stage_all[kWaves * kStageStride];
     __shared__ int64_t wave_tot[kWaves];
     __shared__ int64_t red_mx[kWaves], red_mn[kWaves];
     __shared__ int32_t red_arg[kWaves];
+    __shared__ int64_t piece_max[2][2 * kWaves];   // (kPieces) of the tile at hand and of the one before, in turn
     __shared__ int64_t ahead_off[2][2];   // where the list of the plan after the next starts and ends (see the plan loop)
     typedef SizeReg<kNarrow> SR;
 
@@ -241,6 +243,8 @@ __global__ __launch_bounds__(kThr) __attribute__((amdgpu_waves_per_eu(4, 4))) vo
     // the tile whose results wait in the staging areas (none yet: an empty range stores nothing)
     int64_t *prev_row = a.resident;
     int32_t prev_lo = 0, prev_hi = 0;
+    int64_t *prev_pieces = nullptr;
+    int piece_slot = 0;
     int64_t done_plan = -1;      // the plan whose per-wavefront results wait in red_*
     int64_t nk0 = 0, nk1 = 0;    // the next plan's list
     int64_t ahead = a.B;         // the plan after the next (a.B: none), whose offsets the first wavefront fetches
@@ -254,7 +258,6 @@ __global__ __launch_bounds__(kThr) __attribute__((amdgpu_waves_per_eu(4, 4))) vo
     //  * otherwise (it is the last tile of the previous plan's row, ragged or not, or there is none):
     //    two 8-byte buffer stores over the valid part of that row; the hardware drops what lies
     //    beyond the range, so nothing is conditional here either.
-    typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
     auto store_part = [&](const Ids &L, int j, auto full_tag) {
         constexpr bool kFull = decltype(full_tag)::value;
         if constexpr (kStore) {
@@ -373,6 +376,9 @@ __global__ __launch_bounds__(kThr) __attribute__((amdgpu_waves_per_eu(4, 4))) vo
         }
         store_part(L, 1, prev_full);
         __syncthreads();
+        if constexpr (kPieces) {   // the pieces of the tile before, whichever plan it belongs to
+            if (L.wave_u == kWaves - 1 && prev_hi > 0) store_piece_maxima<kWaves>(a, prev_pieces, prev_lo, piece_max[piece_slot ^ 1], L.lane);
+        }
         if constexpr (kFirst) {
             write_result(L);
             done_plan = -1;
@@ -408,6 +414,7 @@ __global__ __launch_bounds__(kThr) __attribute__((amdgpu_waves_per_eu(4, 4))) vo
         if constexpr (kLast && kFirst) load_sizes(L, nk0, nk1);
         store_part(L, 2, prev_full);
         __syncthreads();
+        int64_t lane_mx = INT64_MIN;
         if (wave_live) {
             int64_t tot = wave_tot[L.lane & (kWaves - 1)];
             tot += dpp_or_zero<0x111, 0xf>(tot);
@@ -454,10 +461,12 @@ __global__ __launch_bounds__(kThr) __attribute__((amdgpu_waves_per_eu(4, 4))) vo
                         if (v[j] == cm) best.arg = t0 + j;
                 }
                 best.mn = cn < best.mn ? cn : best.mn;
+                lane_mx = cm;
             } else {
 #pragma unroll
                 for (int j = 0; j < kVpt; ++j) {
                     if (t0 + j < tile_hi) {
+                        lane_mx = max64(lane_mx, v[j]);
                         if (v[j] > best.mx) {
                             best.mx = v[j];
                             best.arg = t0 + j;
@@ -466,6 +475,10 @@ __global__ __launch_bounds__(kThr) __attribute__((amdgpu_waves_per_eu(4, 4))) vo
                     }
                 }
             }
+        }
+        if constexpr (kPieces) {
+            keep_piece_maxima(piece_max[piece_slot], lane_mx, L.wave, L.lane);
+            piece_slot ^= 1;
         }
         // ---- the previous tile's last quarter leaves the staging area, this tile's results enter it
         store_part(L, 3, prev_full);
@@ -476,6 +489,7 @@ __global__ __launch_bounds__(kThr) __attribute__((amdgpu_waves_per_eu(4, 4))) vo
             for (int j = 0; j < kVpt / 2; ++j) mine_out[j] = ll2{v[2 * j], v[2 * j + 1]};
         }
         prev_row = row;
+        if constexpr (kPieces) prev_pieces = pieces_of(a, plan);
         prev_lo = tile_lo;
         prev_hi = tile_hi;
     };
@@ -537,6 +551,10 @@ __global__ __launch_bounds__(kThr) __attribute__((amdgpu_waves_per_eu(4, 4))) vo
 #pragma unroll
     for (int j = 0; j < kVpt / 2; ++j) store_part(fresh_ids(), j, std::false_type{});
     __syncthreads();
+    if constexpr (kPieces) {
+        const Ids L = fresh_ids();
+        if (L.wave_u == kWaves - 1) store_piece_maxima<kWaves>(a, prev_pieces, prev_lo, piece_max[piece_slot ^ 1], L.lane);
+    }
     write_result(fresh_ids());
 }
 
@@ -816,6 +834,27 @@ bool binning_pays(double avg, int64_t n_tiles) {
     return 0.35 * (avg - kCapTail) / 1024.0 > 1.5 + 3.0 * avg / 1024.0 / static_cast<double>(n_tiles);
 }
 
+// f(output mode) with the mode as a constant: 0 no rows, 1 / 2 / 3 rows with 8-byte, 16-byte, nontemporal 16-byte stores
+// (3 becomes 2 where it is not compiled), with or without the maxima of the rows' pieces.
+template <bool kNt, typename F>
+void with_mode(int out, bool pieces, F f) {
+    auto rows = [&](auto mode) {
+        if (pieces) f(std::integral_constant<int, decltype(mode)::value + kOutPieces>{});
+        else f(mode);
+    };
+    if (out == 0) f(std::integral_constant<int, 0>{});
+    else if (out == 1) rows(std::integral_constant<int, 1>{});
+    else {
+        if constexpr (kNt) {
+            if (out == 3) {
+                rows(std::integral_constant<int, 3>{});
+                return;
+            }
+        }
+        rows(std::integral_constant<int, 2>{});
+    }
+}
+
 // The launches of one geometry: common kernel (three register capacities), tail kernel.
 template <int kThr>
 int launch_geometry(const tensile_tas *tas, Workspace &ws, const EvalArgs &a, int64_t blocks, int cap, int out, bool narrow,
@@ -826,38 +865,30 @@ int launch_geometry(const tensile_tas *tas, Workspace &ws, const EvalArgs &a, in
         if (a.S > 1) hipLaunchKernelGGL((bin_kernel<kThr, true>), dim3(a.B), dim3(1024), 0, stream, a, ws.bin_recs.p, ws.bin_off.p, ws.bin_sum.p);
         else hipLaunchKernelGGL((bin_kernel<kThr, false>), dim3(a.B), dim3(1024), 0, stream, a, ws.bin_recs.p, ws.bin_off.p, ws.bin_sum.p);
         TS_HIP(hipGetLastError());
-        if (out == 3) {
-            hipLaunchKernelGGL((eval_binned_kernel<kThr, 3, true>), grid, block, 0, stream, a);
-            hipLaunchKernelGGL((eval_binned_kernel<kThr, 3, false>), grid, block, 0, stream, a);
-        } else if (out >= 2) {
-            hipLaunchKernelGGL((eval_binned_kernel<kThr, 2, true>), grid, block, 0, stream, a);
-            hipLaunchKernelGGL((eval_binned_kernel<kThr, 2, false>), grid, block, 0, stream, a);
-        } else if (out == 1) {
-            hipLaunchKernelGGL((eval_binned_kernel<kThr, 1, true>), grid, block, 0, stream, a);
-            hipLaunchKernelGGL((eval_binned_kernel<kThr, 1, false>), grid, block, 0, stream, a);
-        } else {
-            hipLaunchKernelGGL((eval_binned_kernel<kThr, 0, true>), grid, block, 0, stream, a);
-            hipLaunchKernelGGL((eval_binned_kernel<kThr, 0, false>), grid, block, 0, stream, a);
-        }
+        auto go = [&](auto mode) {
+            hipLaunchKernelGGL((eval_binned_kernel<kThr, decltype(mode)::value, true>), grid, block, 0, stream, a);
+            hipLaunchKernelGGL((eval_binned_kernel<kThr, decltype(mode)::value, false>), grid, block, 0, stream, a);
+        };
+        with_mode<true>(out, a.blk_max != nullptr, go);
         TS_HIP(hipGetLastError());
         return TENSILE_OK;
     }
-#define TS_LAUNCH_OUT(KERNEL, ...)                                                                   \
-    do {                                                                                             \
-        if (out >= 2) hipLaunchKernelGGL((KERNEL<__VA_ARGS__, 2>), grid, block, 0, stream, a);       \
-        else if (out == 1) hipLaunchKernelGGL((KERNEL<__VA_ARGS__, 1>), grid, block, 0, stream, a);  \
-        else hipLaunchKernelGGL((KERNEL<__VA_ARGS__, 0>), grid, block, 0, stream, a);                \
-    } while (0)
-#define TS_LAUNCH_EVAL(R)                                                    \
-    do {                                                                     \
-        if (persistent) {                                                    \
-            if (narrow) TS_LAUNCH_OUT(eval_stream_kernel, kThr, R, true);    \
-            else TS_LAUNCH_OUT(eval_stream_kernel, kThr, R, false);          \
-        } else {                                                             \
-            if (narrow) TS_LAUNCH_OUT(eval_kernel, kThr, R, true);           \
-            else TS_LAUNCH_OUT(eval_kernel, kThr, R, false);                 \
-        }                                                                    \
-    } while (0)
+    auto eval_with = [&](auto r_tag) {
+        constexpr int R = decltype(r_tag)::value;
+        with_mode<false>(out, a.blk_max != nullptr, [&](auto mode) {
+            constexpr int kOut = decltype(mode)::value;
+            if constexpr (R * kThr <= kCapBig) {
+                if (persistent) {
+                    if (narrow) hipLaunchKernelGGL((eval_stream_kernel<kThr, R, true, kOut>), grid, block, 0, stream, a);
+                    else hipLaunchKernelGGL((eval_stream_kernel<kThr, R, false, kOut>), grid, block, 0, stream, a);
+                    return;
+                }
+            }
+            if (narrow) hipLaunchKernelGGL((eval_kernel<kThr, R, true, kOut>), grid, block, 0, stream, a);
+            else hipLaunchKernelGGL((eval_kernel<kThr, R, false, kOut>), grid, block, 0, stream, a);
+        });
+    };
+    bool launched = false;
     // (with 512 threads only the smallest register capacity leaves room for the next plan's intervals)
     if (kThr == 512 && cap != kCapSmall) persistent = false;
     if (persistent) {   // one workgroup per resident slot, the plans dealt evenly among them
@@ -866,39 +897,39 @@ int launch_geometry(const tensile_tas *tas, Workspace &ws, const EvalArgs &a, in
         const int64_t rounds = (blocks + slots - 1) / slots;
         grid = dim3(static_cast<uint32_t>((blocks + rounds - 1) / rounds));
     }
-    if (out == 3 && kThr == 1024 && !persistent) {   // nontemporal rows: compiled for the large geometry only (long rows use no other)
-#define TS_LAUNCH_NT(R)                                                                                  \
-    do {                                                                                                 \
-        if (narrow) hipLaunchKernelGGL((eval_kernel<1024, R, true, 3>), grid, block, 0, stream, a);      \
-        else hipLaunchKernelGGL((eval_kernel<1024, R, false, 3>), grid, block, 0, stream, a);            \
-    } while (0)
-        if (cap == kCapSmall) TS_LAUNCH_NT(kCapSmall / 1024);
-        else if (cap == kCapMid) TS_LAUNCH_NT(kCapMid / 1024);
-        else if (cap == kCapTail) TS_LAUNCH_NT(kCapTail / 1024);
-        else TS_LAUNCH_NT(kCapBig / 1024);
-#undef TS_LAUNCH_NT
-    } else if (cap == kCapSmall) TS_LAUNCH_EVAL(kCapSmall / kThr);
-    else if (cap == kCapMid) TS_LAUNCH_EVAL(kCapMid / kThr);
-    else if (cap == kCapTail && kThr == 1024) {   // (one workgroup per plan only: the host does not ask for the persistent grid here)
-        if (narrow) TS_LAUNCH_OUT(eval_kernel, 1024, kCapTail / 1024, true);
-        else TS_LAUNCH_OUT(eval_kernel, 1024, kCapTail / 1024, false);
-    } else TS_LAUNCH_EVAL(kCapBig / kThr);
+    if constexpr (kThr == 1024) {
+        if (out == 3 && !persistent) {   // nontemporal rows: compiled for the large geometry only (long rows use no other)
+            auto nt_with = [&](auto r_tag) {
+                constexpr int R = decltype(r_tag)::value;
+                auto go = [&](auto mode) {
+                    if (narrow) hipLaunchKernelGGL((eval_kernel<1024, R, true, decltype(mode)::value>), grid, block, 0, stream, a);
+                    else hipLaunchKernelGGL((eval_kernel<1024, R, false, decltype(mode)::value>), grid, block, 0, stream, a);
+                };
+                if (a.blk_max) go(std::integral_constant<int, 3 + kOutPieces>{});
+                else go(std::integral_constant<int, 3>{});
+            };
+            if (cap == kCapSmall) nt_with(std::integral_constant<int, kCapSmall / 1024>{});
+            else if (cap == kCapMid) nt_with(std::integral_constant<int, kCapMid / 1024>{});
+            else if (cap == kCapTail) nt_with(std::integral_constant<int, kCapTail / 1024>{});
+            else nt_with(std::integral_constant<int, kCapBig / 1024>{});
+            launched = true;
+        } else if (cap == kCapTail) {   // (one workgroup per plan only: the host does not ask for the persistent grid here)
+            eval_with(std::integral_constant<int, kCapTail / 1024>{});
+            launched = true;
+        }
+    }
+    if (launched) {
+    } else if (cap == kCapSmall) eval_with(std::integral_constant<int, kCapSmall / kThr>{});
+    else if (cap == kCapMid) eval_with(std::integral_constant<int, kCapMid / kThr>{});
+    else eval_with(std::integral_constant<int, kCapBig / kThr>{});
     TS_HIP(hipGetLastError());
-#undef TS_LAUNCH_EVAL
-#undef TS_LAUNCH_OUT
     if (a.n_intervals > a.tail_threshold) {   // (otherwise no plan can be longer than the registers hold)
         const int64_t resident = static_cast<int64_t>(tas->num_cus) * (1024 / kThr);
         const dim3 tgrid(static_cast<uint32_t>(blocks < resident ? blocks : resident));
-#define TS_LAUNCH_TAIL(NARROW)                                                                                            \
-    do {                                                                                                                  \
-        if (out == 3 && kThr == 1024) hipLaunchKernelGGL((eval_tail_kernel<1024, NARROW, 3>), tgrid, block, 0, stream, a); \
-        else if (out >= 2) hipLaunchKernelGGL((eval_tail_kernel<kThr, NARROW, 2>), tgrid, block, 0, stream, a);   \
-        else if (out == 1) hipLaunchKernelGGL((eval_tail_kernel<kThr, NARROW, 1>), tgrid, block, 0, stream, a);   \
-        else hipLaunchKernelGGL((eval_tail_kernel<kThr, NARROW, 0>), tgrid, block, 0, stream, a);                 \
-    } while (0)
-        if (narrow) TS_LAUNCH_TAIL(true);
-        else TS_LAUNCH_TAIL(false);
-#undef TS_LAUNCH_TAIL
+        with_mode<kThr == 1024>(out, a.blk_max != nullptr, [&](auto mode) {
+            if (narrow) hipLaunchKernelGGL((eval_tail_kernel<kThr, true, decltype(mode)::value>), tgrid, block, 0, stream, a);
+            else hipLaunchKernelGGL((eval_tail_kernel<kThr, false, decltype(mode)::value>), tgrid, block, 0, stream, a);
+        });
     }
     TS_HIP(hipGetLastError());
     return TENSILE_OK;
@@ -912,22 +943,17 @@ int launch_tiny_geometry(const tensile_tas *tas, Workspace &ws, const EvalArgs &
     const dim3 grid(static_cast<uint32_t>(blocks)), block(kThr);
     const int64_t resident = static_cast<int64_t>(tas->num_cus) * (1024 / kThr);
     const dim3 tgrid(static_cast<uint32_t>(blocks < resident ? blocks : resident));
-#define TS_LAUNCH_TINY(NARROW, OUT)                                                                                  \
-    do {                                                                                                             \
-        hipLaunchKernelGGL((eval_kernel<kThr, kCapSmall / kThr, NARROW, OUT>), grid, block, 0, stream, a);           \
-        if (a.n_intervals > a.tail_threshold) /* else no plan can be longer than the registers hold */              \
-            hipLaunchKernelGGL((eval_tail_kernel<kThr, NARROW, OUT>), tgrid, block, 0, stream, a);                   \
-    } while (0)
-    if (narrow) {
-        if (out >= 2) TS_LAUNCH_TINY(true, 2);
-        else if (out == 1) TS_LAUNCH_TINY(true, 1);
-        else TS_LAUNCH_TINY(true, 0);
-    } else {
-        if (out >= 2) TS_LAUNCH_TINY(false, 2);
-        else if (out == 1) TS_LAUNCH_TINY(false, 1);
-        else TS_LAUNCH_TINY(false, 0);
-    }
-#undef TS_LAUNCH_TINY
+    const bool tail = a.n_intervals > a.tail_threshold;   // (else no plan can be longer than the registers hold)
+    with_mode<false>(out, a.blk_max != nullptr, [&](auto mode) {
+        constexpr int kOut = decltype(mode)::value;
+        if (narrow) {
+            hipLaunchKernelGGL((eval_kernel<kThr, kCapSmall / kThr, true, kOut>), grid, block, 0, stream, a);
+            if (tail) hipLaunchKernelGGL((eval_tail_kernel<kThr, true, kOut>), tgrid, block, 0, stream, a);
+        } else {
+            hipLaunchKernelGGL((eval_kernel<kThr, kCapSmall / kThr, false, kOut>), grid, block, 0, stream, a);
+            if (tail) hipLaunchKernelGGL((eval_tail_kernel<kThr, false, kOut>), tgrid, block, 0, stream, a);
+        }
+    });
     TS_HIP(hipGetLastError());
     return TENSILE_OK;
 }

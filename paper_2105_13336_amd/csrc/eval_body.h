@@ -54,6 +54,7 @@ struct EvalLds {
     int64_t carry_part[Geom<kThr>::kWaves];
     int64_t red_mx[Geom<kThr>::kWaves], red_mn[Geom<kThr>::kWaves];
     int32_t red_arg[Geom<kThr>::kWaves];
+    int64_t piece_max[2][2 * Geom<kThr>::kWaves];   // (kOutPieces) of the tile at hand and of the one before, even and odd tiles
 };
 
 // Workgroup w of a launch -> (plan, segment).  XCD-aware: block w runs on XCD w % 8; XCD x gets the plans
@@ -83,6 +84,45 @@ __device__ __forceinline__ void best_merge(Best &a, int64_t mx, int32_t arg, int
 }
 
 typedef long long ll2 __attribute__((ext_vector_type(2)));
+typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
+
+// The maxima of the row's 256-step pieces, for a scoring pass that follows (kernels with kOutPieces in their output mode,
+// a.blk_max).  A piece is 32 lanes of 8 steps: their maxima (mx) meet in lanes 31 and 63, which put them into the tile's
+// list in LDS; one wavefront stores the list, whole lines, during the next tile.  (Stored by every wavefront itself, two
+// lanes of a store each, it cost as much: 24,000-step rows 0.42 ms without the maxima, 0.44 with, either way.)
+__device__ __forceinline__ void keep_piece_maxima(int64_t *list, int64_t mx, int wave, int lane) {
+    static_assert(32 * kVpt == kScoreMini, "half a wavefront per piece");
+    // (neighbouring steps nearly always share their upper halves: one instruction per step of the reduction)
+    const int32_t hi = static_cast<int32_t>(mx >> 32);
+    if (__builtin_amdgcn_ballot_w64(hi != __builtin_amdgcn_readfirstlane(hi)) == 0) {   // (wave-uniform)
+        uint32_t lo = static_cast<uint32_t>(mx);
+        auto step = [&](uint32_t y) { lo = y > lo ? y : lo; };
+        step(__builtin_amdgcn_update_dpp(0, static_cast<int>(lo), 0x111, 0xf, 0xf, true));
+        step(__builtin_amdgcn_update_dpp(0, static_cast<int>(lo), 0x112, 0xf, 0xf, true));
+        step(__builtin_amdgcn_update_dpp(0, static_cast<int>(lo), 0x114, 0xf, 0xf, true));
+        step(__builtin_amdgcn_update_dpp(0, static_cast<int>(lo), 0x118, 0xf, 0xf, true));
+        step(__builtin_amdgcn_update_dpp(0, static_cast<int>(lo), 0x142, 0xa, 0xf, true));
+        mx = static_cast<int64_t>((static_cast<uint64_t>(static_cast<uint32_t>(hi)) << 32) | lo);
+    } else {
+        mx = max64(mx, dpp_move<0x111, 0xf>(mx, INT64_MIN));
+        mx = max64(mx, dpp_move<0x112, 0xf>(mx, INT64_MIN));
+        mx = max64(mx, dpp_move<0x114, 0xf>(mx, INT64_MIN));
+        mx = max64(mx, dpp_move<0x118, 0xf>(mx, INT64_MIN));
+        mx = max64(mx, dpp_move<0x142, 0xa>(mx, INT64_MIN));
+    }
+    if ((lane & 31) == 31) list[2 * wave + (lane >> 5)] = mx;
+}
+// The list of the tile that starts at step tile_lo of the row whose pieces are at `pieces`; one wavefront.
+template <int kWaves>
+__device__ __forceinline__ void store_piece_maxima(const EvalArgs &a, int64_t *pieces, int32_t tile_lo, const int64_t *list, int lane) {
+    const int32_t k = tile_lo / kScoreMini + lane;
+    if (lane < 2 * kWaves && k < (a.T + kScoreMini - 1) / kScoreMini) pieces[k] = list[lane];   // (T is at most 2^31 - 2^20)
+}
+__device__ __forceinline__ int64_t *pieces_of(const EvalArgs &a, int64_t plan) {
+    return a.blk_max + plan * ((a.T + kScoreMini - 1) / kScoreMini);
+}
+
+constexpr int kOutPieces = 4;   // (flag of the kernels' output mode)
 
 // Sizes are kept in registers either as int64 (kNarrow == false) or, when every
 // size is a multiple of 2^size_shift and fits 32 bits after the shift, as uint32
@@ -140,7 +180,7 @@ __device__ __forceinline__ bool applies(const EvalArgs &a, int32_t i, int32_t o,
 // batch; a workgroup whose plan belongs to the other kernel exits at once.
 // kOut: 0 = no footprint rows are written (peaks only), 1 = rows written with 8-byte stores
 // (odd T or unaligned buffer), 2 = with 16-byte stores, 3 = with nontemporal 16-byte stores (long rows,
-// see launch_eval).  A compile-time property so that every path through the tile loop issues the
+// see launch_eval); + kOutPieces: the maxima of the rows' pieces too (a.blk_max).  A compile-time property so that every path through the tile loop issues the
 // same memory operations: the compiler's waits for the loop's loads count the stores issued after
 // them only when no branch surrounds those stores.
 // kBinned: the batch went through bin_kernel first; nothing is kept in registers (R is 1 and unused),
@@ -157,7 +197,8 @@ template <int kThr, int R, bool kTail, bool kNarrow, int kOut, bool kBinned = fa
 __device__ __forceinline__ void eval_body(const EvalArgs &a, const int32_t plan, const int32_t seg, EvalLds<kThr> &L,
                                           Best *result = nullptr) {
     static_assert(!kBinFast || kBinned, "kBinFast is a form of the binned kernel");
-    constexpr bool kStore = kOut != 0, kVec16 = kOut >= 2;
+    constexpr int kMode = kOut & ~kOutPieces;
+    constexpr bool kStore = kMode != 0, kVec16 = kMode >= 2, kPieces = (kOut & kOutPieces) != 0;
     constexpr int kWaves = Geom<kThr>::kWaves, kTile = Geom<kThr>::kTile, kTileCells = Geom<kThr>::kTileCells;
     int64_t *const delta = L.delta, *const stage_all = L.stage_all, *const wave_tot = L.wave_tot, *const carry_part = L.carry_part;
     int64_t *const red_mx = L.red_mx, *const red_mn = L.red_mn;
@@ -352,7 +393,7 @@ __device__ __forceinline__ void eval_body(const EvalArgs &a, const int32_t plan,
         const ll2 x = (reinterpret_cast<const ll2 *>(stage) + lane + (lane >> 4))[68 * j];
         if (kVec16 && t_hi - t_lo == kTile) {
             ll2 *const at = reinterpret_cast<ll2 *>(row + wave_t0) + lane + 64 * j;
-            if constexpr (kOut == 3) __builtin_nontemporal_store(x, at);
+            if constexpr (kMode == 3) __builtin_nontemporal_store(x, at);
             else *at = x;
         } else {
             const int32_t t = wave_t0 + 2 * (j * 64 + lane);
@@ -471,6 +512,9 @@ __device__ __forceinline__ void eval_body(const EvalArgs &a, const int32_t plan,
         if constexpr (kPrev) store_part(tile_lo - kTile, tile_lo, 1);
         EVAL_MARK(1);
         __syncthreads();
+        if constexpr (kPieces && !kFirst) {
+            if (wave_u == kWaves - 1) store_piece_maxima<kWaves>(a, pieces_of(a, plan), tile_lo - kTile, L.piece_max[(tile_lo / kTile + 1) & 1], lane);
+        }
         EVAL_MARK(2);
 
         // ---- local scan of this lane's 8 cells; the cells receive the next tile's dMF0.  In the
@@ -522,6 +566,7 @@ __device__ __forceinline__ void eval_body(const EvalArgs &a, const int32_t plan,
 
         // ---- reduce
         const int32_t t0 = tile_lo + my;
+        int64_t lane_mx;
         if (t0 + kVpt <= tile_hi) {
             // The lane's 8 values almost always share their upper 32 bits; then max and min are
             // those of the (unsigned) lower halves, single instructions without a condition code.
@@ -556,10 +601,13 @@ __device__ __forceinline__ void eval_body(const EvalArgs &a, const int32_t plan,
                     if (v[j] == cm) best.arg = t0 + j;
             }
             best.mn = cn < best.mn ? cn : best.mn;
+            lane_mx = cm;
         } else {
+            lane_mx = INT64_MIN;
 #pragma unroll
             for (int j = 0; j < kVpt; ++j) {
                 if (t0 + j < tile_hi) {
+                    lane_mx = max64(lane_mx, v[j]);
                     if (v[j] > best.mx) {
                         best.mx = v[j];
                         best.arg = t0 + j;
@@ -568,6 +616,8 @@ __device__ __forceinline__ void eval_body(const EvalArgs &a, const int32_t plan,
                 }
             }
         }
+
+        if constexpr (kPieces) keep_piece_maxima(L.piece_max[(tile_lo / kTile) & 1], lane_mx, wave, lane);
 
         // ---- park the results in the wave's staging area (lane-contiguous, skewed); they are
         // stored during the next iteration, or after the loop
@@ -669,6 +719,9 @@ __device__ __forceinline__ void eval_body(const EvalArgs &a, const int32_t plan,
         red_arg[wave] = best.arg;
     }
     __syncthreads();
+    if constexpr (kPieces) {
+        if (wave_u == kWaves - 1) store_piece_maxima<kWaves>(a, pieces_of(a, plan), last_lo, L.piece_max[(last_lo / kTile) & 1], lane);
+    }
     if (tid == 0) {
 #pragma unroll
         for (int u = 1; u < kWaves; ++u) best_merge(best, red_mx[u], red_arg[u], red_mn[u]);

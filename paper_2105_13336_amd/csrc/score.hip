@@ -14,14 +14,14 @@
 // kernel on a second index in which every gap is filed with o = p, and any interval
 // of a tensor cancels its entries.
 //
-// Per plan, one workgroup of 512 threads:
-//   1. the maxima of the row's blocks of 256 steps (longer blocks for rows of more
-//      than 131,072 or 262,144 steps, see kTab), streamed from the row; then their prefix and suffix
+// Per plan, one workgroup of 256 or 512 threads (Shape):
+//   1. the maxima of the row's blocks of 256 steps (more for rows of over 262,144
+//      steps), streamed from the row or taken from the evaluation; then their prefix and suffix
 //      maxima (two wavefronts), while the plan's own intervals cancel candidates:
 //      an interval inside the gap of an entry of its tensor (Alg. 2 of the paper only
 //      takes tensors that are not swapped out yet).  A per-bucket bit filter over
-//      tensors, kept in LDS, turns most intervals away; the others probe the
-//      bucket's hash table;
+//      tensors, kept in LDS, turns most intervals away and leads the others to their
+//      tensor's entries;
 //   2. every entry with o < t* < q that is not cancelled is bounded from both sides by
 //      the block maxima (score_body.h: classify).  Most are decided by that; the
 //      open ones are listed, and the few blocks of the row that they lie in - those
@@ -30,15 +30,17 @@
 //      in LDS (zeros and -1, then the entries, which are stored in tensor order) and writes whole pieces of the rows, so
 //      that each output line goes to memory once.  (What step 2 found is not kept but found
 //      again: it costs a few LDS reads per entry and no space.)
-// Nothing is kept per entry but a bit or two, so a workgroup needs a third of a CU's LDS, and the phases of
-// three plans overlap on a CU.
-// What bounds it: HBM (rows in, output rows out).  Measured against the kernel before it (one workgroup of 1024 threads per
-// CU that ran two 64-bit max-scans over every 256 steps of the row and met every candidate's o and q on the way, its
-// phases one after the other with nothing beside them): 4,096 plans of 6,000 steps 180 -> 127 us, 8,192 of 24,000
-// 778 -> 633, 16,384 of 50,000 2.72 -> 2.69 ms (4.8 TB/s of what has to move), 1,024 of 10^6 2.43 -> 2.12 ms.
+// Nothing is kept per entry but a bit or two, so a workgroup needs a third of a CU's LDS or less, and the phases of
+// several plans overlap on a CU.
+// What bounds it: HBM (rows in unless the evaluation hands over their maxima, output rows out) on long rows, the
+// chains of dependent loads of a plan's phases on short ones.  Measured against the kernel before it (one workgroup of 1024
+// threads per CU that ran two 64-bit max-scans over every 256 steps of the row and met every candidate's o and q on the way, its
+// phases one after the other with nothing beside them): scoring by itself, 16,384 plans of 50,000 steps 2.72 -> 2.6 ms
+// (4.9 TB/s of what has to move), 1,024 of 10^6 2.43 -> 2.04 ms; evaluation and scoring in one call, 4,096 plans of 6,000
+// steps 243 -> 141 us, 8,192 of 24,000 1.20 -> 0.88 ms, 1,111 ragged ones of 33,331 216 -> 124 us.
 // A plan with more open entries than the list holds, or a bucket with more entries than there are flags
-// (kWindow), takes the general form: rows cleared first, then the entries in runs of 512, written one by one.
-#include <atomic>
+// (kWindow), takes the general form: rows cleared first, then the entries in runs of one per thread, written one by one.
+#include <type_traits>
 
 #include "score_body.h"
 
@@ -46,14 +48,21 @@ namespace tensile {
 
 namespace {
 
-constexpr int kThr = 512, kWaves = kThr / 64;
-static_assert(kWaves == kScoreWaves, "the index holds where each wavefront's tensors start");
-
-// Blocks whose maxima fit in LDS: rows of up to 131,072 steps in blocks of 256 steps; longer rows have twice the table and blocks of
-// as many pieces of 256 steps as that takes.
-constexpr int kTabShort = 512, kTabLong = 1024;
-
-constexpr int kBufs = kWaves / 2;      // wavefronts that read the row's blocks for the open entries (the others' LDS is the stage's)
+// The workgroup and its table of block maxima, by the length of the rows.  Up to 32,768 steps, when the maxima are given: 256
+// threads and 128 blocks, six workgroups per CU, whose chains of short dependent loads cover each other (against 512
+// threads, with evaluation: 4,096 plans of 6,000 steps 161 -> 141 us, 8,192 of 24,000 steps 912 -> 876).  Else, up to 131,072
+// steps: 512 threads, 512 blocks, three per CU (streaming 4,096 rows of 24,000 steps 336 us, with 256 threads 381; 50,000
+// steps 2.62 ms and 2.69).  Longer rows: blocks of as many pieces of 256 steps as fit them into 1,024 blocks, 256
+// threads, four per CU, plans dealt to as many workgroups as are resident (10^6 steps 2.04 ms; with 512 threads 2.17).
+constexpr int kTabSmall = 128, kTabShort = 512, kTabLong = 1024;
+template <int kTab>
+struct Shape {
+    static constexpr int kThr = kTab == kTabShort ? 512 : 256, kWaves = kThr / 64;
+    static constexpr int kSpans = kScoreWaves / kWaves;    // the index holds where each of kScoreWaves ranges of tensors starts
+    static constexpr int kBufs = kWaves / 2;               // wavefronts that read the row's blocks for the open entries
+    static constexpr int kEu = kTab == kTabLong ? 4 : 6;   // wavefronts per SIMD that fit
+    static_assert(kSpans * kWaves == kScoreWaves, "whole ranges per wavefront");
+};
 
 struct StageBuf {
     int64_t score[kStage];
@@ -63,15 +72,16 @@ struct StageBuf {
 template <int kTab>
 struct ScoreLds {
     union {
-        __attribute__((aligned(16))) StageBuf stage[kWaves];
-        __attribute__((aligned(16))) SpanBuf bufs[kBufs];
+        __attribute__((aligned(16))) StageBuf stage[Shape<kTab>::kWaves];
+        __attribute__((aligned(16))) SpanBuf bufs[Shape<kTab>::kBufs];
     };
     BlockMaxima<kTab> mx;
-    OpenList<kThr> open;
+    OpenList<Shape<kTab>::kThr> open;
     uint64_t cancelled[kWindow / 64];    // one bit per entry of the window
     uint64_t open_bits[kWindow / 64];    // the entry is on the open list, at open_base + its rank within the word
     uint16_t open_base[kWindow / 64];
     uint32_t filter[kFilterWords];
+    int32_t filter_base[kFilterWords + 1];
     uint32_t need[kTab / 32];            // blocks of the row that open entries lie in
 };
 
@@ -80,7 +90,7 @@ struct ScoreLds {
 // kStream (rows of more than 131,072 steps): the row is read once, past the L2's allocation.
 template <bool kVec, bool kStream, int kTab>
 __device__ __forceinline__ void stream_block_maxima(const ScoreArgs &a, const int64_t *MF, BlockMaxima<kTab> &mx, int wave, int lane) {
-    constexpr int kAhead = 2;
+    constexpr int kAhead = 2, kWaves = Shape<kTab>::kWaves;
     const int ps = a.piece_shift;
     const int32_t mine = wave < a.n_blk ? (a.n_blk - wave + kWaves - 1) / kWaves : 0;   // blocks of this wavefront
     const int32_t n = mine << ps;
@@ -141,9 +151,25 @@ __device__ __forceinline__ void stream_block_maxima(const ScoreArgs &a, const in
     }
 }
 
-// kBig: rows of more than 131,072 steps.  kVec: the footprint rows are 16-byte aligned and T is even.
-template <bool kBig, bool kVec>
-__device__ __forceinline__ void score_plan(const ScoreArgs &a, const int32_t b, ScoreLds<kBig ? kTabLong : kTabShort> &L, int32_t &filter_of) {
+// Step 1 where the maxima of the row's pieces are known (the evaluation wrote them): the row is not read.
+template <int kTab>
+__device__ __forceinline__ void load_block_maxima(const ScoreArgs &a, const int64_t *pieces, BlockMaxima<kTab> &mx, int tid) {
+    const int ps = a.piece_shift;
+    for (int32_t k = tid; k < a.n_blk; k += Shape<kTab>::kThr) {
+        const int32_t p0 = k << ps, p1 = min(p0 + (1 << ps), a.n_mini);
+        int64_t v = pieces[p0];
+        for (int32_t p = p0 + 1; p < p1; ++p) v = max64(v, pieces[p]);
+        mx.pm[k + 1] = v;
+        mx.sm[k] = v;
+    }
+}
+
+// kVec: the footprint rows are 16-byte aligned and T is even.
+// kTable: the maxima of the rows' pieces are given.
+template <int kTab, bool kVec, bool kTable>
+__device__ __forceinline__ void score_plan(const ScoreArgs &a, const int32_t b, ScoreLds<kTab> &L, int32_t &filter_of) {
+    constexpr int kThr = Shape<kTab>::kThr, kSpans = Shape<kTab>::kSpans, kBufs = Shape<kTab>::kBufs;
+    constexpr bool kBig = kTab == kTabLong;
     // (the thread index is made opaque once per plan: everything derived from it is then
     // recomputed where it is used instead of being held in registers across the whole loop)
     int tid = threadIdx.x;
@@ -156,7 +182,6 @@ __device__ __forceinline__ void score_plan(const ScoreArgs &a, const int32_t b, 
     int32_t *wout = a.win_out ? a.win_out + static_cast<int64_t>(b) * a.N : nullptr;
     int32_t *win = a.win_in ? a.win_in + static_cast<int64_t>(b) * a.N : nullptr;
     PROF_START;
-
     const bool has_peak = tstar >= 0 && tstar < a.T;     // else not produced by the evaluator: no candidate
     const int32_t bk = has_peak ? tstar >> a.bucket_shift : 0;
     const int32_t e0 = uniform_load(a.bucket_off, bk), n_e = has_peak ? uniform_load(a.bucket_off, bk + 1) - e0 : 0;
@@ -169,33 +194,33 @@ __device__ __forceinline__ void score_plan(const ScoreArgs &a, const int32_t b, 
         clear_rows();
         return;
     }
-    const int32_t *hash_dir = reinterpret_cast<const int32_t *>(a.hash_dir);
-    const int2 hd = make_int2(uniform_load(hash_dir, 2 * bk), uniform_load(hash_dir, 2 * bk + 1));
     int64_t k0 = uniform_load(a.plan_offsets, b), k1 = uniform_load(a.plan_offsets, b + 1);
     if (k0 < 0) k0 = 0;
     if (k1 > a.n_intervals) k1 = a.n_intervals;
     const int bs = a.piece_shift + 8;
-    const int2 *const oq_of = a.cand_oq + e0;
-    const int32_t *const tensor_of = a.cand_tensor + e0;
+    const int4 *const entries = a.cand + e0;
     const int64_t *const size_of = a.cand_size + e0;
 
     // ---- 1
     __syncthreads();       // the previous plan has finished with the LDS
     if (filter_of != bk) {
         const uint32_t *src = a.filter + static_cast<int64_t>(bk) * a.filter_words;
+        const int32_t *src_base = a.filter_base + static_cast<int64_t>(bk) * (a.filter_words + 1);
         for (int32_t k = tid; k < a.filter_words; k += kThr) L.filter[k] = src[k];
+        for (int32_t k = tid; k <= a.filter_words; k += kThr) L.filter_base[k] = src_base[k];
         filter_of = bk;
     }
     for (int32_t k = tid; k < kWindow / 64 && k * 64 < n_e; k += kThr) L.cancelled[k] = 0;
     for (int32_t k = tid; k * 32 < a.n_blk; k += kThr) L.need[k] = 0;
     if (tid == 0) L.open.n = 0;
-    stream_block_maxima<kVec, kBig>(a, MF, L.mx, wave, lane);
+    if constexpr (kTable) load_block_maxima(a, a.blk_max + static_cast<int64_t>(b) * a.n_mini, L.mx, tid);
+    else stream_block_maxima<kVec, kBig>(a, MF, L.mx, wave, lane);
     PROF_MARK(0);
     __syncthreads();
     PROF_MARK(1);
     scan_block_maxima(L.mx, a.n_blk, wave, lane);
     PROF_MARK(2);
-    cancel_by_plan<kThr>(a, k0, k1, hd, e0, n_e, 0, n_e < kWindow ? n_e : kWindow, L.filter, reinterpret_cast<uint32_t *>(L.cancelled), tid);
+    cancel_by_plan<kThr>(a, k0, k1, entries, n_e, 0, n_e < kWindow ? n_e : kWindow, L.filter, L.filter_base, reinterpret_cast<uint32_t *>(L.cancelled), tid);
     PROF_MARK(3);
     __syncthreads();
     PROF_MARK(4);
@@ -244,7 +269,8 @@ __device__ __forceinline__ void score_plan(const ScoreArgs &a, const int32_t b, 
         for (int32_t kb = 0; kb < n_e; kb += kThr) {
             const int32_t k = kb + tid, kc = k < n_e ? k : n_e - 1;
             if (kb + wave * 64 >= n_e) break;            // (wave-uniform)
-            const int2 oq = oq_of[kc];
+            const int4 c = entries[kc];
+            const int2 oq = make_int2(c.w, c.z);
             list_open(look(k, kc, oq, size_of[kc]), oq, kb + wave * 64);
         }
         __syncthreads();
@@ -260,17 +286,19 @@ __device__ __forceinline__ void score_plan(const ScoreArgs &a, const int32_t b, 
     // ---- 3
     if (!general) {
         StageBuf &st = L.stage[wave];
-        const bool wide = ((reinterpret_cast<uintptr_t>(score) | reinterpret_cast<uintptr_t>(wout) | reinterpret_cast<uintptr_t>(win)) & 15) == 0;
-        const int32_t t_end = min((wave + 1) * a.tspan, a.N);
+        // With 16-byte aligned arrays the chunks start where the plan's rows are aligned too: `shift` tensors later, when
+        // N is no multiple of four (the first `shift` tensors are a chunk of their own).
+        const bool wide = ((reinterpret_cast<uintptr_t>(a.score) | reinterpret_cast<uintptr_t>(a.win_out) | reinterpret_cast<uintptr_t>(a.win_in)) & 15) == 0;
+        const int32_t shift = wide ? static_cast<int32_t>((0u - static_cast<uint32_t>(b) * static_cast<uint32_t>(a.N)) & 3u) : 0;
+        const int32_t t_begin = wave == 0 ? (shift ? shift - kStage : 0) : wave * kSpans * a.tspan + shift;
+        const int32_t t_end = min((wave + 1) * kSpans * a.tspan + shift, a.N);
         // the wavefront's entries, 64 at a time: those at hand, examined, and the next ones on their way
-        int32_t k = uniform_load(a.wave_ptr, static_cast<int64_t>(bk) * kWaves + wave);
-        int32_t next_tensor;
-        int2 next_oq;
+        int32_t k = uniform_load(a.wave_ptr, static_cast<int64_t>(bk) * kScoreWaves + wave * kSpans);
+        int4 next;
         int64_t next_size;
         auto request = [&](int32_t at) {
             const int32_t kc = at + lane < n_e ? at + lane : n_e - 1;
-            next_tensor = tensor_of[kc];
-            next_oq = oq_of[kc];
+            next = entries[kc];
             next_size = size_of[kc];
         };
         int32_t tensor, o, q;
@@ -279,10 +307,10 @@ __device__ __forceinline__ void score_plan(const ScoreArgs &a, const int32_t b, 
         auto take_up = [&]() {                           // the requested entries become those at hand; request the next
             const int32_t kk = k + lane;
             const int32_t kc = kk < n_e ? kk : n_e - 1;
-            const Entry e = look(kk, kc, next_oq, next_size);
-            tensor = kk < n_e ? next_tensor : INT32_MAX;
-            o = next_oq.x;
-            q = next_oq.y;
+            const Entry e = look(kk, kc, make_int2(next.w, next.z), next_size);
+            tensor = kk < n_e ? next.x : INT32_MAX;
+            o = next.w;
+            q = next.z;
             has = e.valid;
             value = P - outside_of(e, kc);
             request(k + 64);
@@ -290,8 +318,7 @@ __device__ __forceinline__ void score_plan(const ScoreArgs &a, const int32_t b, 
         int32_t pos = 0;                                 // entries at hand that are done
         request(k);
         take_up();
-        for (int32_t t0 = wave * a.tspan; t0 < t_end; t0 += kStage) {
-            const int32_t n_t = min(kStage, a.N - t0);
+        for (int32_t t0 = t_begin; t0 < t_end; t0 += kStage) {
             __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
             reinterpret_cast<ll2 *>(st.score)[lane] = ll2{0, 0};
             reinterpret_cast<ll2 *>(st.win)[lane] = ll2{-1, -1};
@@ -299,7 +326,7 @@ __device__ __forceinline__ void score_plan(const ScoreArgs &a, const int32_t b, 
             __builtin_amdgcn_wave_barrier();
             for (;;) {                                   // (wave-uniform)
                 const bool take = lane >= pos && tensor < t0 + kStage;
-                if (take && has) {
+                if (take && has && tensor >= t0) {       // (one below t0 belongs to the wavefront before)
                     st.score[tensor - t0] = value;
                     st.win[0][tensor - t0] = o;
                     st.win[1][tensor - t0] = q;
@@ -312,7 +339,7 @@ __device__ __forceinline__ void score_plan(const ScoreArgs &a, const int32_t b, 
             }
             __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
             __builtin_amdgcn_wave_barrier();
-            if (wide && n_t == kStage) {
+            if (wide && t0 >= 0 && t0 + kStage <= a.N) {
                 store_out<kBig>(reinterpret_cast<ll2 *>(score + t0) + lane, reinterpret_cast<const ll2 *>(st.score)[lane]);
                 int32_t *const dst = lane < 32 ? wout : win;     // (32 vectors of four each)
                 if (dst) store_out<kBig>(reinterpret_cast<i4 *>(dst + t0) + (lane & 31), reinterpret_cast<const i4 *>(st.win)[lane]);
@@ -320,7 +347,7 @@ __device__ __forceinline__ void score_plan(const ScoreArgs &a, const int32_t b, 
 #pragma unroll
                 for (int j = 0; j < kStage / 64; ++j) {
                     const int32_t u = j * 64 + lane;
-                    if (u < n_t) {
+                    if (t0 + u >= 0 && t0 + u < a.N) {
                         score[t0 + u] = st.score[u];
                         if (wout) wout[t0 + u] = st.win[0][u];
                         if (win) win[t0 + u] = st.win[1][u];
@@ -339,7 +366,7 @@ __device__ __forceinline__ void score_plan(const ScoreArgs &a, const int32_t b, 
         if (w_lo > 0) {                                  // (the first window's flags are there)
             for (int32_t k = tid; k < kWindow / 64; k += kThr) L.cancelled[k] = 0;
             __syncthreads();
-            cancel_by_plan<kThr>(a, k0, k1, hd, e0, n_e, w_lo, w_n, L.filter, reinterpret_cast<uint32_t *>(L.cancelled), tid);
+            cancel_by_plan<kThr>(a, k0, k1, entries, n_e, w_lo, w_n, L.filter, L.filter_base, reinterpret_cast<uint32_t *>(L.cancelled), tid);
         }
         for (int32_t kb = 0; kb < w_n; kb += kThr) {
             __syncthreads();       // everybody has finished with the list and the blocks of the previous run (and clearing the rows)
@@ -347,7 +374,8 @@ __device__ __forceinline__ void score_plan(const ScoreArgs &a, const int32_t b, 
             if (tid == 0) L.open.n = 0;
             __syncthreads();
             const int32_t k = w_lo + kb + tid, kc = k < n_e ? k : n_e - 1;
-            const int2 oq = oq_of[kc];
+            const int4 c = entries[kc];
+            const int2 oq = make_int2(c.w, c.z);
             const Entry e = look(k, kc - w_lo, oq, size_of[kc]);
             if (kb + wave * 64 < w_n) list_open(e, oq, kb + wave * 64);
             __syncthreads();
@@ -357,7 +385,7 @@ __device__ __forceinline__ void score_plan(const ScoreArgs &a, const int32_t b, 
                 __syncthreads();
             }
             if (e.valid && kb + tid < w_n) {
-                const int32_t tensor = tensor_of[kc];
+                const int32_t tensor = c.x;
                 score[tensor] = P - outside_of(e, kb + tid);
                 if (wout) wout[tensor] = oq.x;
                 if (win) win[tensor] = oq.y;
@@ -367,11 +395,12 @@ __device__ __forceinline__ void score_plan(const ScoreArgs &a, const int32_t b, 
 }
 
 // Workgroup w takes the plans w, w + grid, ...
-template <bool kBig, bool kVec>
-__global__ __launch_bounds__(kThr) __attribute__((amdgpu_waves_per_eu(6, 6))) void score_kernel(const ScoreArgs a) {
-    __shared__ ScoreLds<kBig ? kTabLong : kTabShort> lds;
+template <int kTab, bool kVec, bool kTable>
+__global__ __launch_bounds__(Shape<kTab>::kThr) __attribute__((amdgpu_waves_per_eu(Shape<kTab>::kEu, Shape<kTab>::kEu))) void score_kernel(
+    const ScoreArgs a) {
+    __shared__ ScoreLds<kTab> lds;
     int32_t filter_of = -1;      // bucket whose filter is in LDS
-    for (int32_t b = blockIdx.x; b < a.B; b += gridDim.x) score_plan<kBig, kVec>(a, b, lds, filter_of);
+    for (int32_t b = blockIdx.x; b < a.B; b += gridDim.x) score_plan<kTab, kVec, kTable>(a, b, lds, filter_of);
 }
 
 // ---- one iteration of the planner on the device --------------------------------------------------------
@@ -553,8 +582,9 @@ __global__ __launch_bounds__(kPlanThr) void greedy_step_kernel(const GreedyStepA
 #pragma unroll
         for (int j = 0; j < kPer; ++j) {
             const int32_t k = j * kPlanThr + tid, e = e0 + run_lo + (k < n_run ? k : n_run - 1);
-            oq[j] = a.cand_oq[e];
-            tensor[j] = a.cand_tensor[e];
+            const int4 c = a.cand[e];
+            oq[j] = make_int2(c.w, c.z);
+            tensor[j] = c.x;
             gap[j] = a.cand_gap[e];
             size[j] = a.cand_size[e];
         }
@@ -655,35 +685,39 @@ int launch_greedy_step(const tensile_tas *tas, Workspace &ws, const CandIndex &i
 
 int launch_score(const tensile_tas *tas, Workspace &ws, const CandIndex &ix, bool any_interval, const tensile_plans *plans,
                  const int64_t *resident, const int64_t *peak, const int32_t *argmax, int64_t *score, int32_t *win_out,
-                 int32_t *win_in) {
+                 int32_t *win_in, const int64_t *blk_max) {
     if (plans->B == 0 || tas->N == 0) return TENSILE_OK;
-    // as many workgroups as the device keeps resident, the plans dealt evenly among them
-    const bool big = tas->T > kTabShort * kMini;
-    static std::atomic<int> per_cu_of[2];   // (0 = not asked yet; every thread that asks stores the same answer)
-    int per_cu = per_cu_of[big ? 1 : 0].load(std::memory_order_relaxed);
-    if (per_cu == 0) {
-        int n = 0;
-        if (big) TS_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, score_kernel<true, true>, kThr, 0));
-        else TS_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, score_kernel<false, true>, kThr, 0));
-        per_cu = n > 0 ? n : 1;
-        per_cu_of[big ? 1 : 0].store(per_cu, std::memory_order_relaxed);
+    const int tab = tas->T <= kTabSmall * kMini && blk_max ? kTabSmall : tas->T <= kTabShort * kMini ? kTabShort : kTabLong;
+    ScoreArgs a = make_score_args(tas, ix, any_interval, plans, tab, resident, peak, argmax, score, win_out, win_in);
+    a.blk_max = blk_max;
+    // One workgroup per plan, so that they start as others end; on long rows as many as the device keeps resident (four per
+    // CU), the plans dealt evenly among them.  (16,384 plans of 50,000 steps: resident workgroups 2.70 ms, one per plan 2.59;
+    // 4,096 of 6,000 steps 167 and 159 us with evaluation; 1,024 of 10^6 steps 2.08 and 2.16 ms.)
+    int32_t blocks = plans->B;
+    if (tab == kTabLong) {
+        const int64_t resident_blocks = 4 * static_cast<int64_t>(tas->num_cus), rounds = (plans->B + resident_blocks - 1) / resident_blocks;
+        blocks = static_cast<int32_t>((plans->B + rounds - 1) / rounds);
     }
-    const int64_t resident_blocks = static_cast<int64_t>(tas->num_cus) * per_cu;
-    const int64_t rounds = (plans->B + resident_blocks - 1) / resident_blocks;
-    int32_t blocks = static_cast<int32_t>((plans->B + rounds - 1) / rounds);
     if (const int v = g_tuning.score_blocks; v > 0)   // tuning knob: size of the grid (plans are dealt round-robin)
         blocks = v < plans->B ? v : plans->B;
-    const ScoreArgs a = make_score_args(tas, ix, any_interval, plans, big ? kTabLong : kTabShort, resident, peak, argmax, score, win_out, win_in);
     const bool vec16 = tas->T % 2 == 0 && reinterpret_cast<uintptr_t>(resident) % 16 == 0;
-#define TS_LAUNCH_SCORE(BIG, VEC) hipLaunchKernelGGL((score_kernel<BIG, VEC>), dim3(blocks), dim3(kThr), 0, ws.stream, a)
-    if (big) {
-        if (vec16) TS_LAUNCH_SCORE(true, true);
-        else TS_LAUNCH_SCORE(true, false);
-    } else {
-        if (vec16) TS_LAUNCH_SCORE(false, true);
-        else TS_LAUNCH_SCORE(false, false);
-    }
-#undef TS_LAUNCH_SCORE
+    auto launch = [&](auto tab_tag) {
+        constexpr int kTab = decltype(tab_tag)::value;
+        const dim3 grid(blocks), block(Shape<kTab>::kThr);
+        if (vec16) {
+            if (blk_max) hipLaunchKernelGGL((score_kernel<kTab, true, true>), grid, block, 0, ws.stream, a);
+            else hipLaunchKernelGGL((score_kernel<kTab, true, false>), grid, block, 0, ws.stream, a);
+        } else {
+            if (blk_max) hipLaunchKernelGGL((score_kernel<kTab, false, true>), grid, block, 0, ws.stream, a);
+            else hipLaunchKernelGGL((score_kernel<kTab, false, false>), grid, block, 0, ws.stream, a);
+        }
+    };
+    if (tab == kTabSmall) {      // (with the maxima given only)
+        const dim3 grid(blocks), block(Shape<kTabSmall>::kThr);
+        if (vec16) hipLaunchKernelGGL((score_kernel<kTabSmall, true, true>), grid, block, 0, ws.stream, a);
+        else hipLaunchKernelGGL((score_kernel<kTabSmall, false, true>), grid, block, 0, ws.stream, a);
+    } else if (tab == kTabShort) launch(std::integral_constant<int, kTabShort>{});
+    else launch(std::integral_constant<int, kTabLong>{});
     TS_HIP(hipGetLastError());
     return TENSILE_OK;
 }

@@ -11,9 +11,9 @@ namespace tensile {
 namespace {
 
 constexpr int kMini = kScoreMini;    // steps of a piece: 4 consecutive steps per lane of a wavefront
-constexpr int kFilterWords = 1024;   // largest per-bucket filter (32768 bits)
+constexpr int kFilterWords = kScoreFilterWords;
 constexpr int kIvU = 4;              // intervals per thread and round of the cancelling pass
-constexpr int kWindow = 16384;       // entries of a bucket whose flags are in LDS at a time
+constexpr int kWindow = 8192;       // entries of a bucket whose flags are in LDS at a time
 constexpr int kStage = kScoreStage;  // tensors whose output one wavefront composes in LDS at a time
 
 typedef long long ll2 __attribute__((ext_vector_type(2)));
@@ -29,16 +29,16 @@ struct ScoreArgs {
     int64_t n_intervals;
     const int64_t *plan_offsets;
     const int32_t *iv_tensor, *iv_out, *iv_in;
-    int32_t bucket_shift, filter_words;
+    int32_t bucket_shift, filter_shift, filter_words;
     const int32_t *bucket_off;   // the candidate index, see CandIndex
-    const int2 *cand_oq;
-    const int32_t *cand_tensor, *cand_p, *cand_gap;
+    const int4 *cand;
+    const int32_t *cand_gap;
     const int64_t *cand_size;
     const int32_t *wave_ptr;
-    const int2 *hash_dir;
-    const int4 *hash_slots;
     const uint32_t *filter;
+    const int32_t *filter_base;
     const int64_t *resident;
+    const int64_t *blk_max;      // [B][n_mini] maxima of the rows' pieces, or null: they are taken from the rows
     const int64_t *peak;
     const int32_t *argmax;
     int64_t *score;
@@ -291,25 +291,23 @@ __device__ __forceinline__ void resolve_open(const ScoreArgs &a, const int64_t *
 
 // ---- the plan's own intervals cancel candidates ---------------------------------------------------------------
 // Sets the bit of every entry w_lo .. w_lo + w_n - 1 of the bucket that one of the intervals k0 .. k1-1 cancels: an
-// interval inside the gap of an entry of its tensor (any interval of that tensor when a.any_interval).  filter: the
-// bucket's bit filter over tensors, in LDS; hd: the bucket's {first slot, log2(slots)} in the hash table, whose slots
-// lead to a tensor's first entry (its others follow it); e0, n_e: the bucket's entries.
+// interval inside the gap of an entry of its tensor (any interval of that tensor when a.any_interval).  filter, base: the
+// bucket's filter bits over tensors and, per word of them, the first entry of its tensors, both in LDS.  Most intervals
+// end at the filter.  For the others the tensor's first entry lies at or after the word's first entry plus the number of
+// filter bits set below the tensor's - exactly there as long as none of the word's earlier tensors has several entries,
+// else it is searched for.  (A caller's list keeps its intervals in tensor order, and so are the entries: the lanes
+// of a wavefront read neighbouring ones.  The hash table this replaced scattered them over four times the lines.)
 template <int kThr>
-__device__ __forceinline__ void cancel_by_plan(const ScoreArgs &a, const int64_t k0, const int64_t k1, const int2 hd,
-                                               const int32_t e0, const int32_t n_e, const int32_t w_lo, const int32_t w_n,
-                                               const uint32_t *filter, uint32_t *cancelled, const int tid) {
-    const uint32_t fmask = static_cast<uint32_t>(a.filter_words) * 32 - 1;
-    const int hshift = 32 - hd.y;
-    const uint32_t hmask = (1u << hd.y) - 1;
-    const int4 *slots = a.hash_slots + hd.x;
+__device__ __forceinline__ void cancel_by_plan(const ScoreArgs &a, const int64_t k0, const int64_t k1, const int4 *entries,
+                                               const int32_t n_e, const int32_t w_lo, const int32_t w_n, const uint32_t *filter,
+                                               const int32_t *base, uint32_t *cancelled, const int tid) {
     auto cancel = [&](int32_t e) {
         const uint32_t el = static_cast<uint32_t>(e - w_lo);
         if (el < static_cast<uint32_t>(w_n)) atomicOr(&cancelled[el >> 5], 1u << (el & 31));
     };
     for (int64_t kb = k0 + tid; kb < k1; kb += kIvU * kThr) {
-        int32_t i[kIvU], o[kIvU], r[kIvU];
-        uint32_t h[kIvU];
-        int4 s[kIvU];
+        int32_t i[kIvU], o[kIvU], r[kIvU], e[kIvU];
+        int4 c[kIvU];
         bool go[kIvU];
 #pragma unroll
         for (int u = 0; u < kIvU; ++u) {
@@ -324,26 +322,31 @@ __device__ __forceinline__ void cancel_by_plan(const ScoreArgs &a, const int64_t
 #pragma unroll
         for (int u = 0; u < kIvU; ++u) {
             go[u] = static_cast<uint32_t>(i[u]) < static_cast<uint32_t>(a.N) && o[u] >= 0 && r[u] <= a.T && r[u] > o[u];
-            const uint32_t fb = static_cast<uint32_t>(i[u]) & fmask;
-            go[u] = go[u] && ((filter[fb >> 5] >> (fb & 31)) & 1u);
-            h[u] = go[u] ? (static_cast<uint32_t>(i[u]) * 2654435769u) >> hshift : 0u;
-            s[u] = slots[h[u]];
+            const uint32_t bit = go[u] ? static_cast<uint32_t>(i[u]) >> a.filter_shift : 0u;
+            const uint32_t word = filter[bit >> 5];
+            go[u] = go[u] && ((word >> (bit & 31)) & 1u);
+            e[u] = go[u] ? base[bit >> 5] + __builtin_popcount(word & ((1u << (bit & 31)) - 1)) : 0;
+            c[u] = entries[e[u]];                  // (a set bit has an entry: e is one of the word's)
         }
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int u = 0; u < kIvU; ++u) {
-            while (go[u] && s[u].x >= 0) {      // probe until the tensor or an empty slot
-                if (s[u].x == i[u]) {
-                    const int32_t first = s[u].w & INT32_MAX;
-                    if (a.any_interval || (s[u].y <= o[u] && r[u] <= s[u].z)) cancel(first);
-                    if (s[u].w >= 0) {          // more gaps of this tensor lie in the bucket
-                        for (int32_t e = first + 1; e < n_e && a.cand_tensor[e0 + e] == i[u]; ++e)
-                            if (a.any_interval || (a.cand_p[e0 + e] <= o[u] && r[u] <= a.cand_oq[e0 + e].y)) cancel(e);
-                    }
-                    break;
+            if (!go[u]) continue;
+            if (c[u].x < i[u]) {                   // the first entry of tensor i[u] or a later one, behind e
+                int32_t lo = e[u] + 1, hi = base[((static_cast<uint32_t>(i[u]) >> a.filter_shift) >> 5) + 1];
+                while (lo < hi) {
+                    const int32_t mid = (lo + hi) >> 1;
+                    if (entries[mid].x < i[u]) lo = mid + 1;
+                    else hi = mid;
                 }
-                h[u] = (h[u] + 1) & hmask;
-                s[u] = slots[h[u]];
+                e[u] = lo;
+                if (lo < n_e) c[u] = entries[lo];
+                else continue;
+            }
+            while (c[u].x == i[u]) {
+                if (a.any_interval || (c[u].y <= o[u] && r[u] <= c[u].z)) cancel(e[u]);
+                if (++e[u] >= n_e) break;
+                c[u] = entries[e[u]];
             }
         }
     }
@@ -364,11 +367,10 @@ inline ScoreArgs make_score_args(const tensile_tas *tas, const CandIndex &ix, bo
     a.n_intervals = plans->n_intervals;
     a.plan_offsets = plans->plan_offsets;
     a.iv_tensor = plans->iv_tensor; a.iv_out = plans->iv_out; a.iv_in = plans->iv_in;
-    a.bucket_shift = ix.shift; a.filter_words = ix.filter_words;
+    a.bucket_shift = ix.shift; a.filter_shift = ix.filter_shift; a.filter_words = ix.filter_words;
     a.bucket_off = ix.bucket_off.p;
-    a.cand_oq = ix.cand_oq.p; a.cand_tensor = ix.cand_tensor.p; a.cand_p = ix.cand_p.p; a.cand_gap = ix.cand_gap.p;
-    a.cand_size = ix.cand_size.p; a.wave_ptr = ix.wave_ptr.p;
-    a.hash_dir = ix.hash_dir.p; a.hash_slots = ix.hash_slots.p; a.filter = ix.filter.p;
+    a.cand = ix.cand.p; a.cand_gap = ix.cand_gap.p; a.cand_size = ix.cand_size.p; a.wave_ptr = ix.wave_ptr.p;
+    a.filter = ix.filter.p; a.filter_base = ix.filter_base.p;
     a.resident = resident; a.peak = peak; a.argmax = argmax;
     a.score = score; a.win_out = win_out; a.win_in = win_in;
     return a;

@@ -1,6 +1,8 @@
 // Peak analysis and candidate scores of a batch in one call (the body of the paper's Alg. 3 loop: the memory
 // peak analysis of Alg. 1 immediately followed by the choice among the tensors resident at the peak, section
-// IV-C): the evaluation kernel and the scoring kernel enqueued back to back.
+// IV-C): the evaluation kernel and the scoring kernel enqueued back to back.  The evaluation also writes the maximum of
+// every 256 steps of its rows, which is nearly all that scoring wants to know of them (score.hip): where the scoring call
+// by itself reads every row once, here it reads a 256th of that and the one to three blocks around each plan's peak.
 #include "common.h"
 
 namespace tensile {
@@ -13,9 +15,14 @@ int launch_step(const tensile_tas *tas, Workspace &ws, const tensile_plans *plan
     ea.iv_tensor = plans->iv_tensor; ea.iv_out = plans->iv_out; ea.iv_in = plans->iv_in;
     ea.size = tas->d_size.p; ea.size_units = tas->d_size_units.p; ea.size_shift = tas->size_shift;
     ea.MF0 = tas->d_MF0.p; ea.dMF0 = tas->d_dMF0.p; ea.resident = resident;
+    // (what the rows' pieces come to: 1/256 of the rows' bytes.  Without the memory for it, scoring reads the rows.)
+    const size_t n_mini = (static_cast<size_t>(tas->T) + kScoreMini - 1) / kScoreMini;
+    // (tuning knob step_fused: 0 = scoring reads the rows)
+    if (tas->N > 0 && g_tuning.step_fused != 0 && ws.provide(ws.blk_max, static_cast<size_t>(plans->B) * n_mini, "eval_score_plans: maxima of the rows' pieces") == TENSILE_OK)
+        ea.blk_max = ws.blk_max.p;
     const int rc = launch_eval(tas, ws, ea, peak, argmax, min_resident);
     if (rc != TENSILE_OK) return rc;
-    return launch_score(tas, ws, tas->index, false, plans, resident, peak, argmax, score, win_out, win_in);
+    return launch_score(tas, ws, tas->index, false, plans, resident, peak, argmax, score, win_out, win_in, ea.blk_max);
 }
 
 }  // namespace tensile

@@ -245,16 +245,16 @@ int build_candidate_index(const tensile_tas *h, CandIndex &ix, const std::vector
     const size_t G = gp.size();
     const int32_t T = h->T;
     auto usable = [&](size_t g) { return gwin[g] >= 0 && gwin[g] + 1 <= gq[g] - 1; };
-    uint32_t filter_bits = 1024;
-    while (filter_bits < 32768 && filter_bits < static_cast<uint32_t>(h->N)) filter_bits <<= 1;
-    ix.filter_words = static_cast<int32_t>(filter_bits / 32);
+    ix.filter_shift = 0;
+    while ((static_cast<int64_t>(h->N) + (1 << ix.filter_shift) - 1) >> ix.filter_shift > 32 * kScoreFilterWords) ++ix.filter_shift;
+    ix.filter_words = static_cast<int32_t>((((static_cast<int64_t>(h->N) - 1) >> ix.filter_shift) >> 5) + 1);
     int32_t shift = 8;
     uint64_t entries;
     for (;; ++shift) {
         entries = 0;
         for (size_t g = 0; g < G; ++g)
             if (usable(g)) entries += ((gq[g] - 1) >> shift) - ((gwin[g] + 1) >> shift) + 1;
-        const uint64_t filter_bytes = (static_cast<uint64_t>((T - 1) >> shift) + 1) * (filter_bits / 8);
+        const uint64_t filter_bytes = (static_cast<uint64_t>((T - 1) >> shift) + 1) * (8 * static_cast<uint64_t>(ix.filter_words));
         if ((entries <= 16 * static_cast<uint64_t>(G) + 4096 && filter_bytes <= (256u << 20)) || (int64_t{1} << shift) >= T) break;
     }
     if (entries > static_cast<uint64_t>(INT32_MAX) / 4) { set_error("tas_load: candidate index too large"); return TENSILE_E_RANGE; }
@@ -270,8 +270,8 @@ int build_candidate_index(const tensile_tas *h, CandIndex &ix, const std::vector
     for (int32_t b = 0; b < nb; ++b) off[b + 1] += off[b];
     const size_t E = static_cast<size_t>(off[nb]);
     // (the gaps come tensor by tensor and by ascending first step, and a bucket receives them in that order)
-    std::vector<int2> cand_oq(E);
-    std::vector<int32_t> cand_tensor(E), cand_p(E), cand_gap(E);
+    std::vector<int4> cand(E);
+    std::vector<int32_t> cand_gap(E);
     std::vector<int64_t> cand_size(E);
     {
         std::vector<int32_t> fill(off.begin(), off.end() - 1);
@@ -279,47 +279,29 @@ int build_candidate_index(const tensile_tas *h, CandIndex &ix, const std::vector
             if (usable(g))
                 for (int32_t b = (gwin[g] + 1) >> shift; b <= (gq[g] - 1) >> shift; ++b) {
                     const int32_t e = fill[b]++;
-                    cand_oq[e] = make_int2(gwin[g], gq[g]);
-                    cand_tensor[e] = gt[g];
-                    cand_p[e] = gp[g];
+                    cand[e] = make_int4(gt[g], gp[g], gq[g], gwin[g]);
                     cand_gap[e] = static_cast<int32_t>(g);
                     cand_size[e] = h->h_size[gt[g]];
                 }
     }
     std::vector<int32_t> wave_ptr(static_cast<size_t>(nb) * kScoreWaves);
-    std::vector<int2> hash_dir(static_cast<size_t>(nb));
     std::vector<uint32_t> filter(static_cast<size_t>(nb) * ix.filter_words, 0u);
-    // every bucket's hash table has its place before any is filled: the buckets are then independent of each
-    // other and are worked on by several host threads
-    size_t hash_total = 0;
-    for (int32_t b = 0; b < nb; ++b) {
-        const int32_t n = off[b + 1] - off[b];
-        int bits = 1;
-        while ((int64_t{1} << bits) < 2 * static_cast<int64_t>(n)) ++bits;
-        hash_dir[b] = make_int2(static_cast<int32_t>(hash_total), n > 0 ? bits : 0);
-        if (n > 0) hash_total += size_t{1} << bits;
-        if (hash_total > static_cast<size_t>(INT32_MAX)) { set_error("tas_load: candidate index too large"); return TENSILE_E_RANGE; }
-    }
-    std::vector<int4> hash_slots(hash_total, make_int4(-1, 0, 0, 0));
-    auto do_bucket = [&](int32_t b) {
+    std::vector<int32_t> filter_base(static_cast<size_t>(nb) * (ix.filter_words + 1));
+    auto do_bucket = [&](int32_t b) {     // (the buckets are independent of each other: several host threads)
         const int32_t e0 = off[b], n = off[b + 1] - off[b];
-        const int32_t *t = cand_tensor.data() + e0;
+        const int4 *c = cand.data() + e0;
         for (int w = 0; w < kScoreWaves; ++w)
-            wave_ptr[static_cast<size_t>(b) * kScoreWaves + w] =
-                static_cast<int32_t>(std::lower_bound(t, t + n, static_cast<int64_t>(w) * ix.tspan) - t);
-        if (n == 0) return;
-        const size_t base = static_cast<size_t>(hash_dir[b].x);
-        const int bits = hash_dir[b].y;
-        const uint32_t mask = (1u << bits) - 1;
+            wave_ptr[static_cast<size_t>(b) * kScoreWaves + w] = static_cast<int32_t>(
+                std::lower_bound(c, c + n, static_cast<int64_t>(w) * ix.tspan, [](const int4 &e, int64_t v) { return e.x < v; }) - c);
+        uint32_t *bits = filter.data() + static_cast<size_t>(b) * ix.filter_words;
+        int32_t *base = filter_base.data() + static_cast<size_t>(b) * (ix.filter_words + 1);
+        int32_t w = 0;
         for (int32_t k = 0; k < n; ++k) {
-            if (k > 0 && t[k] == t[k - 1]) continue;       // the table leads to a tensor's first entry
-            const bool last = k + 1 == n || t[k + 1] != t[k];
-            uint32_t s = (static_cast<uint32_t>(t[k]) * 2654435769u) >> (32 - bits);
-            while (hash_slots[base + s].x >= 0) s = (s + 1) & mask;
-            hash_slots[base + s] = make_int4(t[k], cand_p[e0 + k], cand_oq[e0 + k].y, k | (last ? INT32_MIN : 0));
-            const uint32_t fb = static_cast<uint32_t>(t[k]) & (filter_bits - 1);
-            filter[static_cast<size_t>(b) * ix.filter_words + (fb >> 5)] |= 1u << (fb & 31);
+            const int32_t bit = c[k].x >> ix.filter_shift;
+            for (; w <= bit >> 5; ++w) base[w] = k;
+            bits[bit >> 5] |= 1u << (bit & 31);
         }
+        for (; w <= ix.filter_words; ++w) base[w] = n;
     };
     {
         unsigned n_threads = std::thread::hardware_concurrency();
@@ -345,15 +327,12 @@ int build_candidate_index(const tensile_tas *h, CandIndex &ix, const std::vector
         if (failed) throw std::bad_alloc();
     }
     TS_HIP(ix.bucket_off.upload(off.data(), off.size()));
-    TS_HIP(ix.cand_oq.upload(cand_oq.data(), E));
-    TS_HIP(ix.cand_tensor.upload(cand_tensor.data(), E));
-    TS_HIP(ix.cand_p.upload(cand_p.data(), E));
+    TS_HIP(ix.cand.upload(cand.data(), E));
     TS_HIP(ix.cand_gap.upload(cand_gap.data(), E));
     TS_HIP(ix.cand_size.upload(cand_size.data(), E));
     TS_HIP(ix.wave_ptr.upload(wave_ptr.data(), wave_ptr.size()));
-    TS_HIP(ix.hash_dir.upload(hash_dir.data(), hash_dir.size()));
-    TS_HIP(ix.hash_slots.upload(hash_slots.data(), hash_slots.size()));
     TS_HIP(ix.filter.upload(filter.data(), filter.size()));
+    TS_HIP(ix.filter_base.upload(filter_base.data(), filter_base.size()));
     return TENSILE_OK;
 }
 
