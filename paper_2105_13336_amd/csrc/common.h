@@ -148,14 +148,10 @@ struct Tuning {
     int eval_slots = 0;        // size of the persistent grid
     int eval_nt = -1;          // footprint rows written with nontemporal stores: 0 never, 1 always, -1 by row length
     int score_blocks = 0;      // size of the scoring grid
-    int link_packed = 1;       // 0: search C itself even when its packed form exists
+    int link_packed = 1;       // 0: every transfer is searched for in C
     int step_fused = -1;       // tensile_eval_score_plans: 0 = scoring reads the rows, else the evaluation hands it their block maxima
 };
 extern Tuning g_tuning;
-
-// C for the link kernel's searches (see link.hip): blocks of kLinkCBlock consecutive values, each block's six
-// differences packed into 16 bytes, 21 bits each (built when every operator latency is below 2^21 ns).
-constexpr int kLinkCBlock = 7;
 
 // Per-job tables of tensile_eval_plans_per_job (see tas.hip), job-major.
 struct JobTables {
@@ -208,8 +204,9 @@ struct tensile_tas {
     tensile::DevBuf<uint32_t> d_size_units;   // empty when the sizes do not fit (see EvalArgs)
     int32_t size_shift = 0;
     tensile::DevBuf<int32_t> d_touch;
-    tensile::DevBuf<uint4> d_Cpack;           // [T / kLinkCBlock + 1] when c_packed
-    bool c_packed = false;
+    tensile::DevBuf<uint4> d_lat_records;     // [T] when timed: latencies of the steps up to each step (see latency_record_kernel)
+    tensile::DevBuf<uint8_t> d_lat8, d_x8;    // [T], [N] when timed: see latency_byte_kernel
+    int32_t lat_form = 0;                     // ... how many a record holds: 6 or 4
     tensile::CandIndex index;                 // swap candidates: o = earliest feasible swap-out step
     // recomputation candidates (every gap, o = p), built by the first tensile_score_recompute
     mutable std::mutex lazy_mu;               // guards the two tables that are built on first use

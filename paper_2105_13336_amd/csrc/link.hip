@@ -10,29 +10,38 @@
 // copy reuse (section III-C: the copy in host memory stays until the tensor's last access) only the
 // earliest swap-out of a tensor within a plan transfers anything.
 //
-// One persistent workgroup of 1024 threads per CU walks the plans slot, slot + grid, ...:
-//  * the start step of a transfer is a search in C: first in a table of every stride-th value kept in
-//    LDS for the whole launch (up to 7167 entries), then, when every operator latency is below 2^21 ns,
-//    one 16-byte load of the block of seven values the table entry starts (see link_kernel), else
-//    log2(stride) probes of C itself (L2 resident); a thread's twelve searches run in lockstep, one
-//    probe each per round, so that their latencies overlap;
-//  * the four endpoints of an interval (+1 at s, -1 at o+1, +1 at s', -1 at r) stay in registers, six
-//    intervals per thread; a longer plan takes several passes of 6144 intervals, each over all tiles,
+// Two persistent workgroups of 512 threads per CU walk the plans slot, slot + grid, ...:
+//  * where a transfer that ends with step e begins follows from the latencies of the steps up to e.  Most transfers of the
+//    sequences of training jobs are shorter than the step they end with, and a byte each says so: the transfer time rounded
+//    up and the step's latency rounded down to a common unit.  For the others a record per
+//    step holds the latencies of the six steps e, e - 1, ... (21 bits each; four of 32 bits when some latency takes more): one
+//    16-byte load settles a transfer of up to six steps, longer ones go on with the record six steps
+//    earlier, up to four of them, and then search C.  (Searching C from the top - a table of 7,167 of its values in LDS,
+//    then one packed block of seven - took 13 LDS probes and two more scattered loads per transfer, and its table kept
+//    a second workgroup off the CU.  Records alone left the kernel waiting for L2 lines, one per lane and
+//    load; the two byte tables are small enough for many of those to be shared or found in the L1.)
+//  * the four endpoints of an interval (+1 at s, -1 at o+1, +1 at s', -1 at r) stay in registers, twelve
+//    intervals per thread, taken up four at a time with the next four's loads in flight; a longer plan
+//    takes several passes of 6144 intervals, each over all tiles,
 //    and the passes add up in the output row (or in a scratch row per workgroup when no rows are
 //    wanted): occupancy is additive over the intervals;
-//  * per tile of 32768 steps: scatter into a difference tile in LDS that packs two steps into one 32-bit
+//  * per tile of 32,764 steps: scatter into a difference tile in LDS that packs two steps into one 32-bit
 //    word (16-bit counters: a pass holds at most 12288 endpoints, so every count and every prefix of
 //    counts fits; the adds are done on the whole word, +-1 or +-65536, and the two halves are taken apart
-//    after the scatter, which is exact because sums are linear modulo 2^32), barrier; each wavefront owns
-//    2048 consecutive steps of the tile as four blocks of 512: per block each lane takes one 16-byte
-//    granule (8 steps), clears it for the next tile, scans locally and across the wave (DPP), blocks
-//    chained through the wavefront's running total; wave totals through LDS, barrier; then per block
-//    reduce (max, earliest argmax, steps occupied twice) and the row leaves through a per-wavefront
-//    staging area as 16 contiguous bytes per lane.  Large tiles matter because every tile tests every
-//    endpoint held in registers: the scatter of a 50,000-step row costs two rounds instead of seven;
-//  * reuse: a table of the earliest swap-out step per tensor is filled before a plan's first pass and cleaned
-//    after its last: in LDS (over the tile and the staging areas, idle at that point) for plans of one pass on
-//    sequences of up to 25,088 tensors, else one row of N entries per workgroup in global memory, L2 atomics.
+//    after the scatter, which is exact because sums are linear modulo 2^32), barrier; every wavefront sums its
+//    eighth of the tile (one add per word), barrier; then it walks its part 256 steps at a time, four steps per
+//    lane: clear, take the halves apart, scan (DPP), reduce (max, earliest argmax, steps occupied twice), and store 16
+//    contiguous bytes per lane straight from the registers.  The tile is laid out so that a lane's four steps are
+//    16-byte aligned in the plan's output row, whatever T;
+//  * reuse: the earliest swap-out step per tensor is found in a table in LDS (over the tile, which is
+//    idle at that point), 16,384 tensors at a time, for plans of one pass on sequences of up to 65,536
+//    tensors, else in one row of N entries per workgroup in global memory, L2 atomics.
+// What bounds it: the scattered loads (three per interval) and the store of the rows.  Measured with rows of 50,000 steps, 16,384 plans of 4,800
+// swaps: 2.62 -> 1.54 ms (with records alone 1.87; four or six intervals at a time spill).  13 bytes per interval and 4
+// per step have to move, 0.78 ms at the rate of a plain kernel; the vector units are busy for about as long.  4,096
+// plans on 6,000 steps 314 -> 72 us, 256 plans of 60,000 intervals on 10^6 steps 21.9 -> 3.96 ms.
+#include <type_traits>
+
 #include "common.h"
 #include "wave_ops.h"
 
@@ -40,24 +49,13 @@ namespace tensile {
 
 namespace {
 
-constexpr int kThr = 1024, kWaves = kThr / 64;
-constexpr int kVpt = 8;                              // steps per lane per block (one 16-byte granule of packed counters)
-constexpr int kSub = 4;                              // blocks per wavefront and tile
-constexpr int kBlock = 64 * kVpt;                    // 512 steps
-constexpr int kWaveSteps = kSub * kBlock;            // 2048 steps per wavefront and tile
-constexpr int kTile = kWaves * kWaveSteps;           // 32768
-constexpr int kTileWords = kTile / 2;                // two 16-bit counters per word: 64 KB
-constexpr int kR = 6;                                // intervals per thread and pass
-constexpr int kPass = kR * kThr;                     // 6144 (at most 2 * kPass endpoints per step: far below 2^15)
-// Coarse table of C in LDS: the descent runs over kTabBits bits, indices are clamped to the last entry,
-// which always holds +inf (the host keeps the number of real entries below kTabMax).
-constexpr int kTabBits = 13, kTabMax = 7168;
-static_assert(kTabMax <= (1 << kTabBits) && 2 * kPass < (1 << 15), "table descent / 16-bit counters");
-// The staging area is skewed by one 16-byte granule per 16 granules (cell u lives at u + 4 * (u >> 6)): both
-// the lane-contiguous pattern (8 cells per lane) and the striped one (one granule per lane) are then
-// free of bank conflicts.  A lane's two granules never straddle a multiple of 16.  The difference tile
-// needs no skew: it is read one granule per lane, lanes side by side.
-constexpr int kStageCells = kBlock + 4 * (kBlock >> 6);   // 544 per wavefront
+constexpr int kCells = 32768;                        // steps the LDS tile has room for
+constexpr int kTile = kCells - 4;                    // ... and holds: up to three cells before its first step are unused
+constexpr int kTileWords = kCells / 2;               // two 16-bit counters per word: 64 KB
+constexpr int kPass = 6144;                          // intervals per pass (at most 2 * kPass endpoints per step: far below 2^15)
+constexpr int kRounds = 4;                           // records a transfer may take before C is searched
+constexpr int kFirstRounds = 4;                      // reuse: at most this many tables of kTileWords tensors, one after the other
+static_assert(2 * kPass < (1 << 15), "16-bit counters");
 
 typedef int i32x4 __attribute__((ext_vector_type(4)));
 
@@ -70,10 +68,10 @@ struct LinkArgs {
     const uint8_t *iv_kind;        // may be null: every interval is a swap
     const int64_t *C;              // [T+1]
     const int64_t *x;              // [N]
-    int32_t tab_stride, n_tab;     // coarse table: C[k * tab_stride], k < n_tab
-    int32_t fine_bits;             // probe rounds after the table: ceil(log2(tab_stride)), packed: ceil(log2(blocks_per_entry))
-    const uint4 *Cpack;            // packed mode: per block of kCBlock steps the differences of its C values (see tas.hip)
-    int32_t blocks_per_entry;      // packed mode: tab_stride / kCBlock
+    const uint4 *records;          // [T], see latency_record_kernel
+    const uint8_t *lat8, *x8;      // [T], [N] the latencies rounded down and the transfer times rounded up to a common unit
+    int32_t search_only;           // (testing aid) the records are not used
+    int32_t search_bits;           // probe rounds of a search in C: T < 2^search_bits
     int32_t *first_out;            // [grid][N], INT32_MAX everywhere between plans (reuse only)
     int32_t *acc_rows;             // [grid][T] scratch rows for plans of several passes when link == null
     int32_t *link;                 // [B*T] or null
@@ -89,6 +87,30 @@ __device__ __forceinline__ int32_t wave_scan_add32(int32_t x) {
     x += __builtin_amdgcn_update_dpp(0, x, 0x142, 0xa, 0xf, true);
     x += __builtin_amdgcn_update_dpp(0, x, 0x143, 0xc, 0xf, true);
     return x;
+}
+
+// How many of the record's steps, taken from the last one backwards, do not add up to x yet (all of them: kForm), and what
+// all of them come to.  x is at most 2^31 - 1 (kForm 6: the six add up to less than 2^24) or 2^32 - 1 (kForm 4: sums
+// that pass it stay there).
+template <int kForm>
+__device__ __forceinline__ int32_t steps_short_of(const uint4 w, const uint32_t x, uint32_t &sum) {
+    int32_t n;
+    if constexpr (kForm == 6) {
+        constexpr uint32_t kM = (1u << 21) - 1;
+        sum = w.x & kM; n = sum < x;
+        sum += ((w.x >> 21) | (w.y << 11)) & kM; n += sum < x;
+        sum += (w.y >> 10) & kM; n += sum < x;
+        sum += ((w.y >> 31) | (w.z << 1)) & kM; n += sum < x;
+        sum += ((w.z >> 20) | (w.w << 12)) & kM; n += sum < x;
+        sum += (w.w >> 9) & kM; n += sum < x;
+    } else {
+        auto add = [](uint32_t p, uint32_t q) { const uint32_t t = p + q; return t < p ? UINT32_MAX : t; };
+        sum = w.x; n = sum < x;
+        sum = add(sum, w.y); n += sum < x;
+        sum = add(sum, w.z); n += sum < x;
+        sum = add(sum, w.w); n += sum < x;
+    }
+    return n;
 }
 
 // Phase timing for tuning, compiled in with -DTENSILE_LINK_PROF only: thread 0 of every workgroup adds the
@@ -107,33 +129,30 @@ __device__ unsigned long long g_link_prof[8];
 #define LINK_MARK(k) do { } while (0)
 #endif
 
-// kPacked: every operator latency is below 2^21 ns and the host has packed C in blocks of kLinkCBlock = 7
-// steps, 16 bytes each: the six 21-bit differences between the block's values.  A search then ends with
-// ONE 16-byte load (the block's first value comes from the table or from the last probe) instead of three
-// dependent 8-byte probes; with the table covering every block (rows up to 50,168 steps) it is the only
-// load of the search.  The searches are bound by the number of scattered loads (the texture unit takes
-// one lane's cache line per cycle), not by their latency.
-template <bool kPacked>
-__global__ __launch_bounds__(kThr) void link_kernel(const LinkArgs a) {
-    // the difference tile and the staging areas, one array: between two plans it also serves as the table of
-    // the earliest swap-out step per tensor (host copy reuse) when the sequence has few enough tensors
-    __shared__ __attribute__((aligned(16))) uint32_t work[kTileWords + kWaves * kStageCells];
-    uint32_t *const delta = work;
-    int32_t *const stage_all = reinterpret_cast<int32_t *>(work + kTileWords);
-    int32_t *const first_lds = reinterpret_cast<int32_t *>(work);
-    constexpr int32_t kFirstLds = kTileWords + kWaves * kStageCells;   // tensors the LDS table has room for
-    __shared__ int64_t tab[kTabMax];
+// kForm: latencies per record.  kNear: rows of at most 65,534 steps, whose endpoints are kept in 16 bits each.
+// kThr: 512, two workgroups per CU, or 1024 for batches of no more plans than CUs, which would leave half of every CU idle
+// (256 plans of 60,000 intervals on 10^6 steps: 33 ms with 512 threads and passes added up step by step; 3.96 with 1024 and
+// passes added up 16 bytes at a time).
+template <int kThr, int kForm, bool kNear>
+__global__ __launch_bounds__(kThr) __attribute__((amdgpu_waves_per_eu(4, 4))) void link_kernel(const LinkArgs a) {
+    constexpr int kWaves = kThr / 64, kR = kPass / kThr;   // intervals per thread and pass
+    constexpr int kBatch = 2, kBatches = kR / kBatch;      // ... and taken up together
+    // the difference tile; between two plans also the table of the earliest swap-out step per tensor (host copy reuse)
+    __shared__ __attribute__((aligned(16))) uint32_t delta[kTileWords];
+    int32_t *const first_lds = reinterpret_cast<int32_t *>(delta);
     __shared__ int32_t wave_tot[kWaves];
     __shared__ int32_t red_mx[kWaves], red_arg[kWaves], red_over[kWaves];
 
-    for (int k = threadIdx.x; k < kTabMax; k += kThr) tab[k] = k < a.n_tab ? a.C[static_cast<int64_t>(k) * a.tab_stride] : INT64_MAX;
     for (int u = threadIdx.x; u < kTileWords; u += kThr) delta[u] = 0;
     __syncthreads();
 
     // C[k] through the uniform base and a 32-bit byte offset (the host keeps T below 2^28): no 64-bit
     // address per probe
     auto c_at = [&](uint32_t k) { return *reinterpret_cast<const int64_t *>(reinterpret_cast<const char *>(a.C) + k * 8u); };
-    int32_t *first_out = a.reuse ? a.first_out + static_cast<int64_t>(blockIdx.x) * a.N : nullptr;
+    auto record_at = [&](int32_t e) {
+        return *reinterpret_cast<const uint4 *>(reinterpret_cast<const char *>(a.records) + static_cast<uint32_t>(e) * 16u);
+    };
+    int32_t *first_out = (a.reuse && a.first_out) ? a.first_out + static_cast<int64_t>(blockIdx.x) * a.N : nullptr;
 
 #ifdef TENSILE_LINK_PROF
     unsigned long long prof_t = wall_clock64();
@@ -144,7 +163,7 @@ __global__ __launch_bounds__(kThr) void link_kernel(const LinkArgs a) {
         // cannot trace back: otherwise dozens of values computed from it are kept (and spilled) across the kernel
         int tid_now = threadIdx.x;
         asm volatile("" : "+v"(tid_now));
-        const int tid = tid_now, lane = tid & 63, wave = tid >> 6;
+        const int tid = tid_now, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
         // (the offsets through the constant address space, i.e. the scalar unit: as a vector load they would queue
         // behind the row stores of the plan before, and the interval loads depend on them)
         typedef const int64_t __attribute__((address_space(4))) *const_i64_ptr;
@@ -152,236 +171,235 @@ __global__ __launch_bounds__(kThr) void link_kernel(const LinkArgs a) {
         if (k0 < 0) k0 = 0;
         if (k1 > a.n_intervals) k1 = a.n_intervals;
         if (k1 < k0) k1 = k0;
-        auto swap_at = [&](int64_t k, int32_t &i, int32_t &o, int32_t &r) {   // an applicable swap interval?
-            i = a.iv_tensor[k];
-            o = a.iv_out[k];
-            r = a.iv_in[k];
-            const bool kind0 = a.iv_kind ? a.iv_kind[k] == 0 : true;
-            return kind0 && static_cast<uint32_t>(i) < static_cast<uint32_t>(a.N) && o >= 0 && r <= a.T && r > o;
+        auto is_swap = [&](int32_t i, int32_t o, int32_t r, uint32_t kind) {   // an applicable swap interval?
+            return kind == 0 && static_cast<uint32_t>(i) < static_cast<uint32_t>(a.N) && o >= 0 && r <= a.T && r > o;
         };
-        // Host copy reuse needs the earliest swap-out step of every tensor of the plan.  A plan of one pass on a
-        // sequence of at most kFirstLds tensors collects them in LDS (below, once its intervals are in registers);
-        // any other plan in a table in global memory, with L2 atomics - six times the time of the whole rest.
-        const bool reuse_lds = a.reuse && a.N <= kFirstLds && k1 - k0 <= kPass;   // (block-uniform)
+        const int64_t n_pass = k1 > k0 ? (k1 - k0 + kPass - 1) / kPass : 1;
+        // Host copy reuse needs the earliest swap-out step of every tensor of the plan: in LDS for a plan of one pass
+        // (`uncharged`: one bit per interval of this thread whose swap-out transfers nothing), else in global memory, with L2 atomics.
+        const bool reuse_lds = a.reuse && a.N <= kFirstRounds * kTileWords && n_pass == 1;   // (block-uniform)
+        uint32_t uncharged = 0;
         if (a.reuse && !reuse_lds) {
             for (int64_t k = k0 + tid; k < k1; k += kThr) {
-                int32_t i, o, r;
-                if (swap_at(k, i, o, r)) atomicMin(&first_out[i], o);
+                const int32_t i = a.iv_tensor[k], o = a.iv_out[k];
+                if (is_swap(i, o, a.iv_in[k], a.iv_kind ? a.iv_kind[k] : 0)) atomicMin(&first_out[i], o);
             }
             __threadfence();   // the minima are in L2 before anyone reads them
             __syncthreads();
+        } else if (a.reuse && k1 > k0) {
+            int32_t i[kR], o[kR];
+            const uint32_t len = static_cast<uint32_t>(k1 - k0);
+#pragma unroll
+            for (int j = 0; j < kR; ++j) {
+                const uint32_t k = j * kThr + tid;
+                const int64_t kc = k0 + (k < len ? k : 0);
+                i[j] = a.iv_tensor[kc];
+                o[j] = a.iv_out[kc];
+                const int32_t r = a.iv_in[kc];
+                const uint32_t kind = a.iv_kind ? a.iv_kind[kc] : 0;
+                if (k >= len || !is_swap(i[j], o[j], r, kind)) i[j] = -1;
+            }
+            for (int32_t base = 0; base < a.N; base += kTileWords) {
+                // only the entries this plan touches are set up, and put back to zero afterwards: the rest of the
+                // tile is zero already (the scan clears what it reads)
+                auto mine = [&](int j) { return static_cast<uint32_t>(i[j] - base) < static_cast<uint32_t>(kTileWords) && i[j] >= 0; };
+#pragma unroll
+                for (int j = 0; j < kR; ++j)
+                    if (mine(j)) first_lds[i[j] - base] = INT32_MAX;
+                __syncthreads();
+#pragma unroll
+                for (int j = 0; j < kR; ++j)
+                    if (mine(j)) atomicMin(&first_lds[i[j] - base], o[j]);
+                __syncthreads();
+#pragma unroll
+                for (int j = 0; j < kR; ++j)
+                    if (mine(j) && first_lds[i[j] - base] != o[j]) uncharged |= 1u << j;
+                __syncthreads();
+#pragma unroll
+                for (int j = 0; j < kR; ++j)
+                    if (mine(j)) first_lds[i[j] - base] = 0;
+                __syncthreads();
+            }
         }
-        const int64_t n_pass = k1 > k0 ? (k1 - k0 + kPass - 1) / kPass : 1;
         int32_t *row = a.link ? a.link + plan * a.T : nullptr;
         // where the passes add up: the output row, else this workgroup's scratch row
         int32_t *acc = row ? row : (n_pass > 1 ? a.acc_rows + static_cast<int64_t>(blockIdx.x) * a.T : nullptr);
-        int32_t best_mx = -1, best_arg = 0, over = 0;
+        // cells before a tile's first step, so that four cells that one lane takes are 16-byte aligned in the row
+        const int32_t pad = acc ? static_cast<int32_t>((reinterpret_cast<uintptr_t>(acc) >> 2) & 3) : 0;
+        int32_t best_mx = -1, best_arg = 0, over = 0;   // (over: wave-uniform)
 
         for (int64_t pass = 0; pass < n_pass; ++pass) {
-            const bool first = pass == 0, last = pass == n_pass - 1;
+            const bool only = n_pass == 1, first = pass == 0, last = pass == n_pass - 1;
             // ---- this pass's intervals: their endpoints (steps), UINT32_MAX = none.
-            // Every load is issued for all kR intervals before the first is used, at clamped indices, and the
-            // 2 * kR searches (start of the swap-out, start of the swap-in) advance together, one probe
-            // each per round: a search alone is a chain of dependent memory latencies.
-            uint32_t e[kR][4];
+            typedef typename std::conditional<kNear, uint16_t, uint32_t>::type Step;
+            constexpr int kWords = kNear ? 2 : 4;        // registers of an interval's endpoints: s and o + 1, s' and r
+            constexpr uint32_t kNone = static_cast<Step>(~Step(0));
+            uint32_t e[kR][kWords];
             int32_t lo_t = INT32_MAX, hi_t = -1;
             const int64_t kb = k0 + pass * kPass;
-            int32_t iv_i[kR], iv_o[kR], iv_r[kR];
-            bool ok[kR], charged[kR];
-            {
-                const uint32_t len = k1 - kb < kPass ? static_cast<uint32_t>(k1 - kb) : kPass;   // (>= 1 unless the plan is empty)
-                uint32_t kind[kR];
+            const uint32_t len = k1 - kb < kPass ? static_cast<uint32_t>(k1 - kb) : kPass;   // (0 only for an empty plan)
+            // a batch of kBatch intervals per thread: its list entries (lanes side by side: every load is whole
+            // lines) are requested a batch ahead, at clamped places
+            int32_t in_i[kBatch], in_o[kBatch], in_r[kBatch];
+            uint32_t in_kind[kBatch];
+            auto request = [&](int b) {
 #pragma unroll
-                for (int j = 0; j < kR; ++j) {
-                    const uint32_t k = j * kThr + tid;   // (lanes side by side: every load is two whole lines per wavefront)
-                    ok[j] = k < len;
-                    const int64_t kc = kb + (ok[j] ? k : 0);
-                    const bool any = len > 0;
-                    iv_i[j] = any ? a.iv_tensor[kc] : 0;
-                    iv_o[j] = any ? a.iv_out[kc] : 0;
-                    iv_r[j] = any ? a.iv_in[kc] : 0;
-                    kind[j] = (any && a.iv_kind) ? a.iv_kind[kc] : 0;
+                for (int j = 0; j < kBatch; ++j) {
+                    const uint32_t k = (b * kBatch + j) * kThr + tid;
+                    const int64_t kc = kb + (k < len ? k : 0);
+                    in_i[j] = a.iv_tensor[kc];
+                    in_o[j] = a.iv_out[kc];
+                    in_r[j] = a.iv_in[kc];
+                    in_kind[j] = a.iv_kind ? a.iv_kind[kc] : 0;
                 }
-#pragma unroll
-                for (int j = 0; j < kR; ++j) {
-                    ok[j] = ok[j] && kind[j] == 0 && static_cast<uint32_t>(iv_i[j]) < static_cast<uint32_t>(a.N) && iv_o[j] >= 0 &&
-                            iv_r[j] <= a.T && iv_r[j] > iv_o[j];
-                    if (!ok[j]) {   // harmless stand-ins for the loads below
-                        iv_i[j] = 0;
-                        iv_o[j] = 0;
-                        iv_r[j] = 1;
-                    }
-                }
-            }
-            if (reuse_lds) {
-                // only the entries this plan touches are set up, and put back to zero afterwards: the rest of the
-                // tile is zero already (the scan clears what it reads) and the staging areas may hold anything
-#pragma unroll
-                for (int j = 0; j < kR; ++j)
-                    if (ok[j]) first_lds[iv_i[j]] = INT32_MAX;
-                __syncthreads();
-#pragma unroll
-                for (int j = 0; j < kR; ++j)
-                    if (ok[j]) atomicMin(&first_lds[iv_i[j]], iv_o[j]);
-                __syncthreads();
-#pragma unroll
-                for (int j = 0; j < kR; ++j) charged[j] = ok[j] && first_lds[iv_i[j]] == iv_o[j];
-                __syncthreads();
-#pragma unroll
-                for (int j = 0; j < kR; ++j)
-                    if (ok[j]) first_lds[iv_i[j]] = 0;
-                __syncthreads();
-            }
-            LINK_MARK(1);
-            int64_t v[kR][2];     // C at the transfer's end minus its duration: the transfer starts inside the last step that begins at or before v
+            };
 #pragma unroll
             for (int j = 0; j < kR; ++j) {
-                const int64_t x = a.x[iv_i[j]];
-                if (!reuse_lds) {
-                    charged[j] = true;
-                    if (a.reuse) charged[j] = __hip_atomic_load(&first_out[iv_i[j]], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == iv_o[j];
-                }
-                v[j][0] = c_at(static_cast<uint32_t>(iv_o[j] + 1)) - x;
-                v[j][1] = c_at(static_cast<uint32_t>(iv_r[j])) - x;
-                ok[j] = ok[j] && x > 0;
+#pragma unroll
+                for (int q = 0; q < kWords; ++q) e[j][q] = UINT32_MAX;
             }
-            LINK_MARK(2);
-            // coarse: the last table entry <= v (none when v < 0: position 0, and the fine rounds then stay at step 0)
-            uint32_t pos[kR][2];
+            if (len > 0) request(0);
 #pragma unroll
-            for (int j = 0; j < kR; ++j) pos[j][0] = pos[j][1] = 0;
+            for (int b = 0; b < kBatches; ++b) {
+                if (static_cast<uint32_t>(b) * (kBatch * kThr) >= len) break;       // (block-uniform)
+                int32_t iv_i[kBatch], iv_o[kBatch], iv_r[kBatch];
+                bool ok[kBatch];
 #pragma unroll
-            for (int bit = kTabBits - 1; bit >= 0; --bit) {
+                for (int j = 0; j < kBatch; ++j) {
+                    const uint32_t k = (b * kBatch + j) * kThr + tid;
+                    ok[j] = k < len && is_swap(in_i[j], in_o[j], in_r[j], in_kind[j]);
+                    iv_i[j] = ok[j] ? in_i[j] : 0;       // (harmless stand-ins for the loads below)
+                    iv_o[j] = ok[j] ? in_o[j] : 0;
+                    iv_r[j] = ok[j] ? in_r[j] : 1;
+                }
+                // the transfer's end, then how far back it has been followed
+                int32_t at[kBatch][2];
+                uint32_t x8[kBatch], l8[kBatch][2];
 #pragma unroll
-                for (int j = 0; j < kR; ++j) {
+                for (int j = 0; j < kBatch; ++j) {
+                    at[j][0] = iv_o[j];
+                    at[j][1] = iv_r[j] - 1;
+                    x8[j] = a.x8[iv_i[j]];
+                    l8[j][0] = a.lat8[at[j][0]];
+                    l8[j][1] = a.lat8[at[j][1]];
+                }
+                bool charged[kBatch];
 #pragma unroll
-                    for (int q = 0; q < 2; ++q) {
-                        const uint32_t cand = pos[j][q] | (1u << bit);
-                        pos[j][q] = tab[cand < kTabMax - 1 ? cand : kTabMax - 1] <= v[j][q] ? cand : pos[j][q];
+                for (int j = 0; j < kBatch; ++j) {
+                    charged[j] = !((uncharged >> (b * kBatch + j)) & 1u);
+                    if (a.reuse && !reuse_lds)
+                        charged[j] = __hip_atomic_load(&first_out[iv_i[j]], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == iv_o[j];
+                }
+                if (b + 1 < kBatches && static_cast<uint32_t>(b + 1) * (kBatch * kThr) < len) request(b + 1);
+                LINK_MARK(1);
+                // a transfer no longer than the step it ends with starts there; what remains of the others (0: found)
+                int64_t rest[kBatch][2];
+                bool open = false;
+#pragma unroll
+                for (int j = 0; j < kBatch; ++j) {
+                    const bool longer[2] = {ok[j] && (x8[j] > l8[j][0] || a.search_only), ok[j] && (x8[j] > l8[j][1] || a.search_only)};
+                    const int64_t x = longer[0] || longer[1] ? a.x[iv_i[j]] : 0;
+                    rest[j][0] = longer[0] ? x : 0;
+                    rest[j][1] = longer[1] ? x : 0;
+                    open = open || longer[0] || longer[1];
+                }
+                uint4 rec[kBatch][2];
+                auto follow = [&](int j, int q) {        // one record
+                    constexpr int64_t kMost = kForm == 6 ? INT32_MAX : UINT32_MAX;
+                    if (kForm == 4 && rest[j][q] > kMost) return;     // (sums stop at kMost there: left to the search)
+                    uint32_t sum;
+                    const int32_t n = steps_short_of<kForm>(rec[j][q], static_cast<uint32_t>(rest[j][q] < kMost ? rest[j][q] : kMost), sum);
+                    at[j][q] -= n;
+                    rest[j][q] = n < kForm ? 0 : rest[j][q] - sum;
+                    if (at[j][q] < 0) {                  // the past is too short: from step 0
+                        at[j][q] = 0;
+                        rest[j][q] = 0;
                     }
-                }
-            }
-            LINK_MARK(3);
-            if constexpr (!kPacked) {
-                // fine: from the block's first step, forward by decreasing powers of two while C stays <= v.  C increases,
-                // so a probe beyond the block (or beyond the transfer's end) fails by itself; only the array's end needs a guard.
+                };
+                for (int round = 0; round < kRounds && __builtin_amdgcn_ballot_w64(open) != 0 && !a.search_only; ++round) {
 #pragma unroll
-                for (int j = 0; j < kR; ++j) {
-                    pos[j][0] *= a.tab_stride;
-                    pos[j][1] *= a.tab_stride;
-                }
-                for (int bit = a.fine_bits - 1; bit >= 0; --bit) {   // (uniform)
-                    int64_t c[kR][2];
+                    for (int j = 0; j < kBatch; ++j) {
 #pragma unroll
-                    for (int j = 0; j < kR; ++j) {
+                        for (int q = 0; q < 2; ++q)
+                            if (rest[j][q] > 0) rec[j][q] = record_at(at[j][q]);
+                    }
+                    open = false;
+#pragma unroll
+                    for (int j = 0; j < kBatch; ++j) {
 #pragma unroll
                         for (int q = 0; q < 2; ++q) {
-                            const uint32_t at = pos[j][q] + (1u << bit);
-                            c[j][q] = c_at(at <= static_cast<uint32_t>(a.T) ? at : static_cast<uint32_t>(a.T));
+                            if (rest[j][q] > 0) follow(j, q);
+                            open = open || rest[j][q] > 0;
+                        }
+                    }
+                }
+                if (__builtin_amdgcn_ballot_w64(open) != 0) {
+                    // the last step s <= at with C[s] <= C[at + 1] - rest (step 0 when there is none), by decreasing powers of two, the
+                    // wavefront's searches in lockstep
+                    int64_t v[kBatch][2];
+                    uint32_t pos[kBatch][2];
+#pragma unroll
+                    for (int j = 0; j < kBatch; ++j) {
+#pragma unroll
+                        for (int q = 0; q < 2; ++q) {
+                            v[j][q] = c_at(static_cast<uint32_t>(at[j][q]) + 1) - rest[j][q];
+                            pos[j][q] = 0;
+                        }
+                    }
+                    for (int bit = a.search_bits - 1; bit >= 0; --bit) {   // (uniform)
+                        int64_t c[kBatch][2];
+#pragma unroll
+                        for (int j = 0; j < kBatch; ++j) {
+#pragma unroll
+                            for (int q = 0; q < 2; ++q) {
+                                const uint32_t p = pos[j][q] + (1u << bit);
+                                c[j][q] = c_at(p <= static_cast<uint32_t>(a.T) ? p : static_cast<uint32_t>(a.T));
+                            }
+                        }
+#pragma unroll
+                        for (int j = 0; j < kBatch; ++j) {
+#pragma unroll
+                            for (int q = 0; q < 2; ++q) {
+                                const uint32_t p = pos[j][q] + (1u << bit);
+                                if (p <= static_cast<uint32_t>(a.T) && c[j][q] <= v[j][q]) pos[j][q] = p;
+                            }
                         }
                     }
 #pragma unroll
-                    for (int j = 0; j < kR; ++j) {
+                    for (int j = 0; j < kBatch; ++j) {
 #pragma unroll
-                        for (int q = 0; q < 2; ++q) {
-                            const uint32_t at = pos[j][q] + (1u << bit);
-                            pos[j][q] = (at <= static_cast<uint32_t>(a.T) && c[j][q] <= v[j][q]) ? at : pos[j][q];
+                        for (int q = 0; q < 2; ++q)
+                            if (rest[j][q] > 0) at[j][q] = static_cast<int32_t>(pos[j][q]);
+                    }
+                }
+#pragma unroll
+                for (int j = 0; j < kBatch; ++j) {
+                    if (ok[j]) {
+                        uint32_t (&out)[kWords] = e[b * kBatch + j];
+                        auto put = [&](int q, int32_t from, int32_t to) {
+                            if constexpr (kNear) {
+                                out[q] = static_cast<uint32_t>(from) | (static_cast<uint32_t>(to) << 16);
+                            } else {
+                                out[2 * q] = static_cast<uint32_t>(from);
+                                out[2 * q + 1] = static_cast<uint32_t>(to);
+                            }
+                        };
+                        if (charged[j]) {
+                            put(0, at[j][0], iv_o[j] + 1);
+                            lo_t = at[j][0] < lo_t ? at[j][0] : lo_t;
                         }
+                        put(1, at[j][1], iv_r[j]);
+                        lo_t = at[j][1] < lo_t ? at[j][1] : lo_t;
+                        hi_t = iv_r[j] > hi_t ? iv_r[j] : hi_t;
                     }
                 }
-            } else {
-                // from table entries to blocks; probes of the blocks' first values when the table skips blocks
-#pragma unroll
-                for (int j = 0; j < kR; ++j) {
-                    pos[j][0] *= a.blocks_per_entry;
-                    pos[j][1] *= a.blocks_per_entry;
-                }
-                const uint32_t last_block = static_cast<uint32_t>(a.T) / kLinkCBlock;
-                for (int bit = a.fine_bits - 1; bit >= 0; --bit) {   // (uniform; no round when the table has every block)
-                    int64_t c[kR][2];
-#pragma unroll
-                    for (int j = 0; j < kR; ++j) {
-#pragma unroll
-                        for (int q = 0; q < 2; ++q) {
-                            const uint32_t at = pos[j][q] + (1u << bit);
-                            c[j][q] = c_at((at <= last_block ? at : last_block) * kLinkCBlock);
-                        }
-                    }
-#pragma unroll
-                    for (int j = 0; j < kR; ++j) {
-#pragma unroll
-                        for (int q = 0; q < 2; ++q) {
-                            const uint32_t at = pos[j][q] + (1u << bit);
-                            pos[j][q] = (at <= last_block && c[j][q] <= v[j][q]) ? at : pos[j][q];
-                        }
-                    }
-                }
-                // v relative to the block's first value
-                if (a.blocks_per_entry == 1) {
-#pragma unroll
-                    for (int j = 0; j < kR; ++j) {
-                        v[j][0] -= tab[pos[j][0]];
-                        v[j][1] -= tab[pos[j][1]];
-                    }
-                } else {
-#pragma unroll
-                    for (int j = 0; j < kR; ++j) {
-                        v[j][0] -= c_at(pos[j][0] * kLinkCBlock);
-                        v[j][1] -= c_at(pos[j][1] * kLinkCBlock);
-                    }
-                }
-                // the block's record: how many of its further values are <= v
-#pragma unroll
-                for (int q = 0; q < 2; ++q) {
-                    uint4 rec[kR];
-#pragma unroll
-                    for (int j = 0; j < kR; ++j)
-                        rec[j] = *reinterpret_cast<const uint4 *>(reinterpret_cast<const char *>(a.Cpack) + pos[j][q] * 16u);
-#pragma unroll
-                    for (int j = 0; j < kR; ++j) {
-                        constexpr uint32_t kM = (1u << 21) - 1;
-                        const uint4 w = rec[j];
-                        const int64_t rest = v[j][q];
-                        const int32_t lim = rest < 0 ? -1 : rest > INT32_MAX ? INT32_MAX : static_cast<int32_t>(rest);
-                        int32_t sum = static_cast<int32_t>(w.x & kM), n = sum <= lim;
-                        sum += static_cast<int32_t>(((w.x >> 21) | (w.y << 11)) & kM); n += sum <= lim;
-                        sum += static_cast<int32_t>((w.y >> 10) & kM); n += sum <= lim;
-                        sum += static_cast<int32_t>(((w.y >> 31) | (w.z << 1)) & kM); n += sum <= lim;
-                        sum += static_cast<int32_t>(((w.z >> 20) | (w.w << 12)) & kM); n += sum <= lim;
-                        sum += static_cast<int32_t>((w.w >> 9) & kM); n += sum <= lim;
-                        const uint32_t at = pos[j][q] * kLinkCBlock + static_cast<uint32_t>(n);
-                        pos[j][q] = at <= static_cast<uint32_t>(a.T) ? at : static_cast<uint32_t>(a.T);
-                    }
-                }
-            }
-#pragma unroll
-            for (int j = 0; j < kR; ++j) {
-                e[j][0] = e[j][1] = e[j][2] = e[j][3] = UINT32_MAX;
-                if (ok[j]) {
-                    const int32_t s = static_cast<int32_t>(pos[j][0]), s2 = static_cast<int32_t>(pos[j][1]);
-                    if (charged[j]) {
-                        e[j][0] = static_cast<uint32_t>(s);
-                        e[j][1] = static_cast<uint32_t>(iv_o[j] + 1);
-                        lo_t = s < lo_t ? s : lo_t;
-                    }
-                    e[j][2] = static_cast<uint32_t>(s2);
-                    e[j][3] = static_cast<uint32_t>(iv_r[j]);
-                    lo_t = s2 < lo_t ? s2 : lo_t;
-                    hi_t = iv_r[j] > hi_t ? iv_r[j] : hi_t;
-                }
+                LINK_MARK(2);
             }
 
-            LINK_MARK(4);
             int32_t carry = 0;
             for (int32_t tile_lo = 0; tile_lo < a.T; tile_lo += kTile) {
                 const int32_t tile_hi = a.T - tile_lo < kTile ? a.T : tile_lo + kTile;
                 const uint32_t tile_n = static_cast<uint32_t>(tile_hi - tile_lo);
-                // (per-lane addresses are derived afresh in every tile, see above: otherwise one 64-bit address per
-                // block and output array is computed per plan and spilled)
-                int tid_tile = tid;
-                asm volatile("" : "+v"(tid_tile));
-                const int lane = tid_tile & 63, wave = __builtin_amdgcn_readfirstlane(tid_tile >> 6);
-                int32_t *stage = stage_all + wave * kStageCells;
                 // ---- scatter (a wavefront none of whose lanes has an endpoint in range skips it)
                 const bool mine = hi_t >= tile_lo && lo_t < tile_hi;
                 if (__builtin_amdgcn_ballot_w64(mine) != 0) {
@@ -389,114 +407,113 @@ __global__ __launch_bounds__(kThr) void link_kernel(const LinkArgs a) {
                     for (int j = 0; j < kR; ++j) {
 #pragma unroll
                         for (int q = 0; q < 4; ++q) {
-                            const uint32_t u = e[j][q] - static_cast<uint32_t>(tile_lo);
+                            const uint32_t step = kNear ? (q & 1 ? e[j][q / 2] >> 16 : e[j][q / 2] & kNone) : e[j][kNear ? 0 : q];
+                            const uint32_t u = step - static_cast<uint32_t>(tile_lo), cell = u + static_cast<uint32_t>(pad);
                             const uint32_t one = (q & 1) ? 0xffffffffu : 1u;          // -1 or +1 ...
-                            if (u < tile_n) atomicAdd(&delta[u >> 1], one << (16 * (u & 1)));   // ... on the step's half
+                            if (u < tile_n) atomicAdd(&delta[cell >> 1], one << (16 * (cell & 1)));   // ... on the cell's half
                         }
                     }
                 }
                 __syncthreads();
-                LINK_MARK(5);
-                // ---- the wavefront's four blocks: read, clear for the next tile, take the halves apart, local
-                // scan, wave scan; v = sums from the wavefront's first step on
-                int32_t v[kSub][kVpt];
-                int32_t run = 0;   // (wave-uniform)
-#pragma unroll
-                for (int g = 0; g < kSub; ++g) {
-                    typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-                    u32x4 *cell = reinterpret_cast<u32x4 *>(&delta[wave * (kWaveSteps / 2) + g * (kBlock / 2) + 4 * lane]);
-                    const u32x4 c = *cell;
-                    *cell = u32x4{0, 0, 0, 0};
-#pragma unroll
-                    for (int h = 0; h < 4; ++h) {
-                        const int32_t lo = static_cast<int16_t>(c[h] & 0xffffu);
-                        v[g][2 * h] = lo;
-                        v[g][2 * h + 1] = static_cast<int32_t>(c[h] - static_cast<uint32_t>(lo)) >> 16;
+                LINK_MARK(3);
+                // ---- the wavefront's part: 256 cells at a time, four per lane
+                const int32_t n_cells = static_cast<int32_t>(tile_n) + pad;
+                const int32_t part = (n_cells + kWaves * 256 - 1) / (kWaves * 256) * 256;
+                const int32_t u_lo = wave * part, u_hi = min(u_lo + part, n_cells);
+                typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+                {
+                    uint32_t s = 0;      // both halves of the words at once: neither sum leaves 16 bits
+                    for (int32_t u = u_lo; u < u_hi; u += 256) {
+                        const u32x2 c = *reinterpret_cast<const u32x2 *>(&delta[(u >> 1) + 2 * lane]);
+                        s += c[0] + c[1];
                     }
-#pragma unroll
-                    for (int j = 1; j < kVpt; ++j) v[g][j] += v[g][j - 1];
-                    const int32_t incl = wave_scan_add32(v[g][kVpt - 1]);
-                    const int32_t before_me = run + incl - v[g][kVpt - 1];
-#pragma unroll
-                    for (int j = 0; j < kVpt; ++j) v[g][j] += before_me;
-                    run += __builtin_amdgcn_readlane(incl, 63);
+                    const int32_t lo = static_cast<int16_t>(s & 0xffffu);
+                    const int32_t incl = wave_scan_add32(lo + (static_cast<int32_t>(s - static_cast<uint32_t>(lo)) >> 16));
+                    if (lane == 63) wave_tot[wave] = incl;
                 }
-                if (lane == 0) wave_tot[wave] = run;
                 __syncthreads();
-                int32_t before = 0, total = 0;
+                LINK_MARK(4);
+                int32_t run = carry;     // occupancy before the part's next cell (wave-uniform)
 #pragma unroll
                 for (int w = 0; w < kWaves; ++w) {
-                    const int32_t t = wave_tot[w];
-                    before += w < wave ? t : 0;
-                    total += t;
+                    const int32_t t = __builtin_amdgcn_readfirstlane(wave_tot[w]);
+                    run += w < wave ? t : 0;
+                    carry += t;
                 }
-                const int32_t base = carry + before;
-                carry += total;
+                for (int32_t u = u_lo; u < u_hi; u += 256) {
+                    u32x2 *cell = reinterpret_cast<u32x2 *>(&delta[(u >> 1) + 2 * lane]);
+                    const u32x2 c = *cell;
+                    *cell = u32x2{0, 0};
+                    int32_t v[4];
 #pragma unroll
-                for (int g = 0; g < kSub; ++g) {
-                    const int32_t block_t0 = tile_lo + wave * kWaveSteps + g * kBlock;   // (wave-uniform)
-                    if (block_t0 >= tile_hi) break;
-                    const int32_t t0 = block_t0 + kVpt * lane;
-#pragma unroll
-                    for (int j = 0; j < kVpt; ++j) v[g][j] += base;
-                    // ---- earlier passes of a long plan
-                    if (!first) {
-#pragma unroll
-                        for (int j = 0; j < kVpt; ++j)
-                            if (t0 + j < tile_hi) v[g][j] += __hip_atomic_load(&acc[t0 + j], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    for (int h = 0; h < 2; ++h) {
+                        const int32_t lo = static_cast<int16_t>(c[h] & 0xffffu);
+                        v[2 * h] = lo;
+                        v[2 * h + 1] = static_cast<int32_t>(c[h] - static_cast<uint32_t>(lo)) >> 16;
                     }
-                    if (!last) {
 #pragma unroll
-                        for (int j = 0; j < kVpt; ++j)
-                            if (t0 + j < tile_hi) __hip_atomic_store(&acc[t0 + j], v[g][j], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                        continue;   // (block-uniform; the next pass reads these sums back in the same lanes)
-                    }
-                    // ---- reduce
+                    for (int j = 1; j < 4; ++j) v[j] += v[j - 1];
+                    const int32_t incl = wave_scan_add32(v[3]);
+                    const int32_t before = run + incl - v[3];
 #pragma unroll
-                    for (int j = 0; j < kVpt; ++j) {
-                        if (t0 + j < tile_hi) {
-                            if (v[g][j] > best_mx) {
-                                best_mx = v[g][j];
-                                best_arg = t0 + j;
+                    for (int j = 0; j < 4; ++j) v[j] += before;
+                    run += __builtin_amdgcn_readlane(incl, 63);
+                    const int32_t t0 = tile_lo - pad + u + 4 * lane;      // (below tile_lo only in the tile's first cells)
+                    if (u >= pad && u + 256 <= n_cells) {                 // (uniform) all of the 256 steps exist
+                        if (!only) {         // passes of a long plan add up, each step in one lane's hands
+                            i32x4 *const sum = reinterpret_cast<i32x4 *>(acc + t0);
+                            if (!first) {
+                                const i32x4 c4 = *sum;
+#pragma unroll
+                                for (int j = 0; j < 4; ++j) v[j] += c4[j];
                             }
-                            over += v[g][j] >= 2 ? 1 : 0;
-                        }
-                    }
-                    // ---- the row: through the wavefront's staging area, 16 contiguous bytes per lane
-                    if (row) {
-                        __builtin_amdgcn_wave_barrier();
-                        i32x4 *mine_out = reinterpret_cast<i32x4 *>(stage + 8 * lane + 4 * (lane >> 3));
-                        mine_out[0] = i32x4{v[g][0], v[g][1], v[g][2], v[g][3]};
-                        mine_out[1] = i32x4{v[g][4], v[g][5], v[g][6], v[g][7]};
-                        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-                        __builtin_amdgcn_wave_barrier();
-                        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-                        const bool wide = (reinterpret_cast<uintptr_t>(row + block_t0) & 15) == 0 && block_t0 + kBlock <= tile_hi;
-#pragma unroll
-                        for (int j = 0; j < 2; ++j) {
-                            const i32x4 xv = (reinterpret_cast<const i32x4 *>(stage) + lane + (lane >> 4))[68 * j];
-                            const int32_t t = block_t0 + 4 * (j * 64 + lane);
-                            if (wide) {
-                                *reinterpret_cast<i32x4 *>(row + t) = xv;
-                            } else {
-#pragma unroll
-                                for (int q = 0; q < 4; ++q)
-                                    if (t + q < tile_hi) row[t + q] = xv[q];
+                            if (!last) {
+                                *sum = i32x4{v[0], v[1], v[2], v[3]};
+                                continue;
                             }
                         }
-                        __builtin_amdgcn_wave_barrier();
+                        const int32_t m = max(max(v[0], v[1]), max(v[2], v[3]));
+                        if (__builtin_amdgcn_ballot_w64(m > best_mx) != 0) {
+                            if (m > best_mx) {
+                                best_mx = m;
+                                best_arg = t0 + (v[0] == m ? 0 : v[1] == m ? 1 : v[2] == m ? 2 : 3);
+                            }
+                        }
+#pragma unroll
+                        for (int j = 0; j < 4; ++j) over += __builtin_popcountll(__builtin_amdgcn_ballot_w64(v[j] >= 2));
+                        if (row) *reinterpret_cast<i32x4 *>(row + t0) = i32x4{v[0], v[1], v[2], v[3]};
+                        continue;
+                    }
+                    bool in[4];
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) in[j] = t0 + j >= tile_lo && t0 + j < tile_hi;
+                    if (!only) {
+#pragma unroll
+                        for (int j = 0; j < 4; ++j) {
+                            if (!first && in[j]) v[j] += acc[t0 + j];
+                            if (!last && in[j]) acc[t0 + j] = v[j];
+                        }
+                        if (!last) continue;   // (block-uniform)
+                    }
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) {
+                        if (in[j] && v[j] > best_mx) {
+                            best_mx = v[j];
+                            best_arg = t0 + j;
+                        }
+                        over += __builtin_popcountll(__builtin_amdgcn_ballot_w64(in[j] && v[j] >= 2));
+                        if (row && in[j]) row[t0 + j] = v[j];
                     }
                 }
-                LINK_MARK(6);
+                __syncthreads();       // every part is clear again before the next scatter
+                LINK_MARK(5);
             }
         }
 
-        LINK_MARK(6);
         // ---- the plan's result
 #pragma unroll
         for (int d = 32; d >= 1; d >>= 1) {
             const int32_t omx = __shfl_xor(best_mx, d, 64), oarg = __shfl_xor(best_arg, d, 64);
-            over += __shfl_xor(over, d, 64);
             if (omx > best_mx || (omx == best_mx && oarg < best_arg)) {
                 best_mx = omx;
                 best_arg = oarg;
@@ -507,9 +524,18 @@ __global__ __launch_bounds__(kThr) void link_kernel(const LinkArgs a) {
             red_arg[wave] = best_arg;
             red_over[wave] = over;
         }
+        if (a.reuse && !reuse_lds) {   // leave the table as it was found
+            for (int64_t k = k0 + tid; k < k1; k += kThr) {
+                const int32_t i = a.iv_tensor[k], o = a.iv_out[k];
+                if (is_swap(i, o, a.iv_in[k], a.iv_kind ? a.iv_kind[k] : 0))
+                    __hip_atomic_store(&first_out[i], INT32_MAX, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            }
+            __threadfence();   // ... before the next plan's minima arrive
+        }
         __syncthreads();
         if (tid == 0) {
             int32_t mx = red_mx[0], arg = red_arg[0], ov = red_over[0];
+#pragma unroll
             for (int w = 1; w < kWaves; ++w) {
                 if (red_mx[w] > mx || (red_mx[w] == mx && red_arg[w] < arg)) {
                     mx = red_mx[w];
@@ -521,14 +547,7 @@ __global__ __launch_bounds__(kThr) void link_kernel(const LinkArgs a) {
             if (a.argmax) a.argmax[plan] = arg;
             if (a.overbooked) a.overbooked[plan] = ov;
         }
-        if (a.reuse && !reuse_lds) {   // leave the table as it was found
-            for (int64_t k = k0 + tid; k < k1; k += kThr) {
-                int32_t i, o, r;
-                if (swap_at(k, i, o, r)) __hip_atomic_store(&first_out[i], INT32_MAX, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            }
-            __threadfence();   // ... before the next plan's minima arrive
-        }
-        __syncthreads();   // red_* and the table are reused by the next plan
+        // (red_* are written again only after the barriers of the next plan's tiles)
     }
 }
 
@@ -568,23 +587,13 @@ int launch_link(const tensile_tas *tas, Workspace &ws, const tensile_plans *plan
     a.plan_offsets = plans->plan_offsets;
     a.iv_tensor = plans->iv_tensor; a.iv_out = plans->iv_out; a.iv_in = plans->iv_in; a.iv_kind = plans->iv_kind;
     a.C = tas->d_C.p; a.x = tas->d_x.p;
-    constexpr int kTabReal = kTabMax - 1;   // the last entry stays +inf
-    const bool packed = tas->c_packed && g_tuning.link_packed != 0;   // (0: testing aid, the probe search)
-    a.fine_bits = 0;
-    if (packed) {
-        const int64_t n_blocks = static_cast<int64_t>(T) / kLinkCBlock + 1;
-        a.blocks_per_entry = static_cast<int32_t>((n_blocks + kTabReal - 1) / kTabReal);
-        a.tab_stride = a.blocks_per_entry * kLinkCBlock;
-        a.Cpack = tas->d_Cpack.p;
-        while ((1 << a.fine_bits) < a.blocks_per_entry) ++a.fine_bits;
-    } else {
-        a.tab_stride = static_cast<int32_t>((static_cast<int64_t>(T) + kTabReal) / kTabReal);   // ceil((T + 1) / kTabReal)
-        while ((1 << a.fine_bits) < a.tab_stride) ++a.fine_bits;
-    }
-    a.n_tab = static_cast<int32_t>(static_cast<int64_t>(T) / a.tab_stride + 1);   // entries k with k * stride <= T: at most kTabReal
-    const int32_t grid = B < tas->num_cus ? B : tas->num_cus;
+    a.records = tas->d_lat_records.p; a.lat8 = tas->d_lat8.p; a.x8 = tas->d_x8.p;
+    a.search_only = g_tuning.link_packed == 0 ? 1 : 0;   // (testing aid)
+    while ((int64_t{1} << a.search_bits) <= T) ++a.search_bits;
+    const bool wide = B <= tas->num_cus;                 // (one workgroup per CU: a large one)
+    const int32_t slots = 2 * tas->num_cus, grid = B < slots ? B : slots;
     // (the table in global memory is only for plans the kernel cannot serve from LDS: see reuse_lds there)
-    if (reuse && (tas->N > kTileWords + kWaves * kStageCells || plans->n_intervals > kPass)) {
+    if (reuse && (tas->N > kFirstRounds * kTileWords || plans->n_intervals > kPass)) {
         const size_t need = static_cast<size_t>(grid) * static_cast<size_t>(tas->N);
         bool fresh = false;
         const int rc = ws.provide(ws.link_first, need, "eval_link: earliest swap-out table", &fresh);
@@ -603,8 +612,20 @@ int launch_link(const tensile_tas *tas, Workspace &ws, const tensile_plans *plan
         a.acc_rows = ws.link_acc.p;
     }
     a.link = link; a.peak = peak; a.argmax = argmax; a.overbooked = overbooked;
-    if (packed) hipLaunchKernelGGL(link_kernel<true>, dim3(grid), dim3(kThr), 0, stream, a);
-    else hipLaunchKernelGGL(link_kernel<false>, dim3(grid), dim3(kThr), 0, stream, a);
+    const bool near = T <= 65534;
+    auto launch = [&](auto thr, auto form) {
+        constexpr int kThr = decltype(thr)::value, kForm = decltype(form)::value;
+        if (near) hipLaunchKernelGGL((link_kernel<kThr, kForm, true>), dim3(grid), dim3(kThr), 0, stream, a);
+        else hipLaunchKernelGGL((link_kernel<kThr, kForm, false>), dim3(grid), dim3(kThr), 0, stream, a);
+    };
+    const std::integral_constant<int, 6> six{};
+    const std::integral_constant<int, 4> four{};
+    const std::integral_constant<int, 512> half{};
+    const std::integral_constant<int, 1024> whole{};
+    if (wide && tas->lat_form == 6) launch(whole, six);
+    else if (wide) launch(whole, four);
+    else if (tas->lat_form == 6) launch(half, six);
+    else launch(half, four);
     TS_HIP(hipGetLastError());
     return TENSILE_OK;
 }

@@ -104,6 +104,38 @@ __global__ void gap_window_kernel(int32_t G, int32_t T, const int32_t *gp, const
     gwin[g] = o;
 }
 
+// For the link kernel: one record per step e with the latencies of the steps e, e - 1, ...: six of 21 bits when every
+// latency is shorter than 2^21 ns, else four of 32 bits, where a longer one counts as 2^32 - 1.  0 before step 0.
+__global__ void latency_record_kernel(int32_t T, const int64_t *step_ns, int32_t form, uint4 *records) {
+    const int32_t e = blockIdx.x * blockDim.x + threadIdx.x;
+    if (e >= T) return;
+    auto at = [&](int32_t back) -> uint64_t { return e - back >= 0 ? static_cast<uint64_t>(step_ns[e - back]) : 0; };
+    if (form == 6) {
+        unsigned __int128 bits = 0;
+#pragma unroll
+        for (int j = 0; j < 6; ++j) bits |= static_cast<unsigned __int128>(at(j)) << (21 * j);
+        records[e] = make_uint4(static_cast<uint32_t>(bits), static_cast<uint32_t>(bits >> 32), static_cast<uint32_t>(bits >> 64),
+                                static_cast<uint32_t>(bits >> 96));
+    } else {
+        auto cut = [](uint64_t v) { return v < UINT32_MAX ? static_cast<uint32_t>(v) : UINT32_MAX; };
+        records[e] = make_uint4(cut(at(0)), cut(at(1)), cut(at(2)), cut(at(3)));
+    }
+}
+
+// For the link kernel: x8 <= lat8 only if the transfer is no longer than the step.  lat8 = the latency in units of 2^shift ns,
+// rounded down, at most 254; x8 = the transfer time rounded up, at most 255.
+__global__ void latency_byte_kernel(int32_t T, const int64_t *step_ns, int32_t N, const int64_t *x, int32_t shift, uint8_t *lat8, uint8_t *x8) {
+    const int32_t k = blockIdx.x * blockDim.x + threadIdx.x;
+    if (k < T) {
+        const int64_t v = step_ns[k] >> shift;
+        lat8[k] = static_cast<uint8_t>(v < 254 ? v : 254);
+    }
+    if (k < N) {
+        const int64_t v = x[k] > 0 ? ((x[k] - 1) >> shift) + 1 : 0;
+        x8[k] = static_cast<uint8_t>(v < 255 ? v : 255);
+    }
+}
+
 // d[t] = MF0[t] - MF0[t-1], d[0] = MF0[0]
 __global__ void difference_kernel(int32_t T, const int64_t *MF0, int64_t *d) {
     const int32_t t = blockIdx.x * blockDim.x + threadIdx.x;
@@ -433,6 +465,19 @@ int build_times_and_index(tensile_tas *h, const int64_t *step_ns) {
         if (N > 0)
             hipLaunchKernelGGL(transfer_time_kernel, dim3((N + 255) / 256), dim3(256), 0, 0, N, h->d_size.p,
                                h->link_bytes_per_us, h->d_x.p);
+        h->lat_form = 0;
+        if (h->timed) {
+            const int64_t longest = *std::max_element(step_ns, step_ns + T);
+            int32_t shift = 0;
+            while ((longest >> shift) > 254) ++shift;
+            h->lat_form = longest < (int64_t{1} << 21) ? 6 : 4;
+            TS_HIP(h->d_lat_records.reserve(T));
+            TS_HIP(h->d_lat8.reserve(T));
+            TS_HIP(h->d_x8.reserve(N));
+            hipLaunchKernelGGL(latency_record_kernel, dim3((T + 255) / 256), dim3(256), 0, 0, T, step.p, h->lat_form, h->d_lat_records.p);
+            hipLaunchKernelGGL(latency_byte_kernel, dim3((std::max(T, N) + 255) / 256), dim3(256), 0, 0, T, step.p, N, h->d_x.p, shift,
+                               h->d_lat8.p, h->d_x8.p);
+        }
         DevBuf<int32_t> d_gp, d_gq, d_gt, d_gwin;
         TS_HIP(d_gp.upload(gp.data(), gp.size()));
         TS_HIP(d_gq.upload(gq.data(), gq.size()));
@@ -452,29 +497,6 @@ int build_times_and_index(tensile_tas *h, const int64_t *step_ns) {
     h->h_x.resize(static_cast<size_t>(N));
     TS_HIP(hipMemcpy(h->h_C.data(), h->d_C.p, (static_cast<size_t>(T) + 1) * sizeof(int64_t), hipMemcpyDeviceToHost));
     if (N > 0) TS_HIP(hipMemcpy(h->h_x.data(), h->d_x.p, static_cast<size_t>(N) * sizeof(int64_t), hipMemcpyDeviceToHost));
-    // C packed for the link kernel: block b holds, 21 bits each, C[7b+1]-C[7b] .. C[7b+6]-C[7b+5] (0 past C[T])
-    h->c_packed = false;
-    if (h->timed) {
-        constexpr int kBits = 21;
-        const std::vector<int64_t> &C = h->h_C;
-        bool fits = true;
-        for (int32_t t = 0; t < T && fits; ++t) fits = C[t + 1] - C[t] < (int64_t{1} << kBits);
-        if (fits) {
-            std::vector<uint4> rec(static_cast<size_t>(T) / kLinkCBlock + 1);
-            for (size_t b = 0; b < rec.size(); ++b) {
-                unsigned __int128 bits = 0;
-                for (int j = 0; j + 1 < kLinkCBlock; ++j) {
-                    const int64_t k = static_cast<int64_t>(b) * kLinkCBlock + j;
-                    const uint64_t d = k + 1 <= T ? static_cast<uint64_t>(C[k + 1] - C[k]) : 0;
-                    bits |= static_cast<unsigned __int128>(d) << (kBits * j);
-                }
-                rec[b] = make_uint4(static_cast<uint32_t>(bits), static_cast<uint32_t>(bits >> 32), static_cast<uint32_t>(bits >> 64),
-                                    static_cast<uint32_t>(bits >> 96));
-            }
-            TS_HIP(h->d_Cpack.upload(rec.data(), rec.size()));
-            h->c_packed = true;
-        }
-    }
     return TENSILE_OK;
 }
 

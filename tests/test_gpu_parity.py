@@ -509,6 +509,28 @@ def test_link_occupancy_with_latencies_too_long_to_pack():
     h.close()
 
 
+@pytest.mark.parametrize("T,B,N,reuse", [(32764, 3, 300, False), (32765, 300, 200, True), (65534, 3, 400, False), (65535, 3, 400, True),
+                                         (65529, 2, 300, False), (500, 2, 16385, True), (500, 300, 16384, True), (700, 2, 40000, True)])
+@pytest.mark.parametrize("longest", [2_000, (1 << 21) - 1, 1 << 21, 1 << 33])
+def test_link_occupancy_transfers_of_every_length(T, B, N, reuse, longest):
+    """Tile edges, endpoints in 16 and in 32 bits, tables of the earliest swap-out in one and in several rounds, small and
+    large batches; step latencies (few of the longest) that fit six or four to a record or pass 32 bits, with
+    transfers from less than a step to hundreds of them and of more than 2^32 ns."""
+    tas = small_random_tas(8800 + T % 97, N=min(N, 3000), T=T, max_acc=4, timed=True)
+    reps = -(-N // tas.N)
+    sizes = np.tile(tas.size_bytes, reps)[:N].astype(np.int64)
+    sizes[::7] = 1 + sizes[::7] % 50
+    tas = tas_from_lists(T, sizes.tolist(), np.tile(tas.alloc_step, reps)[:N].tolist(),
+                         [[int(x) for x in tas.touch_points(i % tas.N)[1:]] for i in range(N)], None,
+                         np.where(prng.randint(5, 1, np.arange(T), 0, 9) == 0, longest, 1 + prng.randint(5, 2, np.arange(T), 0, 3_000)).astype(np.int64),
+                         0, 4_000 if longest < 1 << 33 else 40)
+    pl = merged_plans(tas, B, 3) if reuse else make_plans(tas, B, 3, p_swap=0.5)
+    if B > 100:
+        pl = pl.select(np.arange(B) % 7)
+    say(f"link transfers T={T} B={B} N={N} reuse={reuse} longest={longest}")
+    check_link(tas, pl, reuse, label=f"T={T} N={N} longest={longest}")
+
+
 def test_link_occupancy_long_plans_take_several_passes():
     """Plans of more than 6144 intervals (the registers of one pass), with and without rows."""
     tas = small_random_tas(4100, N=400, T=9000, max_acc=6, timed=True)
