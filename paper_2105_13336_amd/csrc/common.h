@@ -212,7 +212,8 @@ struct tensile_tas {
     mutable std::mutex lazy_mu;               // guards the two tables that are built on first use
     mutable tensile::CandIndex recompute_index;
     mutable bool recompute_index_built = false;
-    std::vector<int32_t> h_gp, h_gq, h_gt;    // gaps of length >= 2 in tensor order (host)
+    std::vector<int32_t> h_gp;                // first steps of the gaps of length >= 2, in tensor order (host)
+    tensile::DevBuf<int32_t> d_gp, d_gq, d_gt;         // [G] the gaps' first and last steps and their tensors
     std::vector<int32_t> h_gap_first;         // [N+1] first gap of every tensor in those lists
     mutable tensile::JobTables job_tables;    // built by the first tensile_eval_plans_per_job
     // host copies used by the greedy driver and the validator

@@ -6,8 +6,6 @@
 #include "wave_ops.h"
 
 #include <algorithm>
-#include <atomic>
-#include <thread>
 #include <cstdarg>
 #include <cstdio>
 #include <new>
@@ -157,6 +155,156 @@ __global__ void lifetime_intervals_kernel(int32_t N, const int64_t *size, const 
     iv_in[i] = free_step[i] + 1;
 }
 
+// ---- the candidate index, built on the device (CandIndex in common.h says what it holds).  A gap is usable when some
+// step lies between its earliest swap-out step and its end.
+__device__ __forceinline__ bool gap_usable(int32_t win, int32_t q) { return win >= 0 && win + 1 <= q - 1; }
+
+constexpr int kIndexThr = 1024, kIndexWaves = kIndexThr / 64;
+constexpr int kIndexShifts = 24;   // bucket widths of 2^8 .. 2^31 steps
+// Up to this many buckets each looks through all gaps; past it the gaps are first filed by 64 buckets and each bucket looks
+// through its 64's only: linear in the buckets times the gaps either way, but the lists keep the factor small (130,000
+// steps, 513 buckets: 0.80 ms flat, 0.70 with lists; 10^6 steps, 3,907 buckets: 15.5 and 4.5; at 512 no difference).
+constexpr int32_t kIndexFlat = 512;
+
+// n_entries[k] += entries an index with buckets of 2^(8 + k) steps would have.
+__global__ __launch_bounds__(kIndexThr) void index_size_kernel(int32_t G, const int32_t *gwin, const int32_t *gq,
+                                                               unsigned long long *n_entries) {
+    __shared__ unsigned long long sum[kIndexShifts];
+    if (threadIdx.x < kIndexShifts) sum[threadIdx.x] = 0;
+    __syncthreads();
+    int64_t mine[kIndexShifts] = {};
+    for (int64_t g = static_cast<int64_t>(blockIdx.x) * kIndexThr + threadIdx.x; g < G; g += static_cast<int64_t>(gridDim.x) * kIndexThr) {
+        const int32_t win = gwin[g], q = gq[g];
+        if (!gap_usable(win, q)) continue;
+#pragma unroll
+        for (int k = 0; k < kIndexShifts; ++k) mine[k] += ((q - 1) >> (8 + k)) - ((win + 1) >> (8 + k)) + 1;
+    }
+#pragma unroll
+    for (int k = 0; k < kIndexShifts; ++k) {
+        const int64_t all = wave_scan_add(mine[k]);
+        if ((threadIdx.x & 63) == 63 && all != 0) atomicAdd(&sum[k], static_cast<unsigned long long>(all));
+    }
+    __syncthreads();
+    if (threadIdx.x < kIndexShifts) atomicAdd(&n_entries[threadIdx.x], sum[threadIdx.x]);
+}
+
+struct IndexArgs {
+    int32_t G, shift;
+    const int32_t *gwin, *gp, *gq, *gt;
+    const int64_t *size;
+    int32_t *place;              // [n_buckets * kIndexWaves] entries of each slab of gaps, then where they begin
+    const int32_t *list, *list_off;   // the gaps of each 2^list_shift buckets (null: all gaps)
+    int32_t list_shift;
+    int4 *cand;                  // (null: cand_gap only)
+    int32_t *cand_gap;
+    int64_t *cand_size;
+};
+
+// One workgroup per bucket, one slab of consecutive gaps per wavefront: the gaps that overlap the bucket are counted
+// (kFill false) or written from the slab's place on (kFill true), in the order of their numbers.  Four loads of each
+// table in flight: a pass is a chain of load latencies.  The host, which followed each gap through its own buckets, took
+// far fewer steps but a cache miss for most, and uploaded the result (the whole of tas_update_latencies: 24,000 steps
+// 951 us there, 203 here; 50,000 steps 2,090 and 285; 10^6 steps 41.5 and 4.5 ms).
+template <bool kFill>
+__global__ __launch_bounds__(kIndexThr) void index_bucket_kernel(const IndexArgs a) {
+    constexpr int kUnroll = 4;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x) >> 6);
+    const int32_t b = blockIdx.x;
+    const int64_t first = a.list ? a.list_off[b >> a.list_shift] : 0;
+    const int64_t end = a.list ? a.list_off[(b >> a.list_shift) + 1] : a.G;
+    const int64_t span = ((end - first + kIndexWaves - 1) / kIndexWaves + 63) / 64 * 64;
+    const int64_t k_end = min(end, first + (wave + 1) * span);
+    int32_t *const place = a.place + static_cast<int64_t>(b) * kIndexWaves + wave;
+    int32_t n = kFill ? *place : 0;
+    for (int64_t k0 = first + wave * span; k0 < k_end; k0 += 64 * kUnroll) {
+        int32_t g[kUnroll], win[kUnroll], q[kUnroll];
+#pragma unroll
+        for (int u = 0; u < kUnroll; ++u) {
+            const int64_t k = k0 + 64 * u + lane;
+            g[u] = k >= k_end ? -1 : a.list ? a.list[k] : static_cast<int32_t>(k);
+        }
+#pragma unroll
+        for (int u = 0; u < kUnroll; ++u) {
+            win[u] = g[u] >= 0 ? a.gwin[g[u]] : -1;
+            q[u] = g[u] >= 0 ? a.gq[g[u]] : 0;
+        }
+#pragma unroll
+        for (int u = 0; u < kUnroll; ++u) {
+            const bool hit = gap_usable(win[u], q[u]) && (win[u] + 1) >> a.shift <= b && b <= (q[u] - 1) >> a.shift;
+            const uint64_t mask = __builtin_amdgcn_ballot_w64(hit);
+            if (kFill && hit) {
+                const int32_t e = n + __builtin_popcountll(mask & ((1ull << lane) - 1));
+                a.cand_gap[e] = g[u];
+                if (a.cand) {
+                    const int32_t t = a.gt[g[u]];
+                    a.cand[e] = make_int4(t, a.gp[g[u]], q[u], win[u]);
+                    a.cand_size[e] = a.size[t];
+                }
+            }
+            n += __builtin_popcountll(mask);
+        }
+    }
+    if (!kFill && lane == 0) *place = n;
+}
+
+// The slabs' counts become places, and bucket_off[b] the first place of bucket b; one workgroup.
+__global__ __launch_bounds__(kIndexThr) void index_place_kernel(int32_t nb, int32_t *place, int32_t *bucket_off) {
+    __shared__ int64_t wave_tot[2][kIndexWaves];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int64_t n = static_cast<int64_t>(nb) * kIndexWaves;
+    int64_t carry = 0;
+    int buf = 0;
+    for (int64_t k0 = 0; k0 < n; k0 += kIndexThr) {
+        const int64_t k = k0 + threadIdx.x;
+        const int64_t c = k < n ? place[k] : 0;
+        const int64_t incl = wave_scan_add(c);
+        if (lane == 63) wave_tot[buf][wave] = incl;
+        __syncthreads();
+        int64_t before = carry + incl - c;
+        for (int w = 0; w < kIndexWaves; ++w) {
+            const int64_t tw = wave_tot[buf][w];
+            if (w < wave) before += tw;
+            carry += tw;
+        }
+        if (k < n) {
+            place[k] = static_cast<int32_t>(before);
+            if (k % kIndexWaves == 0) bucket_off[k / kIndexWaves] = static_cast<int32_t>(before);
+        }
+        buf ^= 1;
+    }
+    if (threadIdx.x == 0) bucket_off[nb] = static_cast<int32_t>(carry);
+}
+
+// Per bucket, from its entries: wave_ptr, filter and filter_base.
+__global__ __launch_bounds__(256) void index_filter_kernel(int32_t filter_shift, int32_t filter_words, int32_t tspan,
+                                                           const int32_t *bucket_off, const int4 *cand, int32_t *wave_ptr,
+                                                           uint32_t *filter, int32_t *filter_base) {
+    __shared__ uint32_t bits[kScoreFilterWords];
+    const int32_t b = blockIdx.x, e0 = bucket_off[b], n = bucket_off[b + 1] - e0;
+    const int4 *c = cand + e0;
+    for (int32_t w = threadIdx.x; w < filter_words; w += 256) bits[w] = 0;
+    __syncthreads();
+    for (int32_t k = threadIdx.x; k < n; k += 256) {
+        const int32_t bit = c[k].x >> filter_shift;
+        atomicOr(&bits[bit >> 5], 1u << (bit & 31));
+    }
+    __syncthreads();
+    for (int32_t w = threadIdx.x; w < filter_words; w += 256) filter[static_cast<int64_t>(b) * filter_words + w] = bits[w];
+    auto first_of = [&](int64_t tensor) {    // first entry of that tensor or a later one
+        int32_t lo = 0, hi = n;
+        while (lo < hi) {
+            const int32_t mid = lo + ((hi - lo) >> 1);
+            if (c[mid].x < tensor) lo = mid + 1;
+            else hi = mid;
+        }
+        return lo;
+    };
+    for (int32_t w = threadIdx.x; w <= filter_words; w += 256)
+        filter_base[static_cast<int64_t>(b) * (filter_words + 1) + w] = first_of(static_cast<int64_t>(w) << (5 + filter_shift));
+    if (threadIdx.x < kScoreWaves)
+        wave_ptr[static_cast<int64_t>(b) * kScoreWaves + threadIdx.x] = first_of(static_cast<int64_t>(threadIdx.x) * tspan);
+}
+
 int check_latencies(const char *who, int32_t T, int32_t N, const int64_t *size_bytes, const int64_t *step_ns,
                     int64_t link_bytes_per_us) {
     if (!step_ns) return TENSILE_OK;
@@ -271,100 +419,68 @@ int build_timeline(const tensile_tas *h, const int64_t *d_size, int64_t base_val
 // t* with o < t* < q.  File it under every bucket of 2^shift steps that o+1 .. q-1 overlaps;
 // the bucket width starts at 256 steps and doubles while the index would hold more than
 // about 16 entries per gap (or its filters more than 256 MiB).  CandIndex (common.h) lists
-// what is kept per bucket.
-int build_candidate_index(const tensile_tas *h, CandIndex &ix, const std::vector<int32_t> &gp,
-                          const std::vector<int32_t> &gq, const std::vector<int32_t> &gt, const std::vector<int32_t> &gwin) {
-    const size_t G = gp.size();
-    const int32_t T = h->T;
-    auto usable = [&](size_t g) { return gwin[g] >= 0 && gwin[g] + 1 <= gq[g] - 1; };
+// what is kept per bucket.  d_gwin: [G] the gaps' earliest swap-out steps.
+int build_candidate_index(const tensile_tas *h, CandIndex &ix, const int32_t *d_gwin) {
+    const int32_t T = h->T, G = h->G;
     ix.filter_shift = 0;
     while ((static_cast<int64_t>(h->N) + (1 << ix.filter_shift) - 1) >> ix.filter_shift > 32 * kScoreFilterWords) ++ix.filter_shift;
     ix.filter_words = static_cast<int32_t>((((static_cast<int64_t>(h->N) - 1) >> ix.filter_shift) >> 5) + 1);
-    int32_t shift = 8;
-    uint64_t entries;
-    for (;; ++shift) {
-        entries = 0;
-        for (size_t g = 0; g < G; ++g)
-            if (usable(g)) entries += ((gq[g] - 1) >> shift) - ((gwin[g] + 1) >> shift) + 1;
-        const uint64_t filter_bytes = (static_cast<uint64_t>((T - 1) >> shift) + 1) * (8 * static_cast<uint64_t>(ix.filter_words));
-        if ((entries <= 16 * static_cast<uint64_t>(G) + 4096 && filter_bytes <= (256u << 20)) || (int64_t{1} << shift) >= T) break;
+    unsigned long long n_entries[kIndexShifts] = {};
+    if (G > 0) {
+        DevBuf<unsigned long long> d_n;
+        TS_HIP(d_n.upload(n_entries, kIndexShifts));
+        const int grid = static_cast<int>(std::min<int64_t>((static_cast<int64_t>(G) + kIndexThr - 1) / kIndexThr, 128));
+        hipLaunchKernelGGL(index_size_kernel, dim3(grid), dim3(kIndexThr), 0, 0, G, d_gwin, h->d_gq.p, d_n.p);
+        TS_HIP(hipGetLastError());
+        TS_HIP(hipMemcpy(n_entries, d_n.p, sizeof n_entries, hipMemcpyDeviceToHost));
     }
+    int32_t shift = 8;
+    for (;; ++shift) {
+        const uint64_t filter_bytes = (static_cast<uint64_t>((T - 1) >> shift) + 1) * (8 * static_cast<uint64_t>(ix.filter_words));
+        if ((n_entries[shift - 8] <= 16 * static_cast<uint64_t>(G) + 4096 && filter_bytes <= (256u << 20)) || (int64_t{1} << shift) >= T) break;
+    }
+    const uint64_t entries = n_entries[shift - 8];
     if (entries > static_cast<uint64_t>(INT32_MAX) / 4) { set_error("tas_load: candidate index too large"); return TENSILE_E_RANGE; }
     const int32_t nb = ((T - 1) >> shift) + 1;
+    const size_t E = static_cast<size_t>(entries);
     ix.shift = shift;
     ix.n_buckets = nb;
     ix.tspan = ((h->N + kScoreWaves - 1) / kScoreWaves + kScoreStage - 1) / kScoreStage * kScoreStage;
 
-    std::vector<int32_t> off(static_cast<size_t>(nb) + 1, 0);
-    for (size_t g = 0; g < G; ++g)
-        if (usable(g))
-            for (int32_t b = (gwin[g] + 1) >> shift; b <= (gq[g] - 1) >> shift; ++b) ++off[b + 1];
-    for (int32_t b = 0; b < nb; ++b) off[b + 1] += off[b];
-    const size_t E = static_cast<size_t>(off[nb]);
-    // (the gaps come tensor by tensor and by ascending first step, and a bucket receives them in that order)
-    std::vector<int4> cand(E);
-    std::vector<int32_t> cand_gap(E);
-    std::vector<int64_t> cand_size(E);
-    {
-        std::vector<int32_t> fill(off.begin(), off.end() - 1);
-        for (size_t g = 0; g < G; ++g)
-            if (usable(g))
-                for (int32_t b = (gwin[g] + 1) >> shift; b <= (gq[g] - 1) >> shift; ++b) {
-                    const int32_t e = fill[b]++;
-                    cand[e] = make_int4(gt[g], gp[g], gq[g], gwin[g]);
-                    cand_gap[e] = static_cast<int32_t>(g);
-                    cand_size[e] = h->h_size[gt[g]];
-                }
-    }
-    std::vector<int32_t> wave_ptr(static_cast<size_t>(nb) * kScoreWaves);
-    std::vector<uint32_t> filter(static_cast<size_t>(nb) * ix.filter_words, 0u);
-    std::vector<int32_t> filter_base(static_cast<size_t>(nb) * (ix.filter_words + 1));
-    auto do_bucket = [&](int32_t b) {     // (the buckets are independent of each other: several host threads)
-        const int32_t e0 = off[b], n = off[b + 1] - off[b];
-        const int4 *c = cand.data() + e0;
-        for (int w = 0; w < kScoreWaves; ++w)
-            wave_ptr[static_cast<size_t>(b) * kScoreWaves + w] = static_cast<int32_t>(
-                std::lower_bound(c, c + n, static_cast<int64_t>(w) * ix.tspan, [](const int4 &e, int64_t v) { return e.x < v; }) - c);
-        uint32_t *bits = filter.data() + static_cast<size_t>(b) * ix.filter_words;
-        int32_t *base = filter_base.data() + static_cast<size_t>(b) * (ix.filter_words + 1);
-        int32_t w = 0;
-        for (int32_t k = 0; k < n; ++k) {
-            const int32_t bit = c[k].x >> ix.filter_shift;
-            for (; w <= bit >> 5; ++w) base[w] = k;
-            bits[bit >> 5] |= 1u << (bit & 31);
-        }
-        for (; w <= ix.filter_words; ++w) base[w] = n;
+    TS_HIP(ix.bucket_off.reserve(static_cast<size_t>(nb) + 1));
+    TS_HIP(ix.cand.reserve(E));
+    TS_HIP(ix.cand_gap.reserve(E));
+    TS_HIP(ix.cand_size.reserve(E));
+    TS_HIP(ix.wave_ptr.reserve(static_cast<size_t>(nb) * kScoreWaves));
+    TS_HIP(ix.filter.reserve(static_cast<size_t>(nb) * ix.filter_words));
+    TS_HIP(ix.filter_base.reserve(static_cast<size_t>(nb) * (ix.filter_words + 1)));
+    DevBuf<int32_t> place, list, list_off;
+    TS_HIP(place.reserve(static_cast<size_t>(nb) * kIndexWaves));
+    IndexArgs a{G, shift, d_gwin, h->d_gp.p, h->d_gq.p, h->d_gt.p, h->d_size.p, place.p, nullptr, nullptr, 0,
+                ix.cand.p, ix.cand_gap.p, ix.cand_size.p};
+    auto file = [](const IndexArgs &args, int32_t n_buckets, int32_t *bucket_off) {
+        hipLaunchKernelGGL(index_bucket_kernel<false>, dim3(n_buckets), dim3(kIndexThr), 0, 0, args);
+        hipLaunchKernelGGL(index_place_kernel, dim3(1), dim3(kIndexThr), 0, 0, n_buckets, args.place, bucket_off);
+        hipLaunchKernelGGL(index_bucket_kernel<true>, dim3(n_buckets), dim3(kIndexThr), 0, 0, args);
     };
-    {
-        unsigned n_threads = std::thread::hardware_concurrency();
-        n_threads = n_threads < 1 ? 1 : n_threads > 16 ? 16 : n_threads;
-        if (E < 50000 || nb < 4) n_threads = 1;
-        if (n_threads > static_cast<unsigned>(nb)) n_threads = static_cast<unsigned>(nb);
-        std::atomic<int32_t> next_bucket{0};
-        std::atomic<bool> failed{false};
-        auto worker = [&]() {
-            try {
-                for (int32_t b; (b = next_bucket.fetch_add(1)) < nb;) do_bucket(b);
-            } catch (...) {
-                failed = true;
-            }
-        };
-        std::vector<std::thread> pool;
-        try {
-            for (unsigned k = 1; k < n_threads; ++k) pool.emplace_back(worker);
-        } catch (...) {   // (no more threads to be had: the ones there and this one do the work)
-        }
-        worker();
-        for (std::thread &t : pool) t.join();
-        if (failed) throw std::bad_alloc();
+    if (nb > kIndexFlat) {     // first by 64 buckets each, then each bucket looks through its 64's gaps only
+        const int32_t wide = shift + 6, n_wide = ((T - 1) >> wide) + 1;
+        TS_HIP(list.reserve(static_cast<size_t>(n_entries[wide - 8])));
+        TS_HIP(list_off.reserve(static_cast<size_t>(n_wide) + 1));
+        IndexArgs w = a;
+        w.shift = wide;
+        w.cand = nullptr;
+        w.cand_gap = list.p;
+        file(w, n_wide, list_off.p);
+        a.list = list.p;
+        a.list_off = list_off.p;
+        a.list_shift = 6;
     }
-    TS_HIP(ix.bucket_off.upload(off.data(), off.size()));
-    TS_HIP(ix.cand.upload(cand.data(), E));
-    TS_HIP(ix.cand_gap.upload(cand_gap.data(), E));
-    TS_HIP(ix.cand_size.upload(cand_size.data(), E));
-    TS_HIP(ix.wave_ptr.upload(wave_ptr.data(), wave_ptr.size()));
-    TS_HIP(ix.filter.upload(filter.data(), filter.size()));
-    TS_HIP(ix.filter_base.upload(filter_base.data(), filter_base.size()));
+    file(a, nb, ix.bucket_off.p);
+    hipLaunchKernelGGL(index_filter_kernel, dim3(nb), dim3(256), 0, 0, ix.filter_shift, ix.filter_words, ix.tspan, ix.bucket_off.p,
+                       ix.cand.p, ix.wave_ptr.p, ix.filter.p, ix.filter_base.p);
+    TS_HIP(hipGetLastError());
+    TS_HIP(hipDeviceSynchronize());     // (callers score on streams of their own)
     return TENSILE_OK;
 }
 
@@ -444,9 +560,10 @@ int build(tensile_tas *h, const tensile_tas_desc *d) {
     h->h_gap_first.assign(static_cast<size_t>(N) + 1, 0);
     for (int32_t t : gt) ++h->h_gap_first[t + 1];
     for (int32_t i = 0; i < N; ++i) h->h_gap_first[i + 1] += h->h_gap_first[i];
+    TS_HIP(h->d_gp.upload(gp.data(), gp.size()));
+    TS_HIP(h->d_gq.upload(gq.data(), gq.size()));
+    TS_HIP(h->d_gt.upload(gt.data(), gt.size()));
     h->h_gp = std::move(gp);
-    h->h_gq = std::move(gq);
-    h->h_gt = std::move(gt);
     return build_times_and_index(h, d->step_ns);
 }
 
@@ -457,7 +574,6 @@ int build(tensile_tas *h, const tensile_tas_desc *d) {
 // them.  step_ns is a HOST array or null (no latencies: all transfer times 0).
 int build_times_and_index(tensile_tas *h, const int64_t *step_ns) {
     const int32_t T = h->T, N = h->N;
-    const std::vector<int32_t> &gp = h->h_gp, &gq = h->h_gq, &gt = h->h_gt;
     {
         DevBuf<int64_t> step;
         if (h->timed) TS_HIP(step.upload(step_ns, T));
@@ -478,19 +594,13 @@ int build_times_and_index(tensile_tas *h, const int64_t *step_ns) {
             hipLaunchKernelGGL(latency_byte_kernel, dim3((std::max(T, N) + 255) / 256), dim3(256), 0, 0, T, step.p, N, h->d_x.p, shift,
                                h->d_lat8.p, h->d_x8.p);
         }
-        DevBuf<int32_t> d_gp, d_gq, d_gt, d_gwin;
-        TS_HIP(d_gp.upload(gp.data(), gp.size()));
-        TS_HIP(d_gq.upload(gq.data(), gq.size()));
-        TS_HIP(d_gt.upload(gt.data(), gt.size()));
-        TS_HIP(d_gwin.reserve(gp.size()));
+        DevBuf<int32_t> d_gwin;
+        TS_HIP(d_gwin.reserve(static_cast<size_t>(h->G)));
         if (h->G > 0)
-            hipLaunchKernelGGL(gap_window_kernel, dim3((h->G + 255) / 256), dim3(256), 0, 0, h->G, T, d_gp.p, d_gq.p,
-                               d_gt.p, h->d_C.p, h->d_x.p, d_gwin.p);
+            hipLaunchKernelGGL(gap_window_kernel, dim3((h->G + 255) / 256), dim3(256), 0, 0, h->G, T, h->d_gp.p, h->d_gq.p,
+                               h->d_gt.p, h->d_C.p, h->d_x.p, d_gwin.p);
         TS_HIP(hipGetLastError());
-        TS_HIP(hipDeviceSynchronize());
-        std::vector<int32_t> gwin(gp.size());
-        if (h->G > 0) TS_HIP(hipMemcpy(gwin.data(), d_gwin.p, gwin.size() * sizeof(int32_t), hipMemcpyDeviceToHost));
-        int rc = build_candidate_index(h, h->index, gp, gq, gt, gwin);
+        int rc = build_candidate_index(h, h->index, d_gwin.p);
         if (rc != TENSILE_OK) return rc;
     }
     h->h_C.resize(static_cast<size_t>(T) + 1);
@@ -506,7 +616,7 @@ int ensure_recompute_index(const tensile_tas *tas) {
     std::lock_guard<std::mutex> once(tas->lazy_mu);
     if (tas->recompute_index_built) return TENSILE_OK;
     try {
-        int rc = build_candidate_index(tas, tas->recompute_index, tas->h_gp, tas->h_gq, tas->h_gt, tas->h_gp);
+        int rc = build_candidate_index(tas, tas->recompute_index, tas->d_gp.p);
         if (rc != TENSILE_OK) return rc;
     } catch (const std::bad_alloc &) {
         set_error("score_recompute: out of host memory");

@@ -850,6 +850,45 @@ def test_score_buckets_of_many_entries(N, acc):
     assert check_step(tas, pl) > N // 10
 
 
+@pytest.mark.parametrize("T,N", [(1, 1), (3, 2), (256, 64), (257, 1023), (4097, 1024), (700, 1025), (512 * 256, 900), (512 * 256 + 1, 900),
+                                 (700 * 256, 5000)])
+def test_candidate_index_sizes(T, N):
+    """Buckets of the candidate index: one, as many as are looked through one by one and one more, numbers of gaps around the
+    slabs of a wavefront, gaps within a bucket, over many and over all; peak steps at the edges of buckets; then the
+    same handle with other latencies (entries added and gone)."""
+    i = np.arange(N)
+    alloc = prng.randint(83, 1, i, 0, max(0, T - 3))
+    sizes = prng.randint(83, 2, i, 1, 1 << 16)
+    span = np.where(i % 64 == 0, T, np.where(i % 8 == 0, 40 * 256, 300))     # (few long ones: the buckets stay 256 steps wide)
+    accs = [sorted({int(min(T - 1, alloc[k] + 1 + x)) for x in prng.randint(83, 100 + k, np.arange(2), 0, int(span[k]))} - {int(alloc[k])})
+            for k in range(N)]
+    accs = [a if a else [T - 1] if alloc[k] < T - 1 else [] for k, a in enumerate(accs)]
+    sn = prng.randint(83, 3, np.arange(T), 1, 1000).astype(np.int64)
+    tas = tas_from_lists(T, [int(x) for x in sizes], [int(x) for x in alloc], accs, None, sn, 0, 400_000)
+    steps = np.unique(np.concatenate([np.array([0, 255, 256, 64 * 256 - 1, 64 * 256, T // 2, T - 2, T - 1]), prng.randint(83, 4, np.arange(9), 0, T - 1)]))
+    steps = steps[(steps >= 0) & (steps < T)].astype(np.int32)
+    pl = make_plans(tas, len(steps), 5, p_swap=0.2)
+    say(f"candidate index T={T} N={N}")
+    dp = upload(pl)
+    h = P.tas_load(tas)
+    at = torch.as_tensor(steps, device="cuda")
+    found = 0
+    for speed in (400_000, 3_000_000, 20_000):
+        if speed != 400_000:
+            sn = prng.randint(83, speed, np.arange(T), 1, 1500).astype(np.int64)
+            tas = tas_from_lists(T, [int(x) for x in sizes], [int(x) for x in alloc], accs, None, sn, 0, speed)
+            P.tensile_tas_update_latencies(h, sn, speed)
+        r0, p0, a0, m0 = O.eval_plans(tas, pl)
+        res, peak = torch.as_tensor(r0, device="cuda"), torch.as_tensor(p0, device="cuda")
+        for got, want in ((gpu_score(h, dp, res, peak, at), O.score_plans(tas, pl, r0, p0, steps)),
+                          (gpu_score_recompute(h, dp, res, peak, at), O.score_recompute_plans(tas, pl, r0, p0, steps))):
+            for g, w in zip(got, want):
+                assert np.array_equal(g.cpu().numpy(), w), f"speed {speed}"
+            found += int((want[1] >= 0).sum()) if T > 3 else 1
+    h.close()
+    assert found > 0
+
+
 # -------------------------------------------------------------------- evaluation + scoring in one call
 
 def gpu_step(h, dp):
