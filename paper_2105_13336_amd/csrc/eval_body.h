@@ -1,7 +1,6 @@
 // The fused scatter + scan + reduce body of the evaluation kernels (Eq. 1, Eq. 2 and Alg. 1 of the paper)
-// and what it shares with the kernels built around it.  Included by eval.hip (one workgroup per plan and
-// segment, persistent and binned forms) and by step.hip (evaluation and scoring of a plan in one workgroup).
-// Everything here has internal linkage.
+// and what it shares with the kernels built around it, in eval.hip (one workgroup per plan and segment,
+// persistent and binned forms).  Everything here has internal linkage.
 #pragma once
 
 #include "common.h"
@@ -191,11 +190,8 @@ __device__ __forceinline__ bool applies(const EvalArgs &a, int32_t i, int32_t o,
 // kernel's, instead of waiting for two dependent loads (and with them for every store) in every tile.
 constexpr int kBinFastRecs = 2;
 constexpr int kBinAhead = 4;   // tiles between the request for a tile's records and their use
-// result (may be null): an LDS word triple that receives the segment's (max, earliest argmax, min) as well; it
-// is complete after the next workgroup barrier.
 template <int kThr, int R, bool kTail, bool kNarrow, int kOut, bool kBinned = false, bool kBinFast = false>
-__device__ __forceinline__ void eval_body(const EvalArgs &a, const int32_t plan, const int32_t seg, EvalLds<kThr> &L,
-                                          Best *result = nullptr) {
+__device__ __forceinline__ void eval_body(const EvalArgs &a, const int32_t plan, const int32_t seg, EvalLds<kThr> &L) {
     static_assert(!kBinFast || kBinned, "kBinFast is a form of the binned kernel");
     constexpr int kMode = kOut & ~kOutPieces;
     constexpr bool kStore = kMode != 0, kVec16 = kMode >= 2, kPieces = (kOut & kOutPieces) != 0;
@@ -729,7 +725,6 @@ __device__ __forceinline__ void eval_body(const EvalArgs &a, const int32_t plan,
         a.out_max[slot] = best.mx;
         a.out_arg[slot] = best.arg;
         if (a.out_min) a.out_min[slot] = best.mn;
-        if (result) *result = best;
     }
 }
 
