@@ -365,6 +365,8 @@ int tensile_greedy_plan(const tensile_tas *tas, int64_t budget_bytes, const tens
  *   "link_packed"     0: every transfer is searched for in the cumulative latencies (1 = automatic)
  *   "step_fused"      0: in tensile_eval_score_plans the scoring reads the rows, as tensile_score_candidates does; else it
  *                     takes the maxima of the rows' 256-step blocks from the evaluation
+ *   "alloc_fail"      n > 0: the n-th allocation of device memory from now on is refused, once (for tests of what
+ *                     happens then)
  * TENSILE_E_INVAL for an unknown name. */
 int tensile_tuning_set(const char *knob, int value);
 

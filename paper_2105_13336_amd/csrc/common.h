@@ -18,6 +18,7 @@ struct GreedyBuffers;   // greedy.hip: what a run of the planner allocates, kept
 
 void set_error(const char *fmt, ...) __attribute__((format(printf, 1, 2)));
 int hip_fail(hipError_t e, const char *what);
+hipError_t device_malloc(void **p, size_t bytes);   // hipMalloc, or what the tuning knob "alloc_fail" makes of it
 
 #define TS_HIP(call)                                               \
     do {                                                           \
@@ -46,7 +47,7 @@ struct DevBuf {
     hipError_t reserve(size_t count) {
         if (p && count <= n) return hipSuccess;
         release();
-        hipError_t e = hipMalloc(reinterpret_cast<void **>(&p), (count ? count : 1) * sizeof(T));
+        hipError_t e = device_malloc(reinterpret_cast<void **>(&p), (count ? count : 1) * sizeof(T));
         if (e == hipSuccess) n = count;
         else p = nullptr;
         return e;
@@ -97,7 +98,7 @@ struct EvalArgs {
 // enqueued on one stream run one after the other and share it, calls on different streams never touch the
 // same memory.  `mu` is held while a call sizes the buffers and enqueues its kernels, so two host threads
 // that use the same stream enqueue whole calls, never interleaved ones.  A buffer that has to grow is
-// replaced (at least doubled) and the old one is parked in `retired` until the handle is freed: kernels
+// replaced (doubled at least, if the memory is there) and the old one is parked in `retired` until the handle is freed: kernels
 // enqueued earlier may still read it, and nothing here ever waits for the device.
 // fixed_base != null: the workspace lives in a preallocated region of fixed_bytes (see eval.hip, the entry
 // point that allocates nothing); buffers are then carved out of it per call and never grow.
@@ -150,6 +151,7 @@ struct Tuning {
     int score_blocks = 0;      // size of the scoring grid
     int link_packed = 1;       // 0: every transfer is searched for in C
     int step_fused = -1;       // tensile_eval_score_plans: 0 = scoring reads the rows, else the evaluation hands it their block maxima
+    int alloc_fail = 0;        // n > 0: the n-th allocation of device memory from now on is refused, once (counts down)
 };
 extern Tuning g_tuning;
 

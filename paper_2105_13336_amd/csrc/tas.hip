@@ -28,6 +28,7 @@ void set_error(const char *fmt, ...) {
 
 int hip_fail(hipError_t e, const char *what) {
     set_error("HIP error %d (%s) in %s", static_cast<int>(e), hipGetErrorString(e), what);
+    (void)hipGetLastError();   // reported here: the runtime keeps it for the thread, and a later launch's check would find it again
     return e == hipErrorOutOfMemory ? TENSILE_E_NOMEM : TENSILE_E_HIP;
 }
 

@@ -8,6 +8,12 @@ namespace tensile {
 
 Tuning g_tuning;
 
+hipError_t device_malloc(void **p, size_t bytes) {
+    // (the refusal is the runtime's own: no GPU has this much)
+    if (g_tuning.alloc_fail > 0 && --g_tuning.alloc_fail == 0) bytes = size_t{1} << 60;
+    return hipMalloc(p, bytes);
+}
+
 Workspace::~Workspace() {
     for (void *p : retired) (void)hipFree(p);
 }
@@ -32,9 +38,15 @@ int Workspace::provide(DevBuf<T> &b, size_t count, const char *what, bool *fresh
     }
     if (b.p && count <= b.n) return TENSILE_OK;
     size_t want = count ? count : 1;
+    const size_t least = want;
     if (want < 2 * b.n) want = 2 * b.n;   // at least doubled: what is parked in `retired` stays below what is in use
     T *fresh_p = nullptr;
-    const hipError_t e = hipMalloc(reinterpret_cast<void **>(&fresh_p), want * sizeof(T));
+    hipError_t e = device_malloc(reinterpret_cast<void **>(&fresh_p), want * sizeof(T));
+    if (e != hipSuccess && want > least) {   // (memory for what is needed may still be there)
+        (void)hipGetLastError();
+        want = least;
+        e = device_malloc(reinterpret_cast<void **>(&fresh_p), want * sizeof(T));
+    }
     if (e != hipSuccess) return hip_fail(e, what);
     if (b.p) retired.push_back(b.p);
     b.p = fresh_p;
@@ -96,7 +108,7 @@ extern "C" int tensile_tuning_set(const char *knob, int value) {
         {"eval_persistent", &Tuning::eval_persistent}, {"eval_slots", &Tuning::eval_slots}, {"eval_nt", &Tuning::eval_nt},
         {"eval_seg_steps", &Tuning::eval_seg_steps},
         {"score_blocks", &Tuning::score_blocks}, {"link_packed", &Tuning::link_packed},
-        {"step_fused", &Tuning::step_fused},
+        {"step_fused", &Tuning::step_fused},   {"alloc_fail", &Tuning::alloc_fail},
     };
     for (const auto &row : table)
         if (std::strcmp(knob, row.name) == 0) {
