@@ -400,7 +400,7 @@ __global__ __launch_bounds__(Shape<kTab>::kThr) __attribute__((amdgpu_waves_per_
     const ScoreArgs a) {
     __shared__ ScoreLds<kTab> lds;
     int32_t filter_of = -1;      // bucket whose filter is in LDS
-    for (int32_t b = blockIdx.x; b < a.B; b += gridDim.x) score_plan<kTab, kVec, kTable>(a, b, lds, filter_of);
+    for (int64_t b = blockIdx.x; b < a.B; b += gridDim.x) score_plan<kTab, kVec, kTable>(a, static_cast<int32_t>(b), lds, filter_of);
 }
 
 // ---- one iteration of the planner on the device --------------------------------------------------------
@@ -693,13 +693,17 @@ int launch_score(const tensile_tas *tas, Workspace &ws, const CandIndex &ix, boo
     // One workgroup per plan, so that they start as others end; on long rows as many as the device keeps resident (four per
     // CU), the plans dealt evenly among them.  (16,384 plans of 50,000 steps: resident workgroups 2.70 ms, one per plan 2.59;
     // 4,096 of 6,000 steps 167 and 159 us with evaluation; 1,024 of 10^6 steps 2.08 and 2.16 ms.)
-    int32_t blocks = plans->B;
+    // (A launch has room for fewer than 2^32 threads: past kMostBlocks a workgroup takes several plans.)
+    constexpr int32_t kMostBlocks = 1 << 22;
+    static_assert(int64_t{kMostBlocks} * Shape<kTabShort>::kThr < int64_t{1} << 32, "threads of a launch");
+    const int32_t most = plans->B < kMostBlocks ? plans->B : kMostBlocks;
+    int32_t blocks = most;
     if (tab == kTabLong) {
         const int64_t resident_blocks = 4 * static_cast<int64_t>(tas->num_cus), rounds = (plans->B + resident_blocks - 1) / resident_blocks;
         blocks = static_cast<int32_t>((plans->B + rounds - 1) / rounds);
     }
     if (const int v = g_tuning.score_blocks; v > 0)   // tuning knob: size of the grid (plans are dealt round-robin)
-        blocks = v < plans->B ? v : plans->B;
+        blocks = v < most ? v : most;
     const bool vec16 = tas->T % 2 == 0 && reinterpret_cast<uintptr_t>(resident) % 16 == 0;
     auto launch = [&](auto tab_tag) {
         constexpr int kTab = decltype(tab_tag)::value;

@@ -10,7 +10,8 @@ if not torch.cuda.is_available():
     pytest.skip("needs a GPU", allow_module_level=True)
 
 import paper_2105_13336_amd as P  # noqa: E402
-from test_gpu_parity import check_step, gpu_eval, say, upload  # noqa: E402
+from oracle import oracle as O  # noqa: E402
+from test_gpu_parity import check_step, gpu_eval, gpu_score, gpu_score_recompute, gpu_step, say, upload  # noqa: E402
 from workloads import make_plans, small_random_tas  # noqa: E402
 
 
@@ -49,4 +50,26 @@ def test_a_refused_allocation_is_reported_once(tuning):
     s.synchronize()
     _, p0, a0, _ = gpu_eval(h, dp)
     assert np.array_equal(peak.cpu().numpy(), p0.cpu().numpy()) and np.array_equal(arg.cpu().numpy(), a0.cpu().numpy())
+    h.close()
+
+
+def test_scores_of_eight_million_plans():
+    """More plans than a launch of one workgroup each has room for (2^32 threads): sixteen plans, over and over."""
+    tas = small_random_tas(9002, N=4, T=12, max_acc=3, timed=True, link_bytes_per_us=400_000)
+    pl = make_plans(tas, 16, 7, p_swap=0.5)
+    times = (1 << 19) + 1
+    r0, p0, a0, m0 = O.eval_plans(tas, pl)
+    want = [np.stack(x) for x in zip(O.score_plans(tas, pl, r0, p0, a0), O.score_recompute_plans(tas, pl, r0, p0, a0))]
+    up = lambda a: torch.from_numpy(np.ascontiguousarray(a)).cuda()
+    lens = up(np.diff(pl.plan_offsets)).repeat(times)
+    dp = P.DevicePlans(torch.cat([lens.new_zeros(1), torch.cumsum(lens, 0)]), *(up(x).repeat(times) for x in (pl.iv_tensor, pl.iv_out, pl.iv_in, pl.iv_kind)))
+    say(f"scores of {dp.B} plans, {dp.n_intervals} intervals")
+    assert dp.B * 512 >= 1 << 32
+    same = lambda got, one: bool((got.view(times, *one.shape) == up(one)).all())
+    h = P.tas_load(tas)
+    res, peak, arg, mn, *step = gpu_step(h, dp)
+    assert same(res, r0) and same(peak, p0) and same(arg, a0) and same(mn, m0)
+    for k, got in enumerate((gpu_score(h, dp, res, peak, arg), gpu_score_recompute(h, dp, res, peak, arg), step)):
+        for g, w in zip(got, want):
+            assert same(g, w[k % 2]), f"call {k}"
     h.close()
