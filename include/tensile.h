@@ -229,7 +229,10 @@ int tensile_score_candidates(const tensile_tas *tas, const tensile_plans *plans,
  * scores are computed from it); the two kernels are enqueued back to back
  * under one lock of the stream's workspace, which holds what the evaluation
  * hands to the scoring (the maxima of every 256 steps of the rows: 1/256 of
- * the rows' size).  Asynchronous on hip_stream.  B == 0 is a no-op. */
+ * the rows' size).  Where that cannot be had - no memory, or the stream is
+ * being captured and no earlier call on it was as large - the scoring reads the
+ * rows instead, with the same results.  Asynchronous on hip_stream.  B == 0 is
+ * a no-op. */
 int tensile_eval_score_plans(const tensile_tas *tas, const tensile_plans *plans, int64_t *resident, int64_t *peak,
                              int32_t *argmax, int64_t *min_resident, int64_t *score, int32_t *win_out, int32_t *win_in,
                              void *hip_stream);

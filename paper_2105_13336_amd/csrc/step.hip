@@ -7,6 +7,19 @@
 
 namespace tensile {
 
+namespace {
+
+// Whether a capture is under way that an allocation would break.  (A question about the default stream is refused while
+// another stream's capture rules out work on it: a capture too.)
+bool capturing(hipStream_t stream) {
+    hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+    const hipError_t e = hipStreamIsCapturing(stream, &status);
+    if (e != hipSuccess) (void)hipGetLastError();
+    return e != hipSuccess || status != hipStreamCaptureStatusNone;
+}
+
+}  // namespace
+
 int launch_step(const tensile_tas *tas, Workspace &ws, const tensile_plans *plans, int64_t *resident, int64_t *peak,
                 int32_t *argmax, int64_t *min_resident, int64_t *score, int32_t *win_out, int32_t *win_in) {
     EvalArgs ea{};
@@ -15,10 +28,13 @@ int launch_step(const tensile_tas *tas, Workspace &ws, const tensile_plans *plan
     ea.iv_tensor = plans->iv_tensor; ea.iv_out = plans->iv_out; ea.iv_in = plans->iv_in;
     ea.size = tas->d_size.p; ea.size_units = tas->d_size_units.p; ea.size_shift = tas->size_shift;
     ea.MF0 = tas->d_MF0.p; ea.dMF0 = tas->d_dMF0.p; ea.resident = resident;
-    // (what the rows' pieces come to: 1/256 of the rows' bytes.  Without the memory for it, scoring reads the rows.)
-    const size_t n_mini = (static_cast<size_t>(tas->T) + kScoreMini - 1) / kScoreMini;
-    // (tuning knob step_fused: 0 = scoring reads the rows)
-    if (tas->N > 0 && g_tuning.step_fused != 0 && ws.provide(ws.blk_max, static_cast<size_t>(plans->B) * n_mini, "eval_score_plans: maxima of the rows' pieces") == TENSILE_OK)
+    // The maxima of the rows' pieces: 1/256 of the rows' bytes.  Without the memory for them scoring reads the rows; so it does
+    // while the stream is being captured, unless an earlier call has left enough (an allocation would end the capture, and
+    // the call has no other need of one), and on request (tuning knob step_fused: 0).
+    const size_t n_max = static_cast<size_t>(plans->B) * ((static_cast<size_t>(tas->T) + kScoreMini - 1) / kScoreMini);
+    const bool there = ws.blk_max.p && n_max <= ws.blk_max.n;
+    if (tas->N > 0 && g_tuning.step_fused != 0 && (there || !capturing(ws.stream)) &&
+        ws.provide(ws.blk_max, n_max, "eval_score_plans: maxima of the rows' pieces") == TENSILE_OK)
         ea.blk_max = ws.blk_max.p;
     const int rc = launch_eval(tas, ws, ea, peak, argmax, min_resident);
     if (rc != TENSILE_OK) return rc;

@@ -73,3 +73,58 @@ def test_scores_of_eight_million_plans():
         for g, w in zip(got, want):
             assert same(g, w[k % 2]), f"call {k}"
     h.close()
+
+
+@pytest.mark.parametrize("first", ["the two calls", "the one call"])
+def test_eval_score_in_a_captured_stream(first):
+    """The call enqueues without allocating in a stream that is being captured: after earlier calls of the two parts (the
+    scoring then reads the rows) and after one of its own.  Several replays on other plans, eager calls in between."""
+    tas = small_random_tas(9003, N=150, T=5003, max_acc=5, timed=True, link_bytes_per_us=400_000)
+    B = 40
+    batches = [make_plans(tas, B, 20 + k, p_swap=0.5) for k in range(4)]
+    K = max(pl.n_intervals for pl in batches)
+    say(f"captured eval+score, warmed by {first}")
+    h = P.tas_load(tas)
+    s = torch.cuda.Stream()
+    with torch.cuda.stream(s):
+        offs = torch.zeros(B + 1, dtype=torch.int64, device="cuda")
+        t, o, r = (torch.zeros(K, dtype=torch.int32, device="cuda") for _ in range(3))
+        dp = P.DevicePlans(offs, t, o, r, None)
+
+        def put(pl):
+            for dst, src in ((offs, pl.plan_offsets), (t, pl.iv_tensor), (o, pl.iv_out), (r, pl.iv_in)):
+                dst[:len(src)].copy_(torch.from_numpy(src))
+
+        def outputs():
+            return [torch.full(shape, -3, dtype=dt, device="cuda") for shape, dt in
+                    (((B, tas.T), torch.int64), ((B,), torch.int64), ((B,), torch.int32), ((B,), torch.int64),
+                     ((B, tas.N), torch.int64), ((B, tas.N), torch.int32), ((B, tas.N), torch.int32))]
+
+        def check(out, pl):
+            r0, p0, a0, m0 = O.eval_plans(tas, pl)
+            s.synchronize()
+            for k, (g, w) in enumerate(zip(out, (r0, p0, a0, m0, *O.score_plans(tas, pl, r0, p0, a0)))):
+                assert np.array_equal(g.cpu().numpy(), w), f"output {k}"
+
+        out, eager = outputs(), outputs()
+        put(batches[0])
+        if first == "the one call":
+            P.tensile_eval_score_plans(h, dp, *eager, stream=s)
+        else:
+            P.tensile_eval_plans(h, dp, *eager[:4], stream=s)
+            P.tensile_score_candidates(h, dp, *eager[:3], *eager[4:], stream=s)
+        check(eager, batches[0])
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=s):
+        P.tensile_eval_score_plans(h, dp, *out, stream=s)
+    with torch.cuda.stream(s):
+        for pl in batches + batches[:1]:
+            put(pl)
+            for x in out:
+                x.fill_(-5)
+            graph.replay()
+            check(out, pl)
+            P.tensile_eval_score_plans(h, dp, *eager, stream=s)
+            check(eager, pl)
+    del graph
+    h.close()
