@@ -119,7 +119,11 @@ int tensile_tas_info(const tensile_tas *tas, int64_t *unscheduled_peak, int32_t 
  * evaluated before stay valid and can be scored again.  step_ns: HOST [T], all
  * > 0, or NULL for "no latencies"; link_bytes_per_us > 0 when step_ns is given.
  * Synchronous (waits for the device first).  The caller must not run any other
- * call on this handle at the same time. */
+ * call on this handle at the same time.  Arguments that are refused leave the
+ * handle as it was.  Should the update fail later (no memory), the calls that
+ * need the latencies - tensile_score_candidates, tensile_eval_score_plans,
+ * tensile_eval_link, tensile_greedy_plan - return TENSILE_E_INVAL until an
+ * update succeeds; the others are not affected. */
 int tensile_tas_update_latencies(tensile_tas *tas, const int64_t *step_ns, int64_t link_bytes_per_us);
 
 /* Copies MF0 into a HOST buffer of T words (synchronous). */

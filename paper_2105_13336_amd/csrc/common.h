@@ -210,6 +210,7 @@ struct tensile_tas {
     tensile::DevBuf<uint8_t> d_lat8, d_x8;    // [T], [N] when timed: see latency_byte_kernel
     int32_t lat_form = 0;                     // ... how many a record holds: 6 or 4
     tensile::CandIndex index;                 // swap candidates: o = earliest feasible swap-out step
+    bool times_built = false;                 // C, x, the link's tables and `index` belong together (false after an update that failed)
     // recomputation candidates (every gap, o = p), built by the first tensile_score_recompute
     mutable std::mutex lazy_mu;               // guards the two tables that are built on first use
     mutable tensile::CandIndex recompute_index;
@@ -287,6 +288,7 @@ void drop_greedy_cache(const tensile_tas *tas);   // (at tensile_tas_free)
 // tas.hip
 int check_plans(const tensile_tas *tas, const tensile_plans *plans, const char *who);   // argument checks shared by the entry points
 int build_times_and_index(tensile_tas *tas, const int64_t *step_ns_host);
+int check_times(const tensile_tas *tas, const char *who);   // whether the tables that follow from the latencies are there
 int ensure_recompute_index(const tensile_tas *tas);
 
 }  // namespace tensile

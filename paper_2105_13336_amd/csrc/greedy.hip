@@ -181,6 +181,7 @@ extern "C" int tensile_greedy_plan(const tensile_tas *tas, int64_t budget_bytes,
         for (int32_t j = 0; j < tas->J; ++j)
             if (opt.msr_num[j] < 0) { set_error("greedy_plan: msr_num[%d] is negative", j); return TENSILE_E_INVAL; }
     }
+    if (const int rc = check_times(tas, "greedy_plan"); rc != TENSILE_OK) return rc;
     const int32_t T = tas->T, N = tas->N;
     const int32_t max_new = opt.max_iters > 0 ? opt.max_iters : INT32_MAX;
 

@@ -55,6 +55,8 @@ extern "C" int tensile_eval_score_plans(const tensile_tas *tas, const tensile_pl
         set_error("eval_score_plans: resident, peak, argmax and score are required");
         return TENSILE_E_INVAL;
     }
+    rc = check_times(tas, "eval_score_plans");
+    if (rc != TENSILE_OK) return rc;
     WorkspaceLock ws = acquire_workspace(tas, static_cast<hipStream_t>(hip_stream));
     return launch_step(tas, *ws, plans, resident, peak, argmax, min_resident, score, win_out, win_in);
 }

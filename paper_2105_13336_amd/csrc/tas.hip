@@ -575,6 +575,7 @@ int build(tensile_tas *h, const tensile_tas_desc *d) {
 // them.  step_ns is a HOST array or null (no latencies: all transfer times 0).
 int build_times_and_index(tensile_tas *h, const int64_t *step_ns) {
     const int32_t T = h->T, N = h->N;
+    h->times_built = false;      // (a table may be replaced and the next one fail)
     {
         DevBuf<int64_t> step;
         if (h->timed) TS_HIP(step.upload(step_ns, T));
@@ -608,7 +609,14 @@ int build_times_and_index(tensile_tas *h, const int64_t *step_ns) {
     h->h_x.resize(static_cast<size_t>(N));
     TS_HIP(hipMemcpy(h->h_C.data(), h->d_C.p, (static_cast<size_t>(T) + 1) * sizeof(int64_t), hipMemcpyDeviceToHost));
     if (N > 0) TS_HIP(hipMemcpy(h->h_x.data(), h->d_x.p, static_cast<size_t>(N) * sizeof(int64_t), hipMemcpyDeviceToHost));
+    h->times_built = true;
     return TENSILE_OK;
+}
+
+int check_times(const tensile_tas *tas, const char *who) {
+    if (tas->times_built) return TENSILE_OK;
+    set_error("%s: the last tensile_tas_update_latencies on this handle failed half way; update the latencies again first", who);
+    return TENSILE_E_INVAL;
 }
 
 // The index of the recomputation candidates: every gap, released right after the access that
@@ -836,6 +844,8 @@ int tensile_eval_link(const tensile_tas *tas, const tensile_plans *plans, int32_
     if (rc != TENSILE_OK) return rc;
     if (plans->B == 0) return TENSILE_OK;
     if (!link_peak) { set_error("eval_link: link_peak is required"); return TENSILE_E_INVAL; }
+    rc = check_times(tas, "eval_link");
+    if (rc != TENSILE_OK) return rc;
     WorkspaceLock ws = acquire_workspace(tas, static_cast<hipStream_t>(hip_stream));
     return launch_link(tas, *ws, plans, reuse_host_copies != 0, link, link_peak, link_argmax, overbooked);
 }
@@ -850,6 +860,8 @@ int tensile_score_candidates(const tensile_tas *tas, const tensile_plans *plans,
         set_error("score_candidates: resident, peak, argmax and score are required");
         return TENSILE_E_INVAL;
     }
+    rc = check_times(tas, "score_candidates");
+    if (rc != TENSILE_OK) return rc;
     WorkspaceLock ws = acquire_workspace(tas, static_cast<hipStream_t>(hip_stream));
     return launch_score(tas, *ws, tas->index, false, plans, resident, peak, argmax, score, win_out, win_in);
 }

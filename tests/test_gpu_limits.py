@@ -11,7 +11,8 @@ if not torch.cuda.is_available():
 
 import paper_2105_13336_amd as P  # noqa: E402
 from oracle import oracle as O  # noqa: E402
-from test_gpu_parity import check_step, gpu_eval, gpu_score, gpu_score_recompute, gpu_step, say, upload  # noqa: E402
+from test_gpu_parity import (check_eval, check_link, check_step, gpu_eval, gpu_score, gpu_score_recompute, gpu_step,  # noqa: E402
+                             same_greedy, say, upload)  # noqa: E402
 from workloads import make_plans, small_random_tas  # noqa: E402
 
 
@@ -128,3 +129,50 @@ def test_eval_score_in_a_captured_stream(first):
             check(eager, pl)
     del graph
     h.close()
+
+
+def test_an_update_of_the_latencies_that_fails_half_way(tuning):
+    """Whichever allocation of the update is refused: what depends on the latencies is refused until an update succeeds,
+    the rest works, and a later update leaves nothing of the failure behind."""
+    import copy
+    tas = small_random_tas(9004, N=200, T=9001, max_acc=5, timed=True, link_bytes_per_us=400_000)
+    before = copy.copy(tas)
+    before.step_ns, before.link_bytes_per_us = None, 0
+    pl = make_plans(tas, 5, 9, p_swap=0.5)
+    dp = upload(pl)
+    r0, p0, a0, _ = O.eval_plans(tas, pl)
+    failed = 0
+    for n in range(1, 40):
+        h = P.tas_load(before)                 # (no latencies: the tables that need them have never been allocated)
+        res, peak, arg, mn = gpu_eval(h, dp)
+        s0 = gpu_score_recompute(h, dp, res, peak, arg)
+        tuning("alloc_fail", n)
+        try:
+            P.tensile_tas_update_latencies(h, tas.step_ns, tas.link_bytes_per_us)
+        except P.TensileError as e:
+            assert e.code == P.binding.TENSILE_E_NOMEM
+            failed += 1
+        else:
+            tuning("alloc_fail", 0)
+            h.close()
+            break
+        say(f"update of the latencies, allocation {n} refused")
+        pk = torch.empty(pl.B, dtype=torch.int32, device="cuda")
+        for call in (lambda: gpu_score(h, dp, res, peak, arg), lambda: gpu_step(h, dp), lambda: P.tensile_eval_link(h, dp, pk, None),
+                     lambda: P.tensile_greedy_plan(h, 0, max_iters=5, capacity=8)):
+            with pytest.raises(P.TensileError) as e:
+                call()
+            assert e.value.code == P.binding.TENSILE_E_INVAL and "update" in str(e.value)
+        with pytest.raises(P.TensileError):    # (refused before anything is touched: changes nothing about it)
+            P.tensile_tas_update_latencies(h, tas.step_ns, 0)
+        check_eval(tas, pl, h=h, label="after a failed update")
+        for g, w in zip(gpu_score_recompute(h, dp, res, peak, arg), s0):
+            assert torch.equal(g, w)
+        P.tensile_tas_update_latencies(h, tas.step_ns, tas.link_bytes_per_us)
+        for g, w in zip(gpu_score(h, dp, res, peak, arg), O.score_plans(tas, pl, r0, p0, a0)):
+            assert np.array_equal(g.cpu().numpy(), w)
+        check_step(tas, pl, h=h)
+        check_link(tas, pl, False, h=h)
+        same_greedy(P.tensile_greedy_plan(h, 0, max_iters=20, capacity=32), O.greedy(tas, 0, max_iters=20))
+        h.close()
+    assert failed >= 4
