@@ -166,6 +166,8 @@ constexpr int kIndexShifts = 24;   // bucket widths of 2^8 .. 2^31 steps
 // through its 64's only: linear in the buckets times the gaps either way, but the lists keep the factor small (130,000
 // steps, 513 buckets: 0.80 ms flat, 0.70 with lists; 10^6 steps, 3,907 buckets: 15.5 and 4.5; at 512 no difference).
 constexpr int32_t kIndexFlat = 512;
+constexpr int32_t kMostBuckets = 1 << 21;   // a workgroup each, and HIP's launches have room for fewer than 2^32 threads
+static_assert(int64_t{kMostBuckets} * kIndexThr < int64_t{1} << 32, "threads of a launch");
 
 // n_entries[k] += entries an index with buckets of 2^(8 + k) steps would have.
 __global__ __launch_bounds__(kIndexThr) void index_size_kernel(int32_t G, const int32_t *gwin, const int32_t *gq,
@@ -419,8 +421,8 @@ int build_timeline(const tensile_tas *h, const int64_t *d_size, int64_t base_val
 // A gap (p, q) with earliest swap-out step o >= 0 is a scoring candidate at the peak steps
 // t* with o < t* < q.  File it under every bucket of 2^shift steps that o+1 .. q-1 overlaps;
 // the bucket width starts at 256 steps and doubles while the index would hold more than
-// about 16 entries per gap (or its filters more than 256 MiB).  CandIndex (common.h) lists
-// what is kept per bucket.  d_gwin: [G] the gaps' earliest swap-out steps.
+// about 16 entries per gap, its filters more than 256 MiB, or more than kMostBuckets buckets
+// (sequences of more than 2^29 steps).  CandIndex (common.h) lists what is kept per bucket.  d_gwin: [G] the gaps' earliest swap-out steps.
 int build_candidate_index(const tensile_tas *h, CandIndex &ix, const int32_t *d_gwin) {
     const int32_t T = h->T, G = h->G;
     ix.filter_shift = 0;
@@ -437,8 +439,9 @@ int build_candidate_index(const tensile_tas *h, CandIndex &ix, const int32_t *d_
     }
     int32_t shift = 8;
     for (;; ++shift) {
-        const uint64_t filter_bytes = (static_cast<uint64_t>((T - 1) >> shift) + 1) * (8 * static_cast<uint64_t>(ix.filter_words));
-        if ((n_entries[shift - 8] <= 16 * static_cast<uint64_t>(G) + 4096 && filter_bytes <= (256u << 20)) || (int64_t{1} << shift) >= T) break;
+        const uint64_t buckets = static_cast<uint64_t>((T - 1) >> shift) + 1, filter_bytes = buckets * (8 * static_cast<uint64_t>(ix.filter_words));
+        const bool fits = n_entries[shift - 8] <= 16 * static_cast<uint64_t>(G) + 4096 && filter_bytes <= (256u << 20) && buckets <= kMostBuckets;
+        if (fits || (int64_t{1} << shift) >= T) break;
     }
     const uint64_t entries = n_entries[shift - 8];
     if (entries > static_cast<uint64_t>(INT32_MAX) / 4) { set_error("tas_load: candidate index too large"); return TENSILE_E_RANGE; }

@@ -13,7 +13,7 @@ import paper_2105_13336_amd as P  # noqa: E402
 from oracle import oracle as O  # noqa: E402
 from test_gpu_parity import (check_eval, check_link, check_step, gpu_eval, gpu_score, gpu_score_recompute, gpu_step,  # noqa: E402
                              same_greedy, say, upload)  # noqa: E402
-from workloads import make_plans, small_random_tas  # noqa: E402
+from workloads import make_plans, small_random_tas, tas_from_lists  # noqa: E402
 
 
 @pytest.mark.parametrize("T,B", [(6000, 300), (20011, 600)])
@@ -176,3 +176,17 @@ def test_an_update_of_the_latencies_that_fails_half_way(tuning):
         same_greedy(P.tensile_greedy_plan(h, 0, max_iters=20, capacity=32), O.greedy(tas, 0, max_iters=20))
         h.close()
     assert failed >= 4
+
+
+def test_a_sequence_of_more_than_a_thousand_million_steps():
+    """So many steps that the candidate index could have more buckets than a launch takes workgroups of its kernels."""
+    T = (1 << 30) + 5
+    say(f"T={T}")
+    #          present          used at            (the gap of tensor 0 around the peak is the one candidate)
+    tas = tas_from_lists(T, [10, 7, 3], [0, 500, T - 9], [[9, 1000], [501], [T - 2]])
+    h = P.tas_load(tas)
+    assert P.tensile_tas_info(h) == (17, 500)
+    g = P.tensile_greedy_plan(h, 0, max_iters=3, capacity=4)
+    assert [x.tolist() for x in (g["iv_tensor"], g["iv_out"], g["iv_in"])] == [[0], [9], [1000]]
+    assert g["peak_trace"].tolist() == [17, 10] and g["final_peak"] == 10
+    h.close()
