@@ -54,6 +54,7 @@ constexpr int kTile = kCells - 4;                    // ... and holds: up to thr
 constexpr int kTileWords = kCells / 2;               // two 16-bit counters per word: 64 KB
 constexpr int kPass = 6144;                          // intervals per pass (at most 2 * kPass endpoints per step: far below 2^15)
 constexpr int kRounds = 4;                           // records a transfer may take before C is searched
+constexpr int64_t kMostScratch = int64_t{4} << 30;   // bytes of scratch that two workgroups per CU may take
 constexpr int kFirstRounds = 4;                      // reuse: at most this many tables of kTileWords tensors, one after the other
 static_assert(2 * kPass < (1 << 15), "16-bit counters");
 
@@ -130,7 +131,7 @@ __device__ unsigned long long g_link_prof[8];
 #endif
 
 // kForm: latencies per record.  kNear: rows of at most 65,534 steps, whose endpoints are kept in 16 bits each.
-// kThr: 512, two workgroups per CU, or 1024 for batches of no more plans than CUs, which would leave half of every CU idle
+// kThr: 512, two workgroups per CU, or 1024 and one, mostly for batches of no more plans than CUs, which would leave half of every CU idle
 // (256 plans of 60,000 intervals on 10^6 steps: 33 ms with 512 threads and passes added up step by step; 3.96 with 1024 and
 // passes added up 16 bytes at a time).
 template <int kThr, int kForm, bool kNear>
@@ -590,10 +591,17 @@ int launch_link(const tensile_tas *tas, Workspace &ws, const tensile_plans *plan
     a.records = tas->d_lat_records.p; a.lat8 = tas->d_lat8.p; a.x8 = tas->d_x8.p;
     a.search_only = g_tuning.link_packed == 0 ? 1 : 0;   // (testing aid)
     while ((int64_t{1} << a.search_bits) <= T) ++a.search_bits;
-    const bool wide = B <= tas->num_cus;                 // (one workgroup per CU: a large one)
-    const int32_t slots = 2 * tas->num_cus, grid = B < slots ? B : slots;
-    // (the table in global memory is only for plans the kernel cannot serve from LDS: see reuse_lds there)
-    if (reuse && (tas->N > kFirstRounds * kTileWords || plans->n_intervals > kPass)) {
+    // scratch per workgroup: the table of plans that the kernel cannot serve from LDS (see reuse_lds there), and the row where
+    // the passes of a long plan add up
+    const bool needs_first = reuse && (tas->N > kFirstRounds * kTileWords || plans->n_intervals > kPass);
+    const bool needs_acc = !link && plans->n_intervals > kPass;
+    const int64_t per_group = 4 * ((needs_first ? int64_t{tas->N} : 0) + (needs_acc ? int64_t{T} : 0));
+    // One large workgroup per CU when there are no more plans than that - and when the scratch of two per CU would be out of
+    // proportion (rows of more than two million steps): a plan is many tiles then, and one workgroup per CU takes plans as
+    // fast as two (60,000 intervals on 10^6 steps: 256 plans in one round 3.79 ms, 1,024 with two per CU 15.2).
+    const bool wide = B <= tas->num_cus || 2 * tas->num_cus * per_group > kMostScratch;
+    const int32_t slots = wide ? tas->num_cus : 2 * tas->num_cus, grid = B < slots ? B : slots;
+    if (needs_first) {
         const size_t need = static_cast<size_t>(grid) * static_cast<size_t>(tas->N);
         bool fresh = false;
         const int rc = ws.provide(ws.link_first, need, "eval_link: earliest swap-out table", &fresh);
@@ -605,7 +613,7 @@ int launch_link(const tensile_tas *tas, Workspace &ws, const tensile_plans *plan
         }
         a.first_out = ws.link_first.p;
     }
-    if (!link && plans->n_intervals > kPass) {   // some plan may need several passes
+    if (needs_acc) {   // some plan may need several passes
         const size_t need = static_cast<size_t>(grid) * static_cast<size_t>(T);
         const int rc = ws.provide(ws.link_acc, need, "eval_link: accumulation rows");
         if (rc != TENSILE_OK) return rc;

@@ -13,7 +13,7 @@ import paper_2105_13336_amd as P  # noqa: E402
 from oracle import oracle as O  # noqa: E402
 from test_gpu_parity import (check_eval, check_link, check_step, gpu_eval, gpu_score, gpu_score_recompute, gpu_step,  # noqa: E402
                              same_greedy, say, upload)  # noqa: E402
-from workloads import make_plans, small_random_tas, tas_from_lists  # noqa: E402
+from workloads import make_plans, plans_from_lists, small_random_tas, tas_from_lists  # noqa: E402
 
 
 @pytest.mark.parametrize("T,B", [(6000, 300), (20011, 600)])
@@ -189,4 +189,36 @@ def test_a_sequence_of_more_than_a_thousand_million_steps():
     g = P.tensile_greedy_plan(h, 0, max_iters=3, capacity=4)
     assert [x.tolist() for x in (g["iv_tensor"], g["iv_out"], g["iv_in"])] == [[0], [9], [1000]]
     assert g["peak_trace"].tolist() == [17, 10] and g["final_peak"] == 10
+    h.close()
+
+
+def test_link_scratch_of_very_long_rows():
+    """Plans of several passes without rows, more of them than CUs, on rows so long that a scratch row per workgroup is
+    kept to one workgroup per CU."""
+    T, B = 2_200_001, 530
+    tas = small_random_tas(9005, N=60, T=T, max_acc=40, timed=True, link_bytes_per_us=400_000)
+    few = make_plans(tas, 3, 11, p_swap=0.9)
+    lists = []
+    for b, n in ((0, 6150), (1, 12_300), (2, 40)):
+        t, o, r, k = few.plan(b)
+        one = [(int(t[j]), int(o[j]), int(r[j]), int(k[j])) for j in range(len(t))]
+        lists.append((one * (n // len(one) + 1))[:n])
+    pl = plans_from_lists(lists)
+    _, p0, a0, o0 = O.link_occupancy(tas, pl, reuse=True)
+    which = np.arange(B) % 3
+    which[3:-3] = 2                            # (the long ones first and last: most plans are short)
+    pl = pl.select(which)
+    say(f"link scratch T={T} B={B} K={pl.n_intervals}")
+    h = P.tas_load(tas)
+    dp = upload(pl)
+    out = [torch.full((B,), -7, dtype=torch.int32, device="cuda") for _ in range(3)]
+    torch.cuda.synchronize()
+    before = torch.cuda.mem_get_info()[0]
+    P.tensile_eval_link(h, dp, out[0], None, out[1], out[2], reuse_host_copies=True)
+    torch.cuda.synchronize()
+    taken = before - torch.cuda.mem_get_info()[0]
+    for g, w in zip(out, (p0, a0, o0)):
+        assert np.array_equal(g.cpu().numpy(), w[which])
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    assert taken <= 1.1 * cus * 4 * (T + tas.N), f"{taken} bytes of scratch"
     h.close()
