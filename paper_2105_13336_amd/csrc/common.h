@@ -149,6 +149,7 @@ struct Tuning {
     int eval_slots = 0;        // size of the persistent grid
     int eval_nt = -1;          // footprint rows written with nontemporal stores: 0 never, 1 always, -1 by row length
     int score_blocks = 0;      // size of the scoring grid
+    int score_wide = -1;       // scoring workgroups of 1024 threads: 0 never, 1 always, -1 by the number of plans
     int link_packed = 1;       // 0: every transfer is searched for in C
     int step_fused = -1;       // tensile_eval_score_plans: 0 = scoring reads the rows, else the evaluation hands it their block maxima
     int alloc_fail = 0;        // n > 0: the n-th allocation of device memory from now on is refused, once (counts down)
@@ -164,7 +165,6 @@ struct JobTables {
 };
 
 // What the scoring kernel shares with the index built at load time (see score.hip).
-constexpr int kScoreWaves = 8;         // wavefronts of the batch kernel's workgroup
 constexpr int kScoreFilterWords = 1024;  // most words of a bucket's filter (32768 bits)
 constexpr int kScoreStage = 128;       // tensors whose output (16 bytes each) one wavefront composes in LDS at a time
 
@@ -173,19 +173,16 @@ constexpr int kScoreStage = 128;       // tensors whose output (16 bytes each) o
 // index = e - e0), in the order of (tensor, p):
 //   cand / cand_size            {tensor, p, q, o} and the tensor's size
 //   cand_gap                    the entry's gap: its number among the gaps of length >= 2 in tensor order
-//   wave_ptr[kScoreWaves]       first entry with tensor >= w * tspan
 //   filter / filter_base        one bit per 2^filter_shift tensors (some entry has one of them), and per word of bits its
 //                               first entry: a tensor's first entry is found from there (see cancel_by_plan)
 struct CandIndex {
     int32_t shift = 0, n_buckets = 0;
-    int32_t tspan = kScoreStage;   // tensors per wavefront: ceil(N / kScoreWaves) rounded up to kScoreStage
     int32_t filter_shift = 0;      // tensors per filter bit, as a power of two
     int32_t filter_words = 0;      // words per bucket: at most kScoreFilterWords
     DevBuf<int32_t> bucket_off;    // [n_buckets + 1]
     DevBuf<int4> cand;
     DevBuf<int32_t> cand_gap;
     DevBuf<int64_t> cand_size;
-    DevBuf<int32_t> wave_ptr;      // [n_buckets][kScoreWaves]
     DevBuf<uint32_t> filter;       // [n_buckets][filter_words]
     DevBuf<int32_t> filter_base;   // [n_buckets][filter_words + 1]
 };

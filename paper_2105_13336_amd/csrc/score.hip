@@ -14,7 +14,7 @@
 // kernel on a second index in which every gap is filed with o = p, and any interval
 // of a tensor cancels its entries.
 //
-// Per plan, one workgroup of 256 or 512 threads (Shape):
+// Per plan, one workgroup of 256, 512 or 1024 threads (Shape):
 //   1. the maxima of the row's blocks of 256 steps (more for rows of over 262,144
 //      steps), streamed from the row or taken from the evaluation; then their prefix and suffix
 //      maxima (two wavefronts), while the plan's own intervals cancel candidates:
@@ -30,8 +30,8 @@
 //      in LDS (zeros and -1, then the entries, which are stored in tensor order) and writes whole pieces of the rows, so
 //      that each output line goes to memory once.  (What step 2 found is not kept but found
 //      again: it costs a few LDS reads per entry and no space.)
-// Nothing is kept per entry but a bit or two, so a workgroup needs a third of a CU's LDS or less, and the phases of
-// several plans overlap on a CU.
+// Nothing is kept per entry but a bit or two, so a workgroup of 256 or 512 threads needs a third of a CU's LDS or less,
+// and the phases of several plans overlap on a CU.
 // What bounds it: HBM (rows in unless the evaluation hands over their maxima, output rows out) on long rows, the
 // chains of dependent loads of a plan's phases on short ones.  Measured against the kernel before it (one workgroup of 1024
 // threads per CU that ran two 64-bit max-scans over every 256 steps of the row and met every candidate's o and q on the way, its
@@ -48,49 +48,60 @@ namespace tensile {
 
 namespace {
 
-// The workgroup and its table of block maxima, by the length of the rows.  Up to 32,768 steps, when the maxima are given: 256
+// The workgroup and its table of block maxima.  In batches of no more plans than CUs, where nothing but a plan's own wavefronts
+// covers the chains of its phases: 1024 threads and 1,024 blocks (of as many pieces of 256 steps as it takes).  Scoring by
+// itself, against 512 threads (rows up to 131,072 steps) or 256 (longer ones): 256 plans of 24,000 steps 32.7 -> 27.0 us, of
+// 50,000 steps 56.8 -> 45.6, 32 of 300,000 steps 161 -> 61, one of 10^6 steps 487 -> 152; evaluation and scoring in one call,
+// against 256 threads, 32 plans of 6,000 steps 25.6 -> 21.3; more pieces ahead than two gain nothing.  Rows of more bytes
+// than the memory-side cache keeps (256 MB) are read past the L2's allocation there: 32 plans of 10^6 steps 236 -> 213 us,
+// 256 of 300,000 202 -> 157; with rows that stay in it that costs (256 of 50,000 steps 45.6 and 53.3, 32 of 300,000 61 and 76).
+// Larger batches, up to 32,768 steps, when the maxima are given: 256
 // threads and 128 blocks, six workgroups per CU, whose chains of short dependent loads cover each other (against 512
 // threads, with evaluation: 4,096 plans of 6,000 steps 161 -> 141 us, 8,192 of 24,000 steps 912 -> 876).  Else, up to 131,072
 // steps: 512 threads, 512 blocks, three per CU (streaming 4,096 rows of 24,000 steps 336 us, with 256 threads 381; 50,000
-// steps 2.62 ms and 2.69).  Longer rows: blocks of as many pieces of 256 steps as fit them into 1,024 blocks, 256
-// threads, four per CU, plans dealt to as many workgroups as are resident (10^6 steps 2.04 ms; with 512 threads 2.17).
-constexpr int kTabSmall = 128, kTabShort = 512, kTabLong = 1024;
-template <int kTab>
+// steps 2.62 ms and 2.69).  Longer rows: 256 threads, 1,024 blocks, four per CU, plans dealt to as many workgroups as are
+// resident (10^6 steps 2.04 ms; with 512 threads 2.17).
+template <int tab, int thr, int eu, bool stream>
 struct Shape {
-    static constexpr int kThr = kTab == kTabShort ? 512 : 256, kWaves = kThr / 64;
-    static constexpr int kSpans = kScoreWaves / kWaves;    // the index holds where each of kScoreWaves ranges of tensors starts
-    static constexpr int kBufs = kWaves / 2;               // wavefronts that read the row's blocks for the open entries
-    static constexpr int kEu = kTab == kTabLong ? 4 : 6;   // wavefronts per SIMD that fit
-    static_assert(kSpans * kWaves == kScoreWaves, "whole ranges per wavefront");
+    static constexpr int kTab = tab, kThr = thr, kWaves = thr / 64;
+    static constexpr int kBufs = kWaves / 2;     // wavefronts that read the row's blocks for the open entries
+    static constexpr int kEu = eu;               // wavefronts per SIMD that fit
+    static constexpr bool kStream = stream;      // rows read and outputs written past the L2's allocation
 };
+typedef Shape<128, 256, 6, false> Small;
+typedef Shape<512, 512, 6, false> Short;
+typedef Shape<1024, 256, 4, true> Long;
+typedef Shape<1024, 1024, 4, false> Wide;
+typedef Shape<1024, 1024, 4, true> WideStream;
+constexpr int64_t kWideStreamBytes = int64_t{192} << 20;
 
 struct StageBuf {
     int64_t score[kStage];
     int32_t win[2][kStage];      // win_out, win_in
 };
 
-template <int kTab>
+template <class S>
 struct ScoreLds {
     union {
-        __attribute__((aligned(16))) StageBuf stage[Shape<kTab>::kWaves];
-        __attribute__((aligned(16))) SpanBuf bufs[Shape<kTab>::kBufs];
+        __attribute__((aligned(16))) StageBuf stage[S::kWaves];
+        __attribute__((aligned(16))) SpanBuf bufs[S::kBufs];
     };
-    BlockMaxima<kTab> mx;
-    OpenList<Shape<kTab>::kThr> open;
+    BlockMaxima<S::kTab> mx;
+    OpenList<S::kThr> open;
     uint64_t cancelled[kWindow / 64];    // one bit per entry of the window
     uint64_t open_bits[kWindow / 64];    // the entry is on the open list, at open_base + its rank within the word
     uint16_t open_base[kWindow / 64];
     uint32_t filter[kFilterWords];
     int32_t filter_base[kFilterWords + 1];
-    uint32_t need[kTab / 32];            // blocks of the row that open entries lie in
+    uint32_t need[S::kTab / 32];         // blocks of the row that open entries lie in
 };
 
 // Step 1: the maxima of the row's blocks into pm[k + 1] and sm[k].  The blocks are dealt round-robin, so that
 // the workgroup reads neighbouring lines at any time, each wavefront kAhead pieces ahead.
-// kStream (rows of more than 131,072 steps): the row is read once, past the L2's allocation.
-template <bool kVec, bool kStream, int kTab>
-__device__ __forceinline__ void stream_block_maxima(const ScoreArgs &a, const int64_t *MF, BlockMaxima<kTab> &mx, int wave, int lane) {
-    constexpr int kAhead = 2, kWaves = Shape<kTab>::kWaves;
+template <bool kVec, class S>
+__device__ __forceinline__ void stream_block_maxima(const ScoreArgs &a, const int64_t *MF, BlockMaxima<S::kTab> &mx, int wave, int lane) {
+    constexpr int kAhead = 2, kWaves = S::kWaves;
+    constexpr bool kStream = S::kStream;
     const int ps = a.piece_shift;
     const int32_t mine = wave < a.n_blk ? (a.n_blk - wave + kWaves - 1) / kWaves : 0;   // blocks of this wavefront
     const int32_t n = mine << ps;
@@ -152,10 +163,10 @@ __device__ __forceinline__ void stream_block_maxima(const ScoreArgs &a, const in
 }
 
 // Step 1 where the maxima of the row's pieces are known (the evaluation wrote them): the row is not read.
-template <int kTab>
-__device__ __forceinline__ void load_block_maxima(const ScoreArgs &a, const int64_t *pieces, BlockMaxima<kTab> &mx, int tid) {
+template <class S>
+__device__ __forceinline__ void load_block_maxima(const ScoreArgs &a, const int64_t *pieces, BlockMaxima<S::kTab> &mx, int tid) {
     const int ps = a.piece_shift;
-    for (int32_t k = tid; k < a.n_blk; k += Shape<kTab>::kThr) {
+    for (int32_t k = tid; k < a.n_blk; k += S::kThr) {
         const int32_t p0 = k << ps, p1 = min(p0 + (1 << ps), a.n_mini);
         int64_t v = pieces[p0];
         for (int32_t p = p0 + 1; p < p1; ++p) v = max64(v, pieces[p]);
@@ -166,10 +177,10 @@ __device__ __forceinline__ void load_block_maxima(const ScoreArgs &a, const int6
 
 // kVec: the footprint rows are 16-byte aligned and T is even.
 // kTable: the maxima of the rows' pieces are given.
-template <int kTab, bool kVec, bool kTable>
-__device__ __forceinline__ void score_plan(const ScoreArgs &a, const int32_t b, ScoreLds<kTab> &L, int32_t &filter_of) {
-    constexpr int kThr = Shape<kTab>::kThr, kSpans = Shape<kTab>::kSpans, kBufs = Shape<kTab>::kBufs;
-    constexpr bool kBig = kTab == kTabLong;
+template <class S, bool kVec, bool kTable>
+__device__ __forceinline__ void score_plan(const ScoreArgs &a, const int32_t b, ScoreLds<S> &L, int32_t &filter_of) {
+    constexpr int kThr = S::kThr, kBufs = S::kBufs;
+    constexpr bool kBig = S::kStream;
     // (the thread index is made opaque once per plan: everything derived from it is then
     // recomputed where it is used instead of being held in registers across the whole loop)
     int tid = threadIdx.x;
@@ -213,8 +224,8 @@ __device__ __forceinline__ void score_plan(const ScoreArgs &a, const int32_t b, 
     for (int32_t k = tid; k < kWindow / 64 && k * 64 < n_e; k += kThr) L.cancelled[k] = 0;
     for (int32_t k = tid; k * 32 < a.n_blk; k += kThr) L.need[k] = 0;
     if (tid == 0) L.open.n = 0;
-    if constexpr (kTable) load_block_maxima(a, a.blk_max + static_cast<int64_t>(b) * a.n_mini, L.mx, tid);
-    else stream_block_maxima<kVec, kBig>(a, MF, L.mx, wave, lane);
+    if constexpr (kTable) load_block_maxima<S>(a, a.blk_max + static_cast<int64_t>(b) * a.n_mini, L.mx, tid);
+    else stream_block_maxima<kVec, S>(a, MF, L.mx, wave, lane);
     PROF_MARK(0);
     __syncthreads();
     PROF_MARK(1);
@@ -290,10 +301,12 @@ __device__ __forceinline__ void score_plan(const ScoreArgs &a, const int32_t b, 
         // N is no multiple of four (the first `shift` tensors are a chunk of their own).
         const bool wide = ((reinterpret_cast<uintptr_t>(a.score) | reinterpret_cast<uintptr_t>(a.win_out) | reinterpret_cast<uintptr_t>(a.win_in)) & 15) == 0;
         const int32_t shift = wide ? static_cast<int32_t>((0u - static_cast<uint32_t>(b) * static_cast<uint32_t>(a.N)) & 3u) : 0;
-        const int32_t t_begin = wave == 0 ? (shift ? shift - kStage : 0) : wave * kSpans * a.tspan + shift;
-        const int32_t t_end = min((wave + 1) * kSpans * a.tspan + shift, a.N);
-        // the wavefront's entries, 64 at a time: those at hand, examined, and the next ones on their way
-        int32_t k = uniform_load(a.wave_ptr, static_cast<int64_t>(bk) * kScoreWaves + wave * kSpans);
+        const int32_t t_begin = wave == 0 ? (shift ? shift - kStage : 0) : wave * a.tspan + shift;
+        const int32_t t_end = min((wave + 1) * a.tspan + shift, a.N);
+        if (t_begin >= t_end) return;                    // (wave-uniform: no tensors for this wavefront)
+        // the wavefront's entries, 64 at a time: those at hand, examined, and the next ones on their way.  They start
+        // with the first entry of the filter word that its first tensor falls into (or some earlier tensor of the word does).
+        int32_t k = __builtin_amdgcn_readfirstlane(L.filter_base[(wave * a.tspan) >> (5 + a.filter_shift)]);
         int4 next;
         int64_t next_size;
         auto request = [&](int32_t at) {
@@ -326,7 +339,7 @@ __device__ __forceinline__ void score_plan(const ScoreArgs &a, const int32_t b, 
             __builtin_amdgcn_wave_barrier();
             for (;;) {                                   // (wave-uniform)
                 const bool take = lane >= pos && tensor < t0 + kStage;
-                if (take && has && tensor >= t0) {       // (one below t0 belongs to the wavefront before)
+                if (take && has && tensor >= t0) {       // (those below t0 belong to the wavefront before)
                     st.score[tensor - t0] = value;
                     st.win[0][tensor - t0] = o;
                     st.win[1][tensor - t0] = q;
@@ -395,12 +408,11 @@ __device__ __forceinline__ void score_plan(const ScoreArgs &a, const int32_t b, 
 }
 
 // Workgroup w takes the plans w, w + grid, ...
-template <int kTab, bool kVec, bool kTable>
-__global__ __launch_bounds__(Shape<kTab>::kThr) __attribute__((amdgpu_waves_per_eu(Shape<kTab>::kEu, Shape<kTab>::kEu))) void score_kernel(
-    const ScoreArgs a) {
-    __shared__ ScoreLds<kTab> lds;
+template <class S, bool kVec, bool kTable>
+__global__ __launch_bounds__(S::kThr) __attribute__((amdgpu_waves_per_eu(S::kEu, S::kEu))) void score_kernel(const ScoreArgs a) {
+    __shared__ ScoreLds<S> lds;
     int32_t filter_of = -1;      // bucket whose filter is in LDS
-    for (int64_t b = blockIdx.x; b < a.B; b += gridDim.x) score_plan<kTab, kVec, kTable>(a, static_cast<int32_t>(b), lds, filter_of);
+    for (int64_t b = blockIdx.x; b < a.B; b += gridDim.x) score_plan<S, kVec, kTable>(a, static_cast<int32_t>(b), lds, filter_of);
 }
 
 // ---- one iteration of the planner on the device --------------------------------------------------------
@@ -436,16 +448,17 @@ struct GreedyStepArgs {
 
 constexpr int kPlanThr = 1024, kPlanWaves = kPlanThr / 64;
 constexpr int kPer = 3, kPlanRun = kPer * kPlanThr;   // entries of the bucket per thread, and per run
-static_assert(kTabLong <= kPlanThr, "one block of the table per thread");
+constexpr int kPlanTab = 1024;
+static_assert(kPlanTab <= kPlanThr, "one block of the table per thread");
 
 struct PlanLds {
     union {
         __attribute__((aligned(16))) SpanBuf bufs[kPlanWaves];
         __attribute__((aligned(16))) ScoreCand stage[kPlanRun];   // records on their way to the host
     };
-    BlockMaxima<kTabLong> mx;
+    BlockMaxima<kPlanTab> mx;
     OpenList<kPlanRun> open;
-    uint32_t need[kTabLong / 32];
+    uint32_t need[kPlanTab / 32];
     int64_t red_v[kPlanWaves];
     int32_t red_t[kPlanWaves];
     int32_t n_stage;
@@ -664,7 +677,7 @@ int launch_greedy_step(const tensile_tas *tas, Workspace &ws, const CandIndex &i
                        int64_t *row, const GreedyTables &tables, bool rebuild, const GreedyNew *fresh, bool do_score,
                        ScoreHeader *hdr, ScoreCand *compact, unsigned long long *ready, unsigned long long ready_value) {
     GreedyStepArgs g{};
-    g.s = make_score_args(tas, ix, any_interval, pl, kTabLong, row, nullptr, nullptr, nullptr, nullptr, nullptr);
+    g.s = make_score_args(tas, ix, any_interval, pl, kPlanTab, row, nullptr, nullptr, nullptr, nullptr, nullptr);
     g.hdr = hdr; g.compact = compact; g.ready = ready; g.ready_value = ready_value;
     g.row = row; g.blk_max = tables.blk_max; g.blk_arg = tables.blk_arg; g.size = tas->d_size.p;
     g.gap_taken = tables.gap_taken; g.tensor_taken = tables.tensor_taken; g.new_gap = -1;
@@ -687,41 +700,42 @@ int launch_score(const tensile_tas *tas, Workspace &ws, const CandIndex &ix, boo
                  const int64_t *resident, const int64_t *peak, const int32_t *argmax, int64_t *score, int32_t *win_out,
                  int32_t *win_in, const int64_t *blk_max) {
     if (plans->B == 0 || tas->N == 0) return TENSILE_OK;
-    const int tab = tas->T <= kTabSmall * kMini && blk_max ? kTabSmall : tas->T <= kTabShort * kMini ? kTabShort : kTabLong;
-    ScoreArgs a = make_score_args(tas, ix, any_interval, plans, tab, resident, peak, argmax, score, win_out, win_in);
-    a.blk_max = blk_max;
-    // One workgroup per plan, so that they start as others end; on long rows as many as the device keeps resident (four per
-    // CU), the plans dealt evenly among them.  (16,384 plans of 50,000 steps: resident workgroups 2.70 ms, one per plan 2.59;
-    // 4,096 of 6,000 steps 167 and 159 us with evaluation; 1,024 of 10^6 steps 2.08 and 2.16 ms.)
+    const bool vec16 = tas->T % 2 == 0 && reinterpret_cast<uintptr_t>(resident) % 16 == 0;
     // (A launch has room for fewer than 2^32 threads: past kMostBlocks a workgroup takes several plans.)
     constexpr int32_t kMostBlocks = 1 << 22;
-    static_assert(int64_t{kMostBlocks} * Shape<kTabShort>::kThr < int64_t{1} << 32, "threads of a launch");
+    static_assert(int64_t{kMostBlocks} * Short::kThr < int64_t{1} << 32, "threads of a launch");
     const int32_t most = plans->B < kMostBlocks ? plans->B : kMostBlocks;
-    int32_t blocks = most;
-    if (tab == kTabLong) {
-        const int64_t resident_blocks = 4 * static_cast<int64_t>(tas->num_cus), rounds = (plans->B + resident_blocks - 1) / resident_blocks;
-        blocks = static_cast<int32_t>((plans->B + rounds - 1) / rounds);
-    }
-    if (const int v = g_tuning.score_blocks; v > 0)   // tuning knob: size of the grid (plans are dealt round-robin)
-        blocks = v < most ? v : most;
-    const bool vec16 = tas->T % 2 == 0 && reinterpret_cast<uintptr_t>(resident) % 16 == 0;
-    auto launch = [&](auto tab_tag) {
-        constexpr int kTab = decltype(tab_tag)::value;
-        const dim3 grid(blocks), block(Shape<kTab>::kThr);
-        if (vec16) {
-            if (blk_max) hipLaunchKernelGGL((score_kernel<kTab, true, true>), grid, block, 0, ws.stream, a);
-            else hipLaunchKernelGGL((score_kernel<kTab, true, false>), grid, block, 0, ws.stream, a);
-        } else {
-            if (blk_max) hipLaunchKernelGGL((score_kernel<kTab, false, true>), grid, block, 0, ws.stream, a);
-            else hipLaunchKernelGGL((score_kernel<kTab, false, false>), grid, block, 0, ws.stream, a);
+    auto launch = [&](auto shape) {
+        typedef decltype(shape) S;
+        ScoreArgs a = make_score_args(tas, ix, any_interval, plans, S::kTab, resident, peak, argmax, score, win_out, win_in);
+        a.blk_max = blk_max;
+        a.tspan = static_cast<int32_t>(((static_cast<int64_t>(tas->N) + S::kWaves - 1) / S::kWaves + kStage - 1) / kStage * kStage);
+        // One workgroup per plan, so that they start as others end; on long rows as many as the device keeps resident (four per
+        // CU), the plans dealt evenly among them.  (16,384 plans of 50,000 steps: resident workgroups 2.70 ms, one per plan 2.59;
+        // 4,096 of 6,000 steps 167 and 159 us with evaluation; 1,024 of 10^6 steps 2.08 and 2.16 ms.)
+        int32_t blocks = most;
+        if constexpr (std::is_same<S, Long>::value) {
+            const int64_t resident_blocks = 4 * static_cast<int64_t>(tas->num_cus), rounds = (plans->B + resident_blocks - 1) / resident_blocks;
+            blocks = static_cast<int32_t>((plans->B + rounds - 1) / rounds);
+        }
+        if (const int v = g_tuning.score_blocks; v > 0)   // tuning knob: size of the grid (plans are dealt round-robin)
+            blocks = v < most ? v : most;
+        const dim3 grid(blocks), block(S::kThr);
+        if (blk_max) {
+            if (vec16) hipLaunchKernelGGL((score_kernel<S, true, true>), grid, block, 0, ws.stream, a);
+            else hipLaunchKernelGGL((score_kernel<S, false, true>), grid, block, 0, ws.stream, a);
+        } else if constexpr (!std::is_same<S, Small>::value) {     // (Small: with the maxima given only)
+            if (vec16) hipLaunchKernelGGL((score_kernel<S, true, false>), grid, block, 0, ws.stream, a);
+            else hipLaunchKernelGGL((score_kernel<S, false, false>), grid, block, 0, ws.stream, a);
         }
     };
-    if (tab == kTabSmall) {      // (with the maxima given only)
-        const dim3 grid(blocks), block(Shape<kTabSmall>::kThr);
-        if (vec16) hipLaunchKernelGGL((score_kernel<kTabSmall, true, true>), grid, block, 0, ws.stream, a);
-        else hipLaunchKernelGGL((score_kernel<kTabSmall, false, true>), grid, block, 0, ws.stream, a);
-    } else if (tab == kTabShort) launch(std::integral_constant<int, kTabShort>{});
-    else launch(std::integral_constant<int, kTabLong>{});
+    const int forced = g_tuning.score_wide;               // tuning knob: 0 / 1 = never / always the large workgroups
+    if (forced >= 0 ? forced == 1 : plans->B <= tas->num_cus) {
+        if (static_cast<int64_t>(plans->B) * tas->T * 8 > kWideStreamBytes) launch(WideStream{});
+        else launch(Wide{});
+    } else if (blk_max && tas->T <= Small::kTab * kMini) launch(Small{});
+    else if (tas->T <= Short::kTab * kMini) launch(Short{});
+    else launch(Long{});
     TS_HIP(hipGetLastError());
     return TENSILE_OK;
 }

@@ -21,7 +21,7 @@ typedef int i4 __attribute__((ext_vector_type(4)));
 
 struct ScoreArgs {
     int32_t T, N, B;
-    int32_t tspan;               // tensors per wavefront of the batch kernel (a multiple of kScoreStage)
+    int32_t tspan;               // (batch kernel) tensors per wavefront, a multiple of kScoreStage
     int32_t n_mini;              // pieces of kMini steps: ceil(T / kMini)
     int32_t piece_shift;         // a block of the LDS tables is 2^piece_shift pieces, so that they hold all of ...
     int32_t n_blk;               // ... the n_blk = ceil(n_mini / 2^piece_shift) blocks
@@ -34,7 +34,6 @@ struct ScoreArgs {
     const int4 *cand;
     const int32_t *cand_gap;
     const int64_t *cand_size;
-    const int32_t *wave_ptr;
     const uint32_t *filter;
     const int32_t *filter_base;
     const int64_t *resident;
@@ -115,8 +114,8 @@ __device__ __forceinline__ int64_t wave_max(int64_t x) {
     return last_lane(wave_scan_max(x));
 }
 
-// A 16-byte piece of an output row.  On long rows (kStream: those of more than 131,072 steps) the store is
-// nontemporal: the lines are not read again by this kernel, and left out of the L2 they leave it to the
+// A 16-byte piece of an output row.  Where the rows are read past the L2's allocation (kStream) the store is
+// nontemporal too: the lines are not read again by this kernel, and left out of the L2 they leave it to the
 // candidate index.
 template <bool kStream, typename V>
 __device__ __forceinline__ void store_out(V *at, const V v) {
@@ -358,7 +357,6 @@ inline ScoreArgs make_score_args(const tensile_tas *tas, const CandIndex &ix, bo
                                  int64_t *score, int32_t *win_out, int32_t *win_in) {
     ScoreArgs a{};
     a.T = tas->T; a.N = tas->N; a.B = plans->B;
-    a.tspan = ix.tspan;
     a.n_mini = static_cast<int32_t>((static_cast<int64_t>(tas->T) + kMini - 1) / kMini);
     a.piece_shift = 0;
     while (((static_cast<int64_t>(a.n_mini) + (1 << a.piece_shift) - 1) >> a.piece_shift) > max_blocks) ++a.piece_shift;
@@ -369,7 +367,7 @@ inline ScoreArgs make_score_args(const tensile_tas *tas, const CandIndex &ix, bo
     a.iv_tensor = plans->iv_tensor; a.iv_out = plans->iv_out; a.iv_in = plans->iv_in;
     a.bucket_shift = ix.shift; a.filter_shift = ix.filter_shift; a.filter_words = ix.filter_words;
     a.bucket_off = ix.bucket_off.p;
-    a.cand = ix.cand.p; a.cand_gap = ix.cand_gap.p; a.cand_size = ix.cand_size.p; a.wave_ptr = ix.wave_ptr.p;
+    a.cand = ix.cand.p; a.cand_gap = ix.cand_gap.p; a.cand_size = ix.cand_size.p;
     a.filter = ix.filter.p; a.filter_base = ix.filter_base.p;
     a.resident = resident; a.peak = peak; a.argmax = argmax;
     a.score = score; a.win_out = win_out; a.win_in = win_in;

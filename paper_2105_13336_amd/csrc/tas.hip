@@ -278,10 +278,9 @@ __global__ __launch_bounds__(kIndexThr) void index_place_kernel(int32_t nb, int3
     if (threadIdx.x == 0) bucket_off[nb] = static_cast<int32_t>(carry);
 }
 
-// Per bucket, from its entries: wave_ptr, filter and filter_base.
-__global__ __launch_bounds__(256) void index_filter_kernel(int32_t filter_shift, int32_t filter_words, int32_t tspan,
-                                                           const int32_t *bucket_off, const int4 *cand, int32_t *wave_ptr,
-                                                           uint32_t *filter, int32_t *filter_base) {
+// Per bucket, from its entries: filter and filter_base.
+__global__ __launch_bounds__(256) void index_filter_kernel(int32_t filter_shift, int32_t filter_words, const int32_t *bucket_off,
+                                                           const int4 *cand, uint32_t *filter, int32_t *filter_base) {
     __shared__ uint32_t bits[kScoreFilterWords];
     const int32_t b = blockIdx.x, e0 = bucket_off[b], n = bucket_off[b + 1] - e0;
     const int4 *c = cand + e0;
@@ -304,8 +303,6 @@ __global__ __launch_bounds__(256) void index_filter_kernel(int32_t filter_shift,
     };
     for (int32_t w = threadIdx.x; w <= filter_words; w += 256)
         filter_base[static_cast<int64_t>(b) * (filter_words + 1) + w] = first_of(static_cast<int64_t>(w) << (5 + filter_shift));
-    if (threadIdx.x < kScoreWaves)
-        wave_ptr[static_cast<int64_t>(b) * kScoreWaves + threadIdx.x] = first_of(static_cast<int64_t>(threadIdx.x) * tspan);
 }
 
 int check_latencies(const char *who, int32_t T, int32_t N, const int64_t *size_bytes, const int64_t *step_ns,
@@ -449,13 +446,11 @@ int build_candidate_index(const tensile_tas *h, CandIndex &ix, const int32_t *d_
     const size_t E = static_cast<size_t>(entries);
     ix.shift = shift;
     ix.n_buckets = nb;
-    ix.tspan = ((h->N + kScoreWaves - 1) / kScoreWaves + kScoreStage - 1) / kScoreStage * kScoreStage;
 
     TS_HIP(ix.bucket_off.reserve(static_cast<size_t>(nb) + 1));
     TS_HIP(ix.cand.reserve(E));
     TS_HIP(ix.cand_gap.reserve(E));
     TS_HIP(ix.cand_size.reserve(E));
-    TS_HIP(ix.wave_ptr.reserve(static_cast<size_t>(nb) * kScoreWaves));
     TS_HIP(ix.filter.reserve(static_cast<size_t>(nb) * ix.filter_words));
     TS_HIP(ix.filter_base.reserve(static_cast<size_t>(nb) * (ix.filter_words + 1)));
     DevBuf<int32_t> place, list, list_off;
@@ -481,8 +476,8 @@ int build_candidate_index(const tensile_tas *h, CandIndex &ix, const int32_t *d_
         a.list_shift = 6;
     }
     file(a, nb, ix.bucket_off.p);
-    hipLaunchKernelGGL(index_filter_kernel, dim3(nb), dim3(256), 0, 0, ix.filter_shift, ix.filter_words, ix.tspan, ix.bucket_off.p,
-                       ix.cand.p, ix.wave_ptr.p, ix.filter.p, ix.filter_base.p);
+    hipLaunchKernelGGL(index_filter_kernel, dim3(nb), dim3(256), 0, 0, ix.filter_shift, ix.filter_words, ix.bucket_off.p,
+                       ix.cand.p, ix.filter.p, ix.filter_base.p);
     TS_HIP(hipGetLastError());
     TS_HIP(hipDeviceSynchronize());     // (callers score on streams of their own)
     return TENSILE_OK;

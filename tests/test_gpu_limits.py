@@ -13,7 +13,7 @@ import paper_2105_13336_amd as P  # noqa: E402
 from oracle import oracle as O  # noqa: E402
 from test_gpu_parity import (check_eval, check_link, check_step, gpu_eval, gpu_score, gpu_score_recompute, gpu_step,  # noqa: E402
                              same_greedy, say, upload)  # noqa: E402
-from workloads import make_plans, plans_from_lists, small_random_tas, tas_from_lists  # noqa: E402
+from workloads import make_plans, plans_from_lists, prng, small_random_tas, tas_from_lists  # noqa: E402
 
 
 @pytest.mark.parametrize("T,B", [(6000, 300), (20011, 600)])
@@ -221,4 +221,33 @@ def test_link_scratch_of_very_long_rows():
         assert np.array_equal(g.cpu().numpy(), w[which])
     cus = torch.cuda.get_device_properties(0).multi_processor_count
     assert taken <= 1.1 * cus * 4 * (T + tas.N), f"{taken} bytes of scratch"
+    h.close()
+
+
+@pytest.mark.parametrize("T,N,B", [(1, 1, 3), (256, 65, 5), (6001, 129, 256), (6001, 2049, 257), (33_334, 4500, 7), (140_001, 40_000, 3),
+                                   (140_002, 70_000, 2), (100_000, 900, 255)])   # (the last: 204 MB of rows)
+def test_scores_by_large_and_small_workgroups(T, N, B, tuning):
+    """Batches of as many plans as CUs take the large workgroups, one more the small ones: both, forced and chosen, over tensors
+    that leave wavefronts without any, that share filter bits (more than 32,768 of them) and rows read past the L2."""
+    i = np.arange(N)
+    alloc = prng.randint(89, 1, i, 0, max(0, 2 * T // 3 - 2))
+    used = np.minimum(T - 1, alloc + 1 + prng.randint(89, 2, i, 0, T // 3))
+    sizes = prng.randint(89, 3, i, 1, 1 << 20)
+    tas = tas_from_lists(T, sizes.tolist(), alloc.tolist(), [[int(u)] if u > x else [] for x, u in zip(alloc, used)], None,
+                         prng.randint(89, 4, np.arange(T), 1, 1000).astype(np.int64), 0, 4_000_000)
+    pl = make_plans(tas, min(B, 7), 13, p_swap=0.4)
+    which = np.arange(B) % pl.B
+    r0, p0, a0, _ = O.eval_plans(tas, pl)
+    want = [O.score_plans(tas, pl, r0, p0, a0), O.score_recompute_plans(tas, pl, r0, p0, a0)]
+    dp = upload(pl.select(which))
+    h = P.tas_load(tas)
+    for wide in (0, 1, -1):
+        say(f"scores T={T} N={N} B={B} wide={wide}")
+        tuning("score_wide", wide)
+        res, peak, arg, mn, *step = gpu_step(h, dp)
+        for g, w in zip((res, peak, arg), (r0, p0, a0)):
+            assert np.array_equal(g[:pl.B].cpu().numpy(), w)
+        for k, got in enumerate((gpu_score(h, dp, res, peak, arg), gpu_score_recompute(h, dp, res, peak, arg), step)):
+            for g, w in zip(got, want[k % 2]):
+                assert bool((g == torch.from_numpy(w).cuda()[which]).all()), f"call {k}, wide={wide}"
     h.close()

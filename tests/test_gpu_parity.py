@@ -815,10 +815,12 @@ def plateau_tas(T, n_big, seed=1):
     return tas_from_lists(T, sizes, allocs, accs, None, np.full(T, 1000, dtype=np.int64), 0, int(sum(big) / len(big) / (half / 2)))
 
 
+@pytest.mark.parametrize("wide", [0, 1])
 @pytest.mark.parametrize("T,n_big", [(4000, 90), (9000, 700), (9001, 1300), (140_000, 60), (262_145, 40), (300_002, 600)])
-def test_score_candidates_that_block_maxima_leave_open(T, n_big):
+def test_score_candidates_that_block_maxima_leave_open(T, n_big, wide, tuning):
     """Every candidate needs the row itself, in blocks all over the plateau: a few of them, more than the list of open
-    entries holds (512), rows with even and odd lengths, blocks of one and of several 256-step pieces."""
+    entries holds (256, 512 or 1024: one per thread), rows with even and odd lengths, blocks of one and of several 256-step pieces."""
+    tuning("score_wide", wide)
     tas = plateau_tas(T, n_big)
     ramp = n_big + 2                                  # plans that swap nothing, a tiny tensor, a large one somewhere
     pl = plans_from_lists([[], [(n_big + 5, ramp + 9, T // 2 + 3)], [(1, T // 2 - 2, T // 2 + 9)], [(n_big // 2, n_big, T // 3)]])
