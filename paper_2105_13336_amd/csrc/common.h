@@ -59,6 +59,8 @@ struct DevBuf {
     }
 };
 
+constexpr int32_t kLinkMostSteps = 1 << 28;   // longest sequence whose link occupancy is evaluated
+
 // Launch geometry of the evaluation kernel (see eval.hip).
 constexpr int kEvalThreads = 1024;
 constexpr int kEvalTile = 8192;   // steps per LDS difference tile
@@ -203,9 +205,9 @@ struct tensile_tas {
     tensile::DevBuf<uint32_t> d_size_units;   // empty when the sizes do not fit (see EvalArgs)
     int32_t size_shift = 0;
     tensile::DevBuf<int32_t> d_touch;
-    tensile::DevBuf<uint4> d_lat_records;     // [T] when timed: latencies of the steps up to each step (see latency_record_kernel)
     tensile::DevBuf<uint8_t> d_lat8, d_x8;    // [T], [N] when timed: see latency_byte_kernel
-    int32_t lat_form = 0;                     // ... how many a record holds: 6 or 4
+    tensile::DevBuf<int32_t> d_time_step;     // when timed: the step at every 2^time_shift ns (see time_step_kernel)
+    int32_t time_shift = 0;
     tensile::CandIndex index;                 // swap candidates: o = earliest feasible swap-out step
     bool times_built = false;                 // C, x, the link's tables and `index` belong together (false after an update that failed)
     // recomputation candidates (every gap, o = p), built by the first tensile_score_recompute

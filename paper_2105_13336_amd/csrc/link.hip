@@ -10,18 +10,17 @@
 // copy reuse (section III-C: the copy in host memory stays until the tensor's last access) only the
 // earliest swap-out of a tensor within a plan transfers anything.
 //
-// Two persistent workgroups of 512 threads per CU walk the plans slot, slot + grid, ...:
-//  * where a transfer that ends with step e begins follows from the latencies of the steps up to e.  Most transfers of the
-//    sequences of training jobs are shorter than the step they end with, and a byte each says so: the transfer time rounded
-//    up and the step's latency rounded down to a common unit.  For the others a record per
-//    step holds the latencies of the six steps e, e - 1, ... (21 bits each; four of 32 bits when some latency takes more): one
-//    16-byte load settles a transfer of up to six steps, longer ones go on with the record six steps
-//    earlier, up to four of them, and then search C.  (Searching C from the top - a table of 7,167 of its values in LDS,
-//    then one packed block of seven - took 13 LDS probes and two more scattered loads per transfer, and its table kept
-//    a second workgroup off the CU.  Records alone left the kernel waiting for L2 lines, one per lane and
-//    load; the two byte tables are small enough for many of those to be shared or found in the L1.)
-//  * the four endpoints of an interval (+1 at s, -1 at o+1, +1 at s', -1 at r) stay in registers, twelve
-//    intervals per thread, taken up four at a time with the next four's loads in flight; a longer plan
+// Two persistent workgroups of 512 threads per CU walk the plans slot, slot + grid, ... (one of 1024 where they are few):
+//  * where a transfer that ends with step e begins: most transfers of the sequences of training jobs are shorter than the
+//    step they end with, and a byte each says so: the transfer time rounded up and the step's latency rounded down to a
+//    common unit.  The others need the last step that starts by the time C[e+1] - x: a table over time (time_step_kernel)
+//    brackets it, and C decides between the few steps in the bracket.  Four loads one after the other, however long the
+//    transfer and however uneven the latencies.  (Records of the last six latencies per step, one load for transfers of up to
+//    six steps and a search through all of C behind them, were as fast on steps of 0.05 to 2 ms and took 20 loads where
+//    transfers span tens of steps: 16,384 plans of 4,800 swaps on 50,000 steps of 0.02 to 0.2 ms 3.57 ms, now 1.69; before
+//    them a table of 7,167 values of C in LDS took 13 probes for every transfer and kept a second workgroup off the CU.)
+//  * the four endpoints of an interval (+1 at s, -1 at o+1, +1 at s', -1 at r) stay in registers, twelve intervals per
+//    thread (six with 1024 threads), taken up two at a time with the next two's list entries on their way; a longer plan
 //    takes several passes of 6144 intervals, each over all tiles,
 //    and the passes add up in the output row (or in a scratch row per workgroup when no rows are
 //    wanted): occupancy is additive over the intervals;
@@ -29,17 +28,18 @@
 //    word (16-bit counters: a pass holds at most 12288 endpoints, so every count and every prefix of
 //    counts fits; the adds are done on the whole word, +-1 or +-65536, and the two halves are taken apart
 //    after the scatter, which is exact because sums are linear modulo 2^32), barrier; every wavefront sums its
-//    eighth of the tile (one add per word), barrier; then it walks its part 256 steps at a time, four steps per
+//    part of the tile (one add per word), barrier; then it walks its part 256 steps at a time, four steps per
 //    lane: clear, take the halves apart, scan (DPP), reduce (max, earliest argmax, steps occupied twice), and store 16
 //    contiguous bytes per lane straight from the registers.  The tile is laid out so that a lane's four steps are
-//    16-byte aligned in the plan's output row, whatever T;
+//    16-byte aligned in the plan's output row, whatever T.  The stores are nontemporal: the rows would push the
+//    tables out of the L2 (4,096 plans on 24,000 steps 180 -> 147 us);
 //  * reuse: the earliest swap-out step per tensor is found in a table in LDS (over the tile, which is
 //    idle at that point), 16,384 tensors at a time, for plans of one pass on sequences of up to 65,536
 //    tensors, else in one row of N entries per workgroup in global memory, L2 atomics.
-// What bounds it: the scattered loads (three per interval) and the store of the rows.  Measured with rows of 50,000 steps, 16,384 plans of 4,800
-// swaps: 2.62 -> 1.54 ms (with records alone 1.87; four or six intervals at a time spill).  13 bytes per interval and 4
-// per step have to move, 0.78 ms at the rate of a plain kernel; the vector units are busy for about as long.  4,096
-// plans on 6,000 steps 314 -> 72 us, 256 plans of 60,000 intervals on 10^6 steps 21.9 -> 3.96 ms.
+// What bounds it: the scattered loads (three per interval at least) and the store of the rows.  Measured with rows of 50,000
+// steps, 16,384 plans of 4,800 swaps, steps of 0.05 to 2 ms: 1.46 ms (three or four intervals at a time spill registers).  13
+// bytes per interval and 4 per step have to move, 0.78 ms at the rate of a plain kernel; the vector units are busy for
+// about as long.  4,096 plans on 6,000 steps 68 us, 256 plans of 60,000 intervals on 10^6 steps 3.9 ms.
 #include <type_traits>
 
 #include "common.h"
@@ -53,7 +53,6 @@ constexpr int kCells = 32768;                        // steps the LDS tile has r
 constexpr int kTile = kCells - 4;                    // ... and holds: up to three cells before its first step are unused
 constexpr int kTileWords = kCells / 2;               // two 16-bit counters per word: 64 KB
 constexpr int kPass = 6144;                          // intervals per pass (at most 2 * kPass endpoints per step: far below 2^15)
-constexpr int kRounds = 4;                           // records a transfer may take before C is searched
 constexpr int64_t kMostScratch = int64_t{4} << 30;   // bytes of scratch that two workgroups per CU may take
 constexpr int kFirstRounds = 4;                      // reuse: at most this many tables of kTileWords tensors, one after the other
 static_assert(2 * kPass < (1 << 15), "16-bit counters");
@@ -69,10 +68,10 @@ struct LinkArgs {
     const uint8_t *iv_kind;        // may be null: every interval is a swap
     const int64_t *C;              // [T+1]
     const int64_t *x;              // [N]
-    const uint4 *records;          // [T], see latency_record_kernel
     const uint8_t *lat8, *x8;      // [T], [N] the latencies rounded down and the transfer times rounded up to a common unit
-    int32_t search_only;           // (testing aid) the records are not used
-    int32_t search_bits;           // probe rounds of a search in C: T < 2^search_bits
+    int32_t search_only;           // (testing aid) the bytes are not used
+    const int32_t *time_step;      // the steps under way at the times k << time_shift
+    int32_t time_shift;
     int32_t *first_out;            // [grid][N], INT32_MAX everywhere between plans (reuse only)
     int32_t *acc_rows;             // [grid][T] scratch rows for plans of several passes when link == null
     int32_t *link;                 // [B*T] or null
@@ -88,30 +87,6 @@ __device__ __forceinline__ int32_t wave_scan_add32(int32_t x) {
     x += __builtin_amdgcn_update_dpp(0, x, 0x142, 0xa, 0xf, true);
     x += __builtin_amdgcn_update_dpp(0, x, 0x143, 0xc, 0xf, true);
     return x;
-}
-
-// How many of the record's steps, taken from the last one backwards, do not add up to x yet (all of them: kForm), and what
-// all of them come to.  x is at most 2^31 - 1 (kForm 6: the six add up to less than 2^24) or 2^32 - 1 (kForm 4: sums
-// that pass it stay there).
-template <int kForm>
-__device__ __forceinline__ int32_t steps_short_of(const uint4 w, const uint32_t x, uint32_t &sum) {
-    int32_t n;
-    if constexpr (kForm == 6) {
-        constexpr uint32_t kM = (1u << 21) - 1;
-        sum = w.x & kM; n = sum < x;
-        sum += ((w.x >> 21) | (w.y << 11)) & kM; n += sum < x;
-        sum += (w.y >> 10) & kM; n += sum < x;
-        sum += ((w.y >> 31) | (w.z << 1)) & kM; n += sum < x;
-        sum += ((w.z >> 20) | (w.w << 12)) & kM; n += sum < x;
-        sum += (w.w >> 9) & kM; n += sum < x;
-    } else {
-        auto add = [](uint32_t p, uint32_t q) { const uint32_t t = p + q; return t < p ? UINT32_MAX : t; };
-        sum = w.x; n = sum < x;
-        sum = add(sum, w.y); n += sum < x;
-        sum = add(sum, w.z); n += sum < x;
-        sum = add(sum, w.w); n += sum < x;
-    }
-    return n;
 }
 
 // Phase timing for tuning, compiled in with -DTENSILE_LINK_PROF only: thread 0 of every workgroup adds the
@@ -130,11 +105,11 @@ __device__ unsigned long long g_link_prof[8];
 #define LINK_MARK(k) do { } while (0)
 #endif
 
-// kForm: latencies per record.  kNear: rows of at most 65,534 steps, whose endpoints are kept in 16 bits each.
+// kNear: rows of at most 65,534 steps, whose endpoints are kept in 16 bits each.
 // kThr: 512, two workgroups per CU, or 1024 and one, mostly for batches of no more plans than CUs, which would leave half of every CU idle
 // (256 plans of 60,000 intervals on 10^6 steps: 33 ms with 512 threads and passes added up step by step; 3.96 with 1024 and
 // passes added up 16 bytes at a time).
-template <int kThr, int kForm, bool kNear>
+template <int kThr, bool kNear>
 __global__ __launch_bounds__(kThr) __attribute__((amdgpu_waves_per_eu(4, 4))) void link_kernel(const LinkArgs a) {
     constexpr int kWaves = kThr / 64, kR = kPass / kThr;   // intervals per thread and pass
     constexpr int kBatch = 2, kBatches = kR / kBatch;      // ... and taken up together
@@ -150,9 +125,6 @@ __global__ __launch_bounds__(kThr) __attribute__((amdgpu_waves_per_eu(4, 4))) vo
     // C[k] through the uniform base and a 32-bit byte offset (the host keeps T below 2^28): no 64-bit
     // address per probe
     auto c_at = [&](uint32_t k) { return *reinterpret_cast<const int64_t *>(reinterpret_cast<const char *>(a.C) + k * 8u); };
-    auto record_at = [&](int32_t e) {
-        return *reinterpret_cast<const uint4 *>(reinterpret_cast<const char *>(a.records) + static_cast<uint32_t>(e) * 16u);
-    };
     int32_t *first_out = (a.reuse && a.first_out) ? a.first_out + static_cast<int64_t>(blockIdx.x) * a.N : nullptr;
 
 #ifdef TENSILE_LINK_PROF
@@ -273,7 +245,7 @@ __global__ __launch_bounds__(kThr) __attribute__((amdgpu_waves_per_eu(4, 4))) vo
                     iv_o[j] = ok[j] ? in_o[j] : 0;
                     iv_r[j] = ok[j] ? in_r[j] : 1;
                 }
-                // the transfer's end, then how far back it has been followed
+                // the step the transfer ends with, then the one it starts with
                 int32_t at[kBatch][2];
                 uint32_t x8[kBatch], l8[kBatch][2];
 #pragma unroll
@@ -293,76 +265,62 @@ __global__ __launch_bounds__(kThr) __attribute__((amdgpu_waves_per_eu(4, 4))) vo
                 }
                 if (b + 1 < kBatches && static_cast<uint32_t>(b + 1) * (kBatch * kThr) < len) request(b + 1);
                 LINK_MARK(1);
-                // a transfer no longer than the step it ends with starts there; what remains of the others (0: found)
-                int64_t rest[kBatch][2];
-                bool open = false;
+                // a transfer no longer than the step it ends with starts there
+                bool open[kBatch][2], any_open = false;
 #pragma unroll
                 for (int j = 0; j < kBatch; ++j) {
-                    const bool longer[2] = {ok[j] && (x8[j] > l8[j][0] || a.search_only), ok[j] && (x8[j] > l8[j][1] || a.search_only)};
-                    const int64_t x = longer[0] || longer[1] ? a.x[iv_i[j]] : 0;
-                    rest[j][0] = longer[0] ? x : 0;
-                    rest[j][1] = longer[1] ? x : 0;
-                    open = open || longer[0] || longer[1];
-                }
-                uint4 rec[kBatch][2];
-                auto follow = [&](int j, int q) {        // one record
-                    constexpr int64_t kMost = kForm == 6 ? INT32_MAX : UINT32_MAX;
-                    if (kForm == 4 && rest[j][q] > kMost) return;     // (sums stop at kMost there: left to the search)
-                    uint32_t sum;
-                    const int32_t n = steps_short_of<kForm>(rec[j][q], static_cast<uint32_t>(rest[j][q] < kMost ? rest[j][q] : kMost), sum);
-                    at[j][q] -= n;
-                    rest[j][q] = n < kForm ? 0 : rest[j][q] - sum;
-                    if (at[j][q] < 0) {                  // the past is too short: from step 0
-                        at[j][q] = 0;
-                        rest[j][q] = 0;
-                    }
-                };
-                for (int round = 0; round < kRounds && __builtin_amdgcn_ballot_w64(open) != 0 && !a.search_only; ++round) {
 #pragma unroll
-                    for (int j = 0; j < kBatch; ++j) {
-#pragma unroll
-                        for (int q = 0; q < 2; ++q)
-                            if (rest[j][q] > 0) rec[j][q] = record_at(at[j][q]);
-                    }
-                    open = false;
-#pragma unroll
-                    for (int j = 0; j < kBatch; ++j) {
-#pragma unroll
-                        for (int q = 0; q < 2; ++q) {
-                            if (rest[j][q] > 0) follow(j, q);
-                            open = open || rest[j][q] > 0;
-                        }
+                    for (int q = 0; q < 2; ++q) {
+                        open[j][q] = ok[j] && (x8[j] > l8[j][q] || a.search_only);
+                        any_open = any_open || open[j][q];
                     }
                 }
-                if (__builtin_amdgcn_ballot_w64(open) != 0) {
-                    // the last step s <= at with C[s] <= C[at + 1] - rest (step 0 when there is none), by decreasing powers of two, the
-                    // wavefront's searches in lockstep
+                if (__builtin_amdgcn_ballot_w64(any_open) != 0) {
+                    // the others with the last step s with C[s] <= v = C[end + 1] - x (step 0 when there is none): one of those
+                    // under way between the times before and after v in the table, the wavefront's searches in lockstep
                     int64_t v[kBatch][2];
-                    uint32_t pos[kBatch][2];
+                    int32_t lo[kBatch][2], hi[kBatch][2];
+#pragma unroll
+                    for (int j = 0; j < kBatch; ++j) {
+                        const int64_t x = open[j][0] || open[j][1] ? a.x[iv_i[j]] : 0;
+#pragma unroll
+                        for (int q = 0; q < 2; ++q) v[j][q] = (open[j][q] ? c_at(static_cast<uint32_t>(at[j][q]) + 1) : 0) - x;
+                    }
 #pragma unroll
                     for (int j = 0; j < kBatch; ++j) {
 #pragma unroll
                         for (int q = 0; q < 2; ++q) {
-                            v[j][q] = c_at(static_cast<uint32_t>(at[j][q]) + 1) - rest[j][q];
-                            pos[j][q] = 0;
+                            const int64_t k = v[j][q] > 0 ? v[j][q] >> a.time_shift : 0;
+                            lo[j][q] = hi[j][q] = 0;
+                            if (open[j][q]) {
+                                lo[j][q] = a.time_step[k];
+                                hi[j][q] = a.time_step[k + 1];
+                            }
                         }
                     }
-                    for (int bit = a.search_bits - 1; bit >= 0; --bit) {   // (uniform)
+                    for (;;) {
+                        bool unsure = false;
+#pragma unroll
+                        for (int j = 0; j < kBatch; ++j) unsure = unsure || lo[j][0] < hi[j][0] || lo[j][1] < hi[j][1];
+                        if (__builtin_amdgcn_ballot_w64(unsure) == 0) break;
+                        int32_t mid[kBatch][2];
                         int64_t c[kBatch][2];
 #pragma unroll
                         for (int j = 0; j < kBatch; ++j) {
 #pragma unroll
                             for (int q = 0; q < 2; ++q) {
-                                const uint32_t p = pos[j][q] + (1u << bit);
-                                c[j][q] = c_at(p <= static_cast<uint32_t>(a.T) ? p : static_cast<uint32_t>(a.T));
+                                mid[j][q] = lo[j][q] + ((hi[j][q] - lo[j][q] + 1) >> 1);
+                                c[j][q] = lo[j][q] < hi[j][q] ? c_at(static_cast<uint32_t>(mid[j][q])) : 0;
                             }
                         }
 #pragma unroll
                         for (int j = 0; j < kBatch; ++j) {
 #pragma unroll
                             for (int q = 0; q < 2; ++q) {
-                                const uint32_t p = pos[j][q] + (1u << bit);
-                                if (p <= static_cast<uint32_t>(a.T) && c[j][q] <= v[j][q]) pos[j][q] = p;
+                                if (lo[j][q] < hi[j][q]) {
+                                    if (c[j][q] <= v[j][q]) lo[j][q] = mid[j][q];
+                                    else hi[j][q] = mid[j][q] - 1;
+                                }
                             }
                         }
                     }
@@ -370,7 +328,7 @@ __global__ __launch_bounds__(kThr) __attribute__((amdgpu_waves_per_eu(4, 4))) vo
                     for (int j = 0; j < kBatch; ++j) {
 #pragma unroll
                         for (int q = 0; q < 2; ++q)
-                            if (rest[j][q] > 0) at[j][q] = static_cast<int32_t>(pos[j][q]);
+                            if (open[j][q]) at[j][q] = lo[j][q];
                     }
                 }
 #pragma unroll
@@ -482,7 +440,7 @@ __global__ __launch_bounds__(kThr) __attribute__((amdgpu_waves_per_eu(4, 4))) vo
                         }
 #pragma unroll
                         for (int j = 0; j < 4; ++j) over += __builtin_popcountll(__builtin_amdgcn_ballot_w64(v[j] >= 2));
-                        if (row) *reinterpret_cast<i32x4 *>(row + t0) = i32x4{v[0], v[1], v[2], v[3]};
+                        if (row) __builtin_nontemporal_store(i32x4{v[0], v[1], v[2], v[3]}, reinterpret_cast<i32x4 *>(row + t0));
                         continue;
                     }
                     bool in[4];
@@ -575,7 +533,7 @@ int launch_link(const tensile_tas *tas, Workspace &ws, const tensile_plans *plan
     const hipStream_t stream = ws.stream;
     const int32_t B = plans->B, T = tas->T;
     if (B == 0) return TENSILE_OK;
-    if (T > (1 << 28)) { set_error("eval_link: T = %d exceeds 2^28 steps", T); return TENSILE_E_RANGE; }
+    if (T > kLinkMostSteps) { set_error("eval_link: T = %d exceeds 2^28 steps", T); return TENSILE_E_RANGE; }
     if (!tas->timed || tas->N == 0) {
         const int64_t n_rows = link ? static_cast<int64_t>(B) * T : 0;
         hipLaunchKernelGGL(link_zero_kernel, dim3(tas->num_cus * 4), dim3(256), 0, stream, n_rows, link, B, peak, argmax, overbooked);
@@ -588,9 +546,9 @@ int launch_link(const tensile_tas *tas, Workspace &ws, const tensile_plans *plan
     a.plan_offsets = plans->plan_offsets;
     a.iv_tensor = plans->iv_tensor; a.iv_out = plans->iv_out; a.iv_in = plans->iv_in; a.iv_kind = plans->iv_kind;
     a.C = tas->d_C.p; a.x = tas->d_x.p;
-    a.records = tas->d_lat_records.p; a.lat8 = tas->d_lat8.p; a.x8 = tas->d_x8.p;
+    a.lat8 = tas->d_lat8.p; a.x8 = tas->d_x8.p;
     a.search_only = g_tuning.link_packed == 0 ? 1 : 0;   // (testing aid)
-    while ((int64_t{1} << a.search_bits) <= T) ++a.search_bits;
+    a.time_step = tas->d_time_step.p; a.time_shift = tas->time_shift;
     // scratch per workgroup: the table of plans that the kernel cannot serve from LDS (see reuse_lds there), and the row where
     // the passes of a long plan add up
     const bool needs_first = reuse && (tas->N > kFirstRounds * kTileWords || plans->n_intervals > kPass);
@@ -621,19 +579,13 @@ int launch_link(const tensile_tas *tas, Workspace &ws, const tensile_plans *plan
     }
     a.link = link; a.peak = peak; a.argmax = argmax; a.overbooked = overbooked;
     const bool near = T <= 65534;
-    auto launch = [&](auto thr, auto form) {
-        constexpr int kThr = decltype(thr)::value, kForm = decltype(form)::value;
-        if (near) hipLaunchKernelGGL((link_kernel<kThr, kForm, true>), dim3(grid), dim3(kThr), 0, stream, a);
-        else hipLaunchKernelGGL((link_kernel<kThr, kForm, false>), dim3(grid), dim3(kThr), 0, stream, a);
+    auto launch = [&](auto thr) {
+        constexpr int kThr = decltype(thr)::value;
+        if (near) hipLaunchKernelGGL((link_kernel<kThr, true>), dim3(grid), dim3(kThr), 0, stream, a);
+        else hipLaunchKernelGGL((link_kernel<kThr, false>), dim3(grid), dim3(kThr), 0, stream, a);
     };
-    const std::integral_constant<int, 6> six{};
-    const std::integral_constant<int, 4> four{};
-    const std::integral_constant<int, 512> half{};
-    const std::integral_constant<int, 1024> whole{};
-    if (wide && tas->lat_form == 6) launch(whole, six);
-    else if (wide) launch(whole, four);
-    else if (tas->lat_form == 6) launch(half, six);
-    else launch(half, four);
+    if (wide) launch(std::integral_constant<int, 1024>{});
+    else launch(std::integral_constant<int, 512>{});
     TS_HIP(hipGetLastError());
     return TENSILE_OK;
 }

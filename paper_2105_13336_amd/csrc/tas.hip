@@ -103,26 +103,11 @@ __global__ void gap_window_kernel(int32_t G, int32_t T, const int32_t *gp, const
     gwin[g] = o;
 }
 
-// For the link kernel: one record per step e with the latencies of the steps e, e - 1, ...: six of 21 bits when every
-// latency is shorter than 2^21 ns, else four of 32 bits, where a longer one counts as 2^32 - 1.  0 before step 0.
-__global__ void latency_record_kernel(int32_t T, const int64_t *step_ns, int32_t form, uint4 *records) {
-    const int32_t e = blockIdx.x * blockDim.x + threadIdx.x;
-    if (e >= T) return;
-    auto at = [&](int32_t back) -> uint64_t { return e - back >= 0 ? static_cast<uint64_t>(step_ns[e - back]) : 0; };
-    if (form == 6) {
-        unsigned __int128 bits = 0;
-#pragma unroll
-        for (int j = 0; j < 6; ++j) bits |= static_cast<unsigned __int128>(at(j)) << (21 * j);
-        records[e] = make_uint4(static_cast<uint32_t>(bits), static_cast<uint32_t>(bits >> 32), static_cast<uint32_t>(bits >> 64),
-                                static_cast<uint32_t>(bits >> 96));
-    } else {
-        auto cut = [](uint64_t v) { return v < UINT32_MAX ? static_cast<uint32_t>(v) : UINT32_MAX; };
-        records[e] = make_uint4(cut(at(0)), cut(at(1)), cut(at(2)), cut(at(3)));
-    }
-}
-
 // For the link kernel: x8 <= lat8 only if the transfer is no longer than the step.  lat8 = the latency in units of 2^shift ns,
-// rounded down, at most 254; x8 = the transfer time rounded up, at most 255.
+// rounded down, at most 254; x8 = the transfer time rounded up, at most 255.  The unit is about a hundredth of the geometric mean
+// of the latencies.  What lies far above that is capped, which costs a search and no more; a unit taken from the longest latency made
+// zeros of all others in a sequence with one very slow step (4,096 plans on 50,000 steps of 20 to 200 us: 921 us, with
+// one step of 50 ms among them 1,056; with this unit there is no difference).
 __global__ void latency_byte_kernel(int32_t T, const int64_t *step_ns, int32_t N, const int64_t *x, int32_t shift, uint8_t *lat8, uint8_t *x8) {
     const int32_t k = blockIdx.x * blockDim.x + threadIdx.x;
     if (k < T) {
@@ -133,6 +118,23 @@ __global__ void latency_byte_kernel(int32_t T, const int64_t *step_ns, int32_t N
         const int64_t v = x[k] > 0 ? ((x[k] - 1) >> shift) + 1 : 0;
         x8[k] = static_cast<uint8_t>(v < 255 ? v : 255);
     }
+}
+
+// For the link kernel: which step is under way at the times 0, 2^shift, 2 * 2^shift, ...: the last s with C[s] <= k << shift.  The
+// last step that starts by some time v is then one of those between two neighbouring entries: with two to four entries per
+// step on average, mostly one or two looks at C.  (Two entries or one per step are 1 and 3 % slower; 4 to 8 bytes per step less.)
+constexpr int64_t kTimesPerStep = 4;
+__global__ void time_step_kernel(int32_t n, int32_t T, const int64_t *C, int32_t shift, int32_t *step) {
+    const int32_t k = blockIdx.x * blockDim.x + threadIdx.x;
+    if (k >= n) return;
+    const int64_t at = static_cast<int64_t>(k) << shift;
+    int32_t lo = 0, hi = T;
+    while (lo < hi) {
+        const int32_t mid = lo + ((hi - lo + 1) >> 1);
+        if (C[mid] <= at) lo = mid;
+        else hi = mid - 1;
+    }
+    step[k] = lo;
 }
 
 // d[t] = MF0[t] - MF0[t-1], d[0] = MF0[0]
@@ -581,17 +583,21 @@ int build_times_and_index(tensile_tas *h, const int64_t *step_ns) {
         if (N > 0)
             hipLaunchKernelGGL(transfer_time_kernel, dim3((N + 255) / 256), dim3(256), 0, 0, N, h->d_size.p,
                                h->link_bytes_per_us, h->d_x.p);
-        h->lat_form = 0;
-        if (h->timed) {
-            const int64_t longest = *std::max_element(step_ns, step_ns + T);
-            int32_t shift = 0;
-            while ((longest >> shift) > 254) ++shift;
-            h->lat_form = longest < (int64_t{1} << 21) ? 6 : 4;
-            TS_HIP(h->d_lat_records.reserve(T));
+        if (h->timed && T <= kLinkMostSteps) {      // (longer sequences have no link occupancy)
+            int64_t total = 0, logs = 0;
+            for (int32_t t = 0; t < T; ++t) {
+                total += step_ns[t];
+                logs += 63 - __builtin_clzll(static_cast<unsigned long long>(step_ns[t]));
+            }
+            const int32_t unit_shift = static_cast<int32_t>(std::max<int64_t>(logs / T - 6, 0));
+            h->time_shift = 0;
+            while ((total >> h->time_shift) > kTimesPerStep * static_cast<int64_t>(T)) ++h->time_shift;
+            const int32_t n_times = static_cast<int32_t>(total >> h->time_shift) + 2;
+            TS_HIP(h->d_time_step.reserve(n_times));
             TS_HIP(h->d_lat8.reserve(T));
             TS_HIP(h->d_x8.reserve(N));
-            hipLaunchKernelGGL(latency_record_kernel, dim3((T + 255) / 256), dim3(256), 0, 0, T, step.p, h->lat_form, h->d_lat_records.p);
-            hipLaunchKernelGGL(latency_byte_kernel, dim3((std::max(T, N) + 255) / 256), dim3(256), 0, 0, T, step.p, N, h->d_x.p, shift,
+            hipLaunchKernelGGL(time_step_kernel, dim3((n_times + 255) / 256), dim3(256), 0, 0, n_times, T, h->d_C.p, h->time_shift, h->d_time_step.p);
+            hipLaunchKernelGGL(latency_byte_kernel, dim3((std::max(T, N) + 255) / 256), dim3(256), 0, 0, T, step.p, N, h->d_x.p, unit_shift,
                                h->d_lat8.p, h->d_x8.p);
         }
         DevBuf<int32_t> d_gwin;

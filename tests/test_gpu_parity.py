@@ -472,8 +472,8 @@ def test_link_occupancy_shapes(T, B, reuse):
 @pytest.mark.parametrize("T,B,packed", [(32767, 3, 1), (32768, 3, 1), (32769, 4, 1), (50168, 3, 1), (50169, 3, 1), (65537, 3, 1),
                                          (120001, 2, 1), (32769, 3, 0), (120001, 2, 0)])
 def test_link_occupancy_long_rows(T, B, packed, tuning):
-    """Edges of the 32768-step tile, rows whose table of C covers every block of seven steps (up to 50,168
-    steps) and rows where it skips blocks, with the packed differences of C and with the probe search."""
+    """Edges of the 32,764-step tile and of the 16-bit endpoints, several tiles; with the bytes that settle short transfers
+    (packed) and with every transfer searched for."""
     tuning("link_packed", packed)
     tas = small_random_tas(4300 + T, N=200, T=T, max_acc=6, timed=True)
     pl = merged_plans(tas, B, 31, p_swap=0.8)
@@ -481,9 +481,9 @@ def test_link_occupancy_long_rows(T, B, packed, tuning):
     check_link(tas, pl, bool(T & 1), label=f"link T={T} packed={packed}")
 
 
-def test_link_occupancy_with_latencies_too_long_to_pack():
-    """Operator latencies of 2^21 ns and more cannot be packed: the probe search runs, also after an update
-    of the latencies of a loaded sequence switched the handle from one form to the other."""
+def test_link_occupancy_after_updates_of_the_latencies():
+    """The tables of the link follow the latencies of a loaded sequence: thousands of times slower, back, and with single
+    steps far above the others."""
     tas = small_random_tas(4400, N=120, T=9001, max_acc=5, timed=True)
     pl = merged_plans(tas, 5, 41, p_swap=0.7)
     h = P.tas_load(tas)
@@ -499,8 +499,7 @@ def test_link_occupancy_with_latencies_too_long_to_pack():
     tas.step_ns, tas.link_bytes_per_us = fast, 50_000
     say("link: latencies updated back")
     check_link(tas, pl, False, h=h, label="link short latencies again")
-    # exactly at the limit of the packed form: 2^21 - 1 fits, 2^21 does not
-    for top in ((1 << 21) - 1, 1 << 21):
+    for top in ((1 << 21) - 1, 1 << 40):
         edge = fast.copy()
         edge[::97] = top
         P.tensile_tas_update_latencies(h, edge, 50_000)
@@ -514,7 +513,7 @@ def test_link_occupancy_with_latencies_too_long_to_pack():
 @pytest.mark.parametrize("longest", [2_000, (1 << 21) - 1, 1 << 21, 1 << 33])
 def test_link_occupancy_transfers_of_every_length(T, B, N, reuse, longest):
     """Tile edges, endpoints in 16 and in 32 bits, tables of the earliest swap-out in one and in several rounds, small and
-    large batches; step latencies (few of the longest) that fit six or four to a record or pass 32 bits, with
+    large batches; step latencies of which few are far longer than the others, up to past 32 bits, with
     transfers from less than a step to hundreds of them and of more than 2^32 ns."""
     tas = small_random_tas(8800 + T % 97, N=min(N, 3000), T=T, max_acc=4, timed=True)
     reps = -(-N // tas.N)
@@ -529,6 +528,37 @@ def test_link_occupancy_transfers_of_every_length(T, B, N, reuse, longest):
         pl = pl.select(np.arange(B) % 7)
     say(f"link transfers T={T} B={B} N={N} reuse={reuse} longest={longest}")
     check_link(tas, pl, reuse, label=f"T={T} N={N} longest={longest}")
+
+
+@pytest.mark.parametrize("packed", [0, 1])
+@pytest.mark.parametrize("T,kind", [(1, "ones"), (2, "ones"), (9, "ones"), (5000, "ones"), (5000, "powers"), (5003, "first"), (5003, "middle"),
+                                    (5003, "last"), (70_001, "tail"), (70_001, "slow half")])
+def test_link_transfers_on_uneven_latencies(T, kind, packed, tuning):
+    """Transfers found through the table over time: transfer times that are exactly some steps' sum, more than the whole past,
+    and spans from one step to all of them, where an entry of the table covers one step, none or thousands."""
+    tuning("link_packed", packed)
+    t = np.arange(T)
+    ns = np.ones(T, dtype=np.int64)
+    if kind == "powers":
+        ns = 1 << prng.randint(97, 1, t, 0, 30)
+    elif kind in ("first", "middle", "last"):
+        ns = prng.randint(97, 2, t, 1, 50)
+        ns[{"first": 0, "middle": T // 2, "last": T - 1}[kind]] = 10 ** 12
+    elif kind == "tail":
+        ns = np.rint(np.exp(np.log(3e5) + 2.5 * np.sin(1.0 + t * 12.9898) ** 3)).astype(np.int64)
+    elif kind == "slow half":
+        ns = np.where(t < T // 2, 1 + t % 3, 10 ** 9 + t)
+    ns = np.ascontiguousarray(ns, dtype=np.int64)
+    base = small_random_tas(9700 + T, N=max(1, min(250, T // 2)), T=T, max_acc=4 if T > 8 else 1, timed=True)
+    total = int(ns.sum())
+    # transfer times (1000 bytes per us: one byte per ns) from one ns to more than the sequence takes
+    sizes = np.maximum(1, np.rint(np.exp(prng.randint(97, 3, np.arange(base.N), 0, 1000) / 1000.0 * np.log(2.0 * total + 2)))).astype(np.int64)
+    sizes[::5] = ns[prng.randint(97, 4, np.arange(len(sizes[::5])), 0, T - 1)]
+    tas = tas_from_lists(T, sizes.tolist(), base.alloc_step.tolist(), [[int(x) for x in base.touch_points(i)[1:]] for i in range(base.N)],
+                         None, ns, 0, 1000)
+    pl = merged_plans(tas, 300 if T == 9 else 4, 3) if T > 2 else plans_from_lists([[(0, 0, 1)], [(0, 0, T)], []])
+    say(f"link uneven latencies T={T} {kind} packed={packed} K={pl.n_intervals}")
+    check_link(tas, pl, bool(T & 1), label=f"{kind} T={T}")
 
 
 def test_link_occupancy_long_plans_take_several_passes():
