@@ -52,7 +52,9 @@ namespace {
 // covers the chains of its phases: 1024 threads and 1,024 blocks (of as many pieces of 256 steps as it takes).  Scoring by
 // itself, against 512 threads (rows up to 131,072 steps) or 256 (longer ones): 256 plans of 24,000 steps 32.7 -> 27.0 us, of
 // 50,000 steps 56.8 -> 45.6, 32 of 300,000 steps 161 -> 61, one of 10^6 steps 487 -> 152; evaluation and scoring in one call,
-// against 256 threads, 32 plans of 6,000 steps 25.6 -> 21.3; more pieces ahead than two gain nothing.  Rows of more bytes
+// against 256 threads, 32 plans of 6,000 steps 25.6 -> 21.3; more pieces ahead than two gain nothing.  Not where four wavefronts
+// have a piece of work each and more would idle (60 tensors, 200 steps: 64 plans 15.9 us with 1024 threads, 15.7 with 256; 534 tensors,
+// 1,000 steps: 18.9 and 19.1).  Rows of more bytes
 // than the memory-side cache keeps (256 MB) are read past the L2's allocation there: 32 plans of 10^6 steps 236 -> 213 us,
 // 256 of 300,000 202 -> 157; with rows that stay in it that costs (256 of 50,000 steps 45.6 and 53.3, 32 of 300,000 61 and 76).
 // Larger batches, up to 32,768 steps, when the maxima are given: 256
@@ -730,7 +732,8 @@ int launch_score(const tensile_tas *tas, Workspace &ws, const CandIndex &ix, boo
         }
     };
     const int forced = g_tuning.score_wide;               // tuning knob: 0 / 1 = never / always the large workgroups
-    if (forced >= 0 ? forced == 1 : plans->B <= tas->num_cus) {
+    const bool little = tas->N <= Small::kWaves * kStage && tas->T <= 4 * Small::kWaves * kMini;
+    if (forced >= 0 ? forced == 1 : plans->B <= tas->num_cus && !little) {
         if (static_cast<int64_t>(plans->B) * tas->T * 8 > kWideStreamBytes) launch(WideStream{});
         else launch(Wide{});
     } else if (blk_max && tas->T <= Small::kTab * kMini) launch(Small{});

@@ -224,11 +224,11 @@ def test_link_scratch_of_very_long_rows():
     h.close()
 
 
-@pytest.mark.parametrize("T,N,B", [(1, 1, 3), (256, 65, 5), (6001, 129, 256), (6001, 2049, 257), (33_334, 4500, 7), (140_001, 40_000, 3),
+@pytest.mark.parametrize("T,N,B", [(1, 1, 3), (256, 65, 5), (4096, 512, 4), (4097, 512, 4), (4096, 513, 4), (6001, 129, 256), (6001, 2049, 257), (33_334, 4500, 7), (140_001, 40_000, 3),
                                    (140_002, 70_000, 2), (100_000, 900, 255)])   # (the last: 204 MB of rows)
 def test_scores_by_large_and_small_workgroups(T, N, B, tuning):
-    """Batches of as many plans as CUs take the large workgroups, one more the small ones: both, forced and chosen, over tensors
-    that leave wavefronts without any, that share filter bits (more than 32,768 of them) and rows read past the L2."""
+    """Batches of as many plans as CUs take the large workgroups, one more or little work per plan the small ones: both, forced and
+    chosen, over tensors that leave wavefronts without any, that share filter bits (more than 32,768 of them) and rows read past the L2."""
     i = np.arange(N)
     alloc = prng.randint(89, 1, i, 0, max(0, 2 * T // 3 - 2))
     used = np.minimum(T - 1, alloc + 1 + prng.randint(89, 2, i, 0, T // 3))
