@@ -61,9 +61,7 @@ struct DevBuf {
 
 constexpr int32_t kLinkMostSteps = 1 << 28;   // longest sequence whose link occupancy is evaluated
 
-// Launch geometry of the evaluation kernel (see eval.hip).
-constexpr int kEvalThreads = 1024;
-constexpr int kEvalTile = 8192;   // steps per LDS difference tile
+constexpr int kEvalTile = 8192;   // steps per LDS difference tile of the evaluation kernel's largest geometry (see eval.hip)
 constexpr int kScoreMini = 256;   // steps of a piece of the row in the scoring passes: 4 consecutive steps per lane
 
 // Arguments of the fused scatter + scan + reduce kernel.

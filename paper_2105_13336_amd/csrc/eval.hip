@@ -877,8 +877,8 @@ int launch_geometry(const tensile_tas *tas, Workspace &ws, const EvalArgs &a, in
         constexpr int R = decltype(r_tag)::value;
         with_mode<false>(out, a.blk_max != nullptr, [&](auto mode) {
             constexpr int kOut = decltype(mode)::value;
-            if constexpr (R * kThr <= kCapBig) {
-                if (persistent) {
+            if constexpr (R * kThr <= (kThr == 512 ? kCapSmall : kCapBig)) {
+                if (persistent) {   // (with 512 threads only the smallest register capacity leaves room for the next plan's intervals)
                     if (narrow) hipLaunchKernelGGL((eval_stream_kernel<kThr, R, true, kOut>), grid, block, 0, stream, a);
                     else hipLaunchKernelGGL((eval_stream_kernel<kThr, R, false, kOut>), grid, block, 0, stream, a);
                     return;
@@ -889,8 +889,7 @@ int launch_geometry(const tensile_tas *tas, Workspace &ws, const EvalArgs &a, in
         });
     };
     bool launched = false;
-    // (with 512 threads only the smallest register capacity leaves room for the next plan's intervals)
-    if (kThr == 512 && cap != kCapSmall) persistent = false;
+    if (kThr == 512 && cap != kCapSmall) persistent = false;   // (see eval_with)
     if (persistent) {   // one workgroup per resident slot, the plans dealt evenly among them
         int64_t slots = static_cast<int64_t>(tas->num_cus) * (1024 / kThr);
         if (g_tuning.eval_slots > 0) slots = g_tuning.eval_slots;
