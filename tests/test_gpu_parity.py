@@ -861,10 +861,10 @@ def test_score_candidates_that_block_maxima_leave_open(T, n_big, wide, tuning):
         assert check_score_recompute(tas, pl, label=f"open T={T}") > 2 * n_big
 
 
-@pytest.mark.parametrize("N,acc", [(16384, 1), (16385, 1), (20000, 1), (300, 60)])
+@pytest.mark.parametrize("N,acc", [(8191, 1), (8192, 1), (8193, 1), (16384, 1), (16385, 1), (20000, 1), (300, 60)])
 def test_score_buckets_of_many_entries(N, acc):
-    """Buckets with as many entries as there are flags for, one more, two windows of them; tensors with many gaps in one
-    bucket (an interval then cancels an entry behind its tensor's first)."""
+    """Buckets with one entry less than there are flags for (8192), as many, one more, two windows of them and one more, three;
+    tensors with many gaps in one bucket (an interval then cancels an entry behind its tensor's first)."""
     T = 700
     i = np.arange(N)
     alloc = prng.randint(79, 1, i, 0, 249)
@@ -950,46 +950,70 @@ def check_step(tas, pl, h=None, label=""):
     return int((o0 >= 0).sum())
 
 
-@pytest.mark.parametrize("fused", [1, 0, -1])
+@pytest.mark.parametrize("wide", [0, 1])
+@pytest.mark.parametrize("handover", [0, -1])
 @pytest.mark.parametrize("T,B,timed", [(8, 3, False), (4096, 5, True), (8192, 300, False), (8194, 7, True), (20012, 9, True),
                                        (50000, 4, True), (33334, 600, True)])
-def test_eval_score_in_one_call(T, B, timed, fused, tuning):
-    """The fused kernel forced onto every shape it is compiled for (one tile, tile edges, ragged last tiles,
-    fewer plans than workgroups and several plans per workgroup), the two kernels one after the other, and the
-    library's own choice: the same outputs as the oracle's evaluation followed by its scores."""
-    tuning("step_fused", fused)
+def test_eval_score_in_one_call(T, B, timed, handover, wide, tuning):
+    """The evaluation and the scoring back to back (one tile, tile edges, ragged last tiles, fewer and more plans than CUs),
+    with the maxima of the rows' blocks handed over and with the rows read, in small and in large scoring workgroups: the
+    same outputs as the oracle's evaluation followed by its scores."""
+    tuning("step_fused", handover)
+    tuning("score_wide", wide)
     N = max(2, min(400, T // 2))
     tas = small_random_tas(6000 + T, N=N, T=T, max_acc=5 if T > 8 else 1, timed=timed, base_bytes=21, link_bytes_per_us=400_000)
     pl = make_plans(tas, B, 17, p_swap=0.5)
-    say(f"eval+score T={T} B={B} timed={timed} fused={fused} K={pl.n_intervals}")
-    n = check_step(tas, pl, label=f"T={T} fused={fused}")
+    say(f"eval+score T={T} B={B} timed={timed} handover={handover} wide={wide} K={pl.n_intervals}")
+    n = check_step(tas, pl, label=f"T={T} handover={handover}")
     assert n > 0 or T <= 8
 
 
-def test_eval_score_in_one_call_long_and_empty_plans(tuning):
-    """Plans that do not fit the registers of the evaluation phase (it takes them through the form that re-reads
-    its list per tile), empty plans, and peaks in different buckets of the candidate index from plan to plan."""
-    tuning("step_fused", 1)
+@pytest.mark.parametrize("form", [dict(eval_threads=256), dict(eval_threads=512), dict(eval_threads=1024), dict(eval_threads=512, eval_segments=3),
+                                  dict(eval_threads=1024, eval_segments=2), dict(eval_threads=512, eval_binned=1),
+                                  dict(eval_threads=1024, eval_binned=1, eval_segments=3), dict(eval_threads=1024, eval_binned=1, eval_nt=1),
+                                  dict(eval_threads=512, eval_persistent=1, eval_segments=1, eval_slots=3),
+                                  dict(eval_threads=1024, eval_persistent=1, eval_segments=1, eval_slots=3),
+                                  dict(eval_threads=1024, eval_nt=1), dict(eval_threads=1024, eval_r=8)], ids=str)
+def test_eval_score_hand_over_of_every_form(form, tuning):
+    """Every form of the evaluation kernel hands over the maxima of its rows' 256-step blocks: lengths around blocks and tiles,
+    odd and even (8- and 16-byte stores), empty plans, and plans too long for the registers, which another kernel takes.
+    On the plateau sequences every score depends on these maxima."""
+    for knob, v in form.items():
+        tuning(knob, v)
+    for T in (255, 256, 257, 2047, 2049, 4096, 4097, 8191, 8193, 16640, 20011):
+        tas = small_random_tas(6300 + T, N=min(300, T // 2), T=T, max_acc=5, timed=True, base_bytes=T, link_bytes_per_us=400_000)
+        base = make_plans(tas, 11, 17, p_swap=0.5)
+        lists = [repeated(base, b, len(base.plan(b)[0])) for b in range(base.B)]
+        lists[3] = lists[10] = []
+        if T > 4097:
+            lists[0], lists[6] = repeated(base, 0, 2100), repeated(base, 6, 9000)
+        pl = plans_from_lists(lists)
+        say(f"hand-over {form} T={T} K={pl.n_intervals}")
+        assert check_step(tas, pl, label=f"{form} T={T}") > 0
+    for T in (4000, 9001):
+        tas = plateau_tas(T, 90)
+        pl = plans_from_lists([[], [(95, 101, T // 2 + 3)], [(1, T // 2 - 2, T // 2 + 9)], [(45, 90, T // 3)], []])
+        say(f"hand-over {form} plateau T={T}")
+        assert check_step(tas, pl, label=f"{form} plateau T={T}") > 180
+
+
+def test_eval_score_in_one_call_long_and_empty_plans():
+    """Plans that do not fit the registers of the evaluation, empty plans, and peaks in different buckets of the candidate index
+    from plan to plan."""
     tas = small_random_tas(6100, N=400, T=24576, max_acc=6, timed=True, link_bytes_per_us=400_000)
     base = make_plans(tas, 14, 19, p_swap=0.6)
-    lists = []
-    for b in range(base.B):
-        t, o, r, k = base.plan(b)
-        one = [(int(t[j]), int(o[j]), int(r[j]), int(k[j])) for j in range(len(t))]
-        if b in (2, 9):
-            one = (one * (9000 // len(one) + 1))[:2100 + 700 * b]      # 3500 and 8400 intervals
-        if b in (0, 5, 13):
-            one = []
-        lists.append(one)
+    lists = [repeated(base, b, len(base.plan(b)[0])) for b in range(base.B)]
+    for b in (2, 9):
+        lists[b] = repeated(base, b, 2100 + 700 * b)                   # 3500 and 8400 intervals
+    for b in (0, 5, 13):
+        lists[b] = []
     pl = plans_from_lists(lists)
-    say(f"eval+score fused, long and empty plans: {[len(x) for x in lists]}")
+    say(f"eval+score, long and empty plans: {[len(x) for x in lists]}")
     assert check_step(tas, pl, label="long and empty") > 0
 
 
-def test_eval_score_in_one_call_falls_back(tuning):
-    """Shapes the fused kernel is not compiled for (odd T, sizes beyond 32 bits) run the two kernels even when the
-    fused one is asked for; the scoring-only outputs may be left out."""
-    tuning("step_fused", 1)
+def test_eval_score_in_one_call_odd_rows_wide_sizes_and_left_out_outputs():
+    """Odd T, sizes beyond 32 bits; the minimum and the windows may be left out."""
     tas = small_random_tas(6200, N=300, T=20011, max_acc=5, timed=True, link_bytes_per_us=400_000)
     check_step(tas, make_plans(tas, 6, 3, p_swap=0.5), label="odd T")
     tas = small_random_tas(6201, N=300, T=20012, max_acc=5, timed=True, max_size=1 << 36, link_bytes_per_us=1 << 24)
