@@ -63,18 +63,18 @@ namespace {
 // steps: 512 threads, 512 blocks, three per CU (streaming 4,096 rows of 24,000 steps 336 us, with 256 threads 381; 50,000
 // steps 2.62 ms and 2.69).  Longer rows: 256 threads, 1,024 blocks, four per CU, plans dealt to as many workgroups as are
 // resident (10^6 steps 2.04 ms; with 512 threads 2.17).
-template <int tab, int thr, int eu, bool stream>
+template <int tab, int thr, int eu, int bufs, bool stream>
 struct Shape {
     static constexpr int kTab = tab, kThr = thr, kWaves = thr / 64;
-    static constexpr int kBufs = kWaves / 2;     // wavefronts that read the row's blocks for the open entries
+    static constexpr int kBufs = bufs;           // wavefronts that read the row's blocks for the open entries: as many as the LDS has room for
     static constexpr int kEu = eu;               // wavefronts per SIMD that fit
     static constexpr bool kStream = stream;      // rows read and outputs written past the L2's allocation
 };
-typedef Shape<128, 256, 6, false> Small;
-typedef Shape<512, 512, 6, false> Short;
-typedef Shape<1024, 256, 4, true> Long;
-typedef Shape<1024, 1024, 4, false> Wide;
-typedef Shape<1024, 1024, 4, true> WideStream;
+typedef Shape<128, 256, 6, 3, false> Small;
+typedef Shape<512, 512, 6, 5, false> Short;
+typedef Shape<1024, 256, 4, 2, true> Long;
+typedef Shape<1024, 1024, 4, 16, false> Wide;
+typedef Shape<1024, 1024, 4, 16, true> WideStream;
 constexpr int64_t kWideStreamBytes = int64_t{192} << 20;
 
 struct StageBuf {
