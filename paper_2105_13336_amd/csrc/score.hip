@@ -52,7 +52,9 @@ namespace {
 // covers the chains of its phases: 1024 threads and 1,024 blocks (of as many pieces of 256 steps as it takes).  Scoring by
 // itself, against 512 threads (rows up to 131,072 steps) or 256 (longer ones): 256 plans of 24,000 steps 32.7 -> 27.0 us, of
 // 50,000 steps 56.8 -> 45.6, 32 of 300,000 steps 161 -> 61, one of 10^6 steps 487 -> 152; evaluation and scoring in one call,
-// against 256 threads, 32 plans of 6,000 steps 25.6 -> 21.3; more pieces ahead than two gain nothing.  Not where four wavefronts
+// against 256 threads, 32 plans of 6,000 steps 25.6 -> 21.3; more pieces ahead than two gain nothing.  The rest of the LDS holds
+// a copy of the bucket's entries, which the cancelling looks at again and again when a plan's list is in no order (256 ragged,
+// shuffled plans of 50,000 steps 56 -> 48 us).  Not where four wavefronts
 // have a piece of work each and more would idle (60 tensors, 200 steps: 64 plans 15.9 us with 1024 threads, 15.7 with 256; 534 tensors,
 // 1,000 steps: 18.9 and 19.1).  Rows of more bytes
 // than the memory-side cache keeps (256 MB) are read past the L2's allocation there: 32 plans of 10^6 steps 236 -> 213 us,
@@ -63,18 +65,19 @@ namespace {
 // steps: 512 threads, 512 blocks, three per CU (streaming 4,096 rows of 24,000 steps 336 us, with 256 threads 381; 50,000
 // steps 2.62 ms and 2.69).  Longer rows: 256 threads, 1,024 blocks, four per CU, plans dealt to as many workgroups as are
 // resident (10^6 steps 2.04 ms; with 512 threads 2.17).
-template <int tab, int thr, int eu, int bufs, bool stream>
+template <int tab, int thr, int eu, int bufs, int entries, bool stream>
 struct Shape {
     static constexpr int kTab = tab, kThr = thr, kWaves = thr / 64;
     static constexpr int kBufs = bufs;           // wavefronts that read the row's blocks for the open entries: as many as the LDS has room for
     static constexpr int kEu = eu;               // wavefronts per SIMD that fit
+    static constexpr int kEntries = entries;     // entries of the bucket that are copied to the LDS for the cancelling
     static constexpr bool kStream = stream;      // rows read and outputs written past the L2's allocation
 };
-typedef Shape<128, 256, 6, 3, false> Small;
-typedef Shape<512, 512, 6, 5, false> Short;
-typedef Shape<1024, 256, 4, 2, true> Long;
-typedef Shape<1024, 1024, 4, 16, false> Wide;
-typedef Shape<1024, 1024, 4, 16, true> WideStream;
+typedef Shape<128, 256, 6, 3, 0, false> Small;
+typedef Shape<512, 512, 6, 5, 0, false> Short;
+typedef Shape<1024, 256, 4, 2, 0, true> Long;
+typedef Shape<1024, 1024, 4, 16, 4096, false> Wide;
+typedef Shape<1024, 1024, 4, 16, 4096, true> WideStream;
 constexpr int64_t kWideStreamBytes = int64_t{192} << 20;
 
 struct StageBuf {
@@ -96,6 +99,7 @@ struct ScoreLds {
     uint32_t filter[kFilterWords];
     int32_t filter_base[kFilterWords + 1];
     uint32_t need[S::kTab / 32];         // blocks of the row that open entries lie in
+    __attribute__((aligned(16))) int4 entries[S::kEntries ? S::kEntries : 1];   // the bucket's, if that many hold them
 };
 
 // Step 1: the maxima of the row's blocks into pm[k + 1] and sm[k].  The blocks are dealt round-robin, so that
@@ -226,6 +230,11 @@ __device__ __forceinline__ void score_plan(const ScoreArgs &a, const int32_t b, 
     for (int32_t k = tid; k < kWindow / 64 && k * 64 < n_e; k += kThr) L.cancelled[k] = 0;
     for (int32_t k = tid; k * 32 < a.n_blk; k += kThr) L.need[k] = 0;
     if (tid == 0) L.open.n = 0;
+    const bool copied = n_e <= S::kEntries;
+    if constexpr (S::kEntries > 0) {
+        if (copied)
+            for (int32_t k = tid; k < n_e; k += kThr) L.entries[k] = entries[k];
+    }
     if constexpr (kTable) load_block_maxima<S>(a, a.blk_max + static_cast<int64_t>(b) * a.n_mini, L.mx, tid);
     else stream_block_maxima<kVec, S>(a, MF, L.mx, wave, lane);
     PROF_MARK(0);
@@ -233,7 +242,15 @@ __device__ __forceinline__ void score_plan(const ScoreArgs &a, const int32_t b, 
     PROF_MARK(1);
     scan_block_maxima(L.mx, a.n_blk, wave, lane);
     PROF_MARK(2);
-    cancel_by_plan<kThr>(a, k0, k1, entries, n_e, 0, n_e < kWindow ? n_e : kWindow, L.filter, L.filter_base, reinterpret_cast<uint32_t *>(L.cancelled), tid);
+    auto cancel_from = [&](const int4 *list) {
+        cancel_by_plan<kThr>(a, k0, k1, list, n_e, 0, n_e < kWindow ? n_e : kWindow, L.filter, L.filter_base, reinterpret_cast<uint32_t *>(L.cancelled), tid);
+    };
+    if constexpr (S::kEntries > 0) {
+        if (copied) cancel_from(L.entries);
+        else cancel_from(entries);
+    } else {
+        cancel_from(entries);
+    }
     PROF_MARK(3);
     __syncthreads();
     PROF_MARK(4);

@@ -861,10 +861,10 @@ def test_score_candidates_that_block_maxima_leave_open(T, n_big, wide, tuning):
         assert check_score_recompute(tas, pl, label=f"open T={T}") > 2 * n_big
 
 
-@pytest.mark.parametrize("N,acc", [(8191, 1), (8192, 1), (8193, 1), (16384, 1), (16385, 1), (20000, 1), (300, 60)])
+@pytest.mark.parametrize("N,acc", [(4096, 1), (4097, 1), (8191, 1), (8192, 1), (8193, 1), (16384, 1), (16385, 1), (20000, 1), (300, 60)])
 def test_score_buckets_of_many_entries(N, acc):
-    """Buckets with one entry less than there are flags for (8192), as many, one more, two windows of them and one more, three;
-    tensors with many gaps in one bucket (an interval then cancels an entry behind its tensor's first)."""
+    """Buckets with as many entries as are copied to the LDS (4096) and one more; one less than there are flags for (8192), as
+    many, one more, two windows of them and one more, three; tensors with many gaps in one bucket (an interval then cancels an entry behind its tensor's first)."""
     T = 700
     i = np.arange(N)
     alloc = prng.randint(79, 1, i, 0, 249)
