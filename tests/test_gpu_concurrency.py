@@ -93,6 +93,48 @@ def test_two_threads_two_streams_one_handle(tuning):
     h.close()
 
 
+def test_one_call_steps_of_two_threads_on_one_handle():
+    """Evaluation and scoring in one call from two host threads on two streams: what the one kernel hands to the other lives in
+    the stream's workspace, which grows from batch to batch."""
+    tas = small_random_tas(7003, N=700, T=12_001, max_acc=5, timed=True, link_bytes_per_us=400_000)
+    batches = [[make_plans(tas, B, 31 + B, p_swap=0.4) for B in sizes] for sizes in ((5, 300, 40), (270, 9, 600))]
+    say("one-call steps on two streams")
+    want = [[(*O.eval_plans(tas, pl), O.score_plans(tas, pl, *O.eval_plans(tas, pl)[:3])) for pl in mine] for mine in batches]
+    h = P.tas_load(tas)
+    got, errors = [[], []], []
+    start = threading.Barrier(2)
+
+    def worker(k):
+        try:
+            torch.cuda.set_device(0)
+            s = torch.cuda.Stream()
+            with torch.cuda.stream(s):
+                dps = [P.DevicePlans.from_numpy(pl.plan_offsets, pl.iv_tensor, pl.iv_out, pl.iv_in, pl.iv_kind) for pl in batches[k]]
+                outs = [[torch.empty(shape, dtype=dt, device="cuda") for shape, dt in
+                         (((dp.B, tas.T), torch.int64), ((dp.B,), torch.int64), ((dp.B,), torch.int32), ((dp.B,), torch.int64),
+                          ((dp.B, tas.N), torch.int64), ((dp.B, tas.N), torch.int32), ((dp.B, tas.N), torch.int32))] for dp in dps]
+                start.wait()
+                for _ in range(8):
+                    for dp, out in zip(dps, outs):
+                        P.tensile_eval_score_plans(h, dp, *out, stream=s)
+                s.synchronize()
+                got[k] = [[x.cpu().numpy() for x in out] for out in outs]
+        except Exception as e:      # noqa: BLE001 - reported below
+            errors.append(e)
+
+    threads = [threading.Thread(target=worker, args=(k,)) for k in range(2)]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    assert not errors, errors
+    for k in range(2):
+        for b, (r0, p0, a0, m0, scores) in enumerate(want[k]):
+            for j, (g, w) in enumerate(zip(got[k][b], (r0, p0, a0, m0, *scores))):
+                assert np.array_equal(g, w), f"thread {k}, batch {b}, output {j}"
+    h.close()
+
+
 def test_greedy_next_to_a_batch_on_another_stream():
     """tensile_greedy_plan works on the default stream while a batch is evaluated over and over on another."""
     tas = small_random_tas(7002, N=200, T=9001, max_acc=5, timed=True, link_bytes_per_us=300_000)

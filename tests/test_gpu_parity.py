@@ -1271,6 +1271,23 @@ def test_greedy_random_timed():
 
 # ------------------------------------------------------------------ validate
 
+@pytest.mark.parametrize("T", [131_072, 131_073, 262_144, 262_145, 300_002])
+def test_greedy_long_rows(T):
+    """Rows of as many blocks of 256 steps as the planner's table holds (262,144 steps) and of larger blocks: peaks, scores and
+    placements of both phases, candidates that the table leaves open among them."""
+    tas = plateau_tas(T, 40)
+    say(f"greedy long rows T={T}")
+    h = P.tas_load(tas)
+    same_greedy(P.tensile_greedy_plan(h, 0, max_iters=25, capacity=64, recompute=True), O.greedy(tas, 0, max_iters=25, recompute=True))
+    h.close()
+    tas = small_random_tas(1700 + T % 97, N=120, T=T, max_acc=6, timed=True, link_bytes_per_us=400_000)
+    h = P.tas_load(tas)
+    g = P.tensile_greedy_plan(h, 0, max_iters=60, capacity=64, recompute=True)
+    same_greedy(g, O.greedy(tas, 0, max_iters=60, recompute=True))
+    assert len(g["iv_tensor"]) > 10
+    h.close()
+
+
 def test_validate_plans(configs_small):
     tas = configs_small[1]
     h = P.tas_load(tas)
