@@ -158,7 +158,9 @@ void drop_greedy_cache(const tensile_tas *tas) {
 
 using namespace tensile;
 
-extern "C" int tensile_greedy_plan(const tensile_tas *tas, int64_t budget_bytes, const tensile_greedy_opts *opts,
+// (aligned to a cache line: the host's passes over the candidates' records are short loops, and where they fall within a line should not
+// depend on what is linked in front - 256 iterations on 24,000 steps 4.67 ms at 16 bytes past a line, 4.60 here)
+extern "C" __attribute__((aligned(64))) int tensile_greedy_plan(const tensile_tas *tas, int64_t budget_bytes, const tensile_greedy_opts *opts,
                                    int32_t capacity, int32_t n_initial, int32_t *iv_tensor, int32_t *iv_out,
                                    int32_t *iv_in, uint8_t *iv_kind, int32_t *n_intervals, int64_t *peak_trace,
                                    int64_t *final_peak) {
