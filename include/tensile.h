@@ -369,7 +369,8 @@ int tensile_greedy_plan(const tensile_tas *tas, int64_t budget_bytes, const tens
  *                     kernel at hand, -1 (default) for rows whose unscheduled timeline exceeds 1 MiB
  *   "eval_r"          intervals per thread kept in registers (0 = automatic)
  *   "score_blocks"    size of the scoring grid (0 = automatic)
- *   "score_wide"      scoring workgroups of 1024 threads: 0 never, 1 always (-1 = for no more plans than CUs)
+ *   "score_wide"      scoring workgroups of 1024 threads: 0 never, 1 always (-1 = for no more plans than CUs, unless there
+ *                     is little to do for each)
  *   "link_packed"     0: every transfer is searched for in the cumulative latencies (1 = automatic)
  *   "step_fused"      0: in tensile_eval_score_plans the scoring reads the rows, as tensile_score_candidates does; else it
  *                     takes the maxima of the rows' 256-step blocks from the evaluation
